@@ -65,6 +65,8 @@ def _kernel_name(rec, mixed):
         return "k_bl_eval<%s, false>" % ("true" if mixed else "false")
     if rec["kind"] == 1:
         return "k_eval_small%s<%d, false>" % ("_mixed" if mixed else "", rec["ipl"])
+    if rec["block"] == 512:
+        return "k_eval_wg<2, %d, false>" % rec["ipl"]
     if mixed:
         return "k_eval_mixed<%d, %d, false>" % (rec["block"], rec["ipl"])
     return "k_eval_f64<2, %d, %d, false>" % (rec["block"], rec["ipl"])

@@ -39,23 +39,6 @@ __device__ __forceinline__ void comp_merge(double &s, double &c, double s2, doub
     c += err + c2;
 }
 
-// Sum of a compensated pair over the 64 lanes of a wave by a fixed
-// butterfly (both partners merge lower-lane value first), so the result is
-// the same on every run; every lane ends with the total.
-__device__ __forceinline__ void wave_comp_sum(double &s, double &c) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double s2 = __shfl_xor(s, off, 64);
-        const double c2 = __shfl_xor(c, off, 64);
-        double a = (lane & off) ? s2 : s, ac = (lane & off) ? c2 : c;
-        const double b = (lane & off) ? s : s2, bc = (lane & off) ? c : c2;
-        comp_merge(a, ac, b, bc);
-        s = a;
-        c = ac;
-    }
-}
-
 // A double moved across lanes by a DPP lane pattern (both 32-bit halves);
 // lanes of rows outside ROWS get 0.
 template <int CTRL, int ROWS = 0xF>

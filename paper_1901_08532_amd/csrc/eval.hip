@@ -25,6 +25,7 @@
 #include <climits>
 
 #include "eval_body.h"
+#include "eval_wg_body.h"
 
 namespace h6 {
 namespace {
@@ -38,6 +39,27 @@ __attribute__((amdgpu_waves_per_eu(IPL == 1 ? 4 : 2))) void k_eval_f64(
     OutPtrs out, int64_t slice_stride) {
     eval_tile_body<ORDER, BLOCK, IPL, SKIPSELF>(src, active, n, n_act, eps2, slice_len, out,
                                                 slice_stride, blockIdx.x, blockIdx.y);
+}
+
+// Evaluation by whole workgroups (eval_wg_body.h): target group blockIdx.x,
+// source slice blockIdx.y.
+template <int ORDER, int TGT, bool SKIPSELF>
+__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_wg(
+    SrcPtrs src, const int32_t *__restrict__ active, int n, int n_act, double eps2, int slice_len,
+    OutPtrs out, int64_t slice_stride) {
+    using T = Traits<ORDER>;
+    __shared__ double2 pool[wg_pool<ORDER>()];
+    __shared__ double fs[TGT * T::NACC];
+    const int g = blockIdx.x, jb = (int)blockIdx.y * slice_len;
+    wg_sums<ORDER, TGT, SKIPSELF>(PredSrc{src, active}, n_act, eps2, g, jb, min(n, jb + slice_len),
+                                  pool, fs);
+    const int k = g * TGT + (int)threadIdx.x;
+    if ((int)threadIdx.x < TGT && k < n_act) {
+#pragma unroll
+        for (int q = 0; q < T::NACC; ++q)
+            out.p[T::OUT0 + q][(int64_t)blockIdx.y * slice_stride + k] =
+                fs[threadIdx.x * T::NACC + q];
+    }
 }
 
 // Slice reduction, few slices: one thread per (component, target), a
@@ -68,33 +90,41 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const double *__restrict_
     }
 }
 
-// Slice reduction, many slices: one wave per (component, target). Each lane
-// sums every 64th slice (Neumaier), then a fixed butterfly of compensated
-// merges combines the lanes, so the result does not depend on timing.
-__global__ __launch_bounds__(256) void k_reduce_slices_wave(const double *__restrict__ partial,
-                                                            int64_t ld, int n_split, int ncomp,
-                                                            int out0, int n_act, OutPtrs out,
-                                                            unsigned acc_mask) {
-    const int lane = threadIdx.x & 63;
+// Slice reduction, many slices: 64 consecutive outputs per workgroup, one a
+// lane (coalesced), each wave summing every kRedWaves-th slice (Neumaier);
+// the waves' pairs are then merged in order.
+constexpr int kRedWaves = 8;
+__global__ __launch_bounds__(64 * kRedWaves) void k_reduce_slices_many(
+    const double *__restrict__ partial, int n_split, int ncomp, int out0, int n_act, OutPtrs out,
+    unsigned acc_mask) {
+    __shared__ double2 part[64 * kRedWaves];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t total = (int64_t)ncomp * n_act;
-    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
-    for (int64_t idx = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); idx < total;
-         idx += waves) {
-        const int c = (int)(idx / n_act);
-        const int k = (int)(idx - (int64_t)c * n_act);
-        double s = 0.0, comp = 0.0;
-        for (int sl = lane; sl < n_split; sl += 64) {
-            const double x = partial[((int64_t)sl * ncomp + c) * ld + k];
-            const double t = s + x;
-            comp += fabs(s) >= fabs(x) ? (s - t) + x : (x - t) + s;
+    const int64_t idx = (int64_t)blockIdx.x * 64 + lane;
+    const double *__restrict__ p = partial + (idx < total ? idx : total - 1);
+    double s = 0.0, comp = 0.0;
+    for (int s0 = w; s0 < n_split; s0 += 8 * kRedWaves) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int sl = s0 + u * kRedWaves;
+            x[u] = sl < n_split ? p[(int64_t)sl * total] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const double t = s + x[u];
+            comp += fabs(s) >= fabs(x[u]) ? (s - t) + x[u] : (x[u] - t) + s;
             s = t;
         }
-        wave_comp_sum(s, comp);
-        if (lane == 0) {
-            double *dst = &out.p[out0 + c][k];
-            *dst = ((acc_mask >> c) & 1u) ? *dst + (s + comp) : s + comp;
-        }
     }
+    part[threadIdx.x] = make_double2(s, comp);
+    __syncthreads();
+    if (w != 0 || idx >= total) return;
+#pragma unroll
+    for (int q = 1; q < kRedWaves; ++q) comp_merge(s, comp, part[q * 64 + lane].x, part[q * 64 + lane].y);
+    const int c = (int)(idx / n_act);
+    double *dst = &out.p[out0 + c][idx - (int64_t)c * n_act];
+    *dst = ((acc_mask >> c) & 1u) ? *dst + (s + comp) : s + comp;
 }
 
 template <int TPW, bool SKIPSELF>
@@ -162,10 +192,38 @@ hipError_t dispatch_small(int tpw, bool skipself, dim3 grid, hipStream_t st, con
     return hipErrorInvalidValue;
 }
 
-// Above this many slices the reduction gives each output a whole wave.
-constexpr int kWaveReduceMinSplit = 24;
+template <int ORDER>
+hipError_t dispatch_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                       const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                       const OutPtrs &out, int64_t slice_stride) {
+#define H6_WG(T)                                                                                \
+    if (tgt == T) {                                                                             \
+        if (skipself)                                                                           \
+            hipLaunchKernelGGL((k_eval_wg<ORDER, T, true>), grid, dim3(kWgThreads), 0, st, src, \
+                               active, n, n_act, eps2, slice_len, out, slice_stride);           \
+        else                                                                                    \
+            hipLaunchKernelGGL((k_eval_wg<ORDER, T, false>), grid, dim3(kWgThreads), 0, st,     \
+                               src, active, n, n_act, eps2, slice_len, out, slice_stride);      \
+        return hipGetLastError();                                                               \
+    }
+    H6_WG(1)
+    H6_WG(2)
+    H6_WG(4)
+    H6_WG(8)
+    H6_WG(16)
+    H6_WG(32)
+#undef H6_WG
+    return hipErrorInvalidValue;
+}
+
+// From this many slices the reduction splits them over waves.
+constexpr int kManyReduceMinSplit = 16;
 // Active sets up to this size use the source-parallel kernel by default.
 constexpr int kDefaultSmallMax = 32;
+// Active sets up to this size use the whole-workgroup kernel (FP64); beyond,
+// the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets
+// 252 against 254 us, all 495 against 468).
+constexpr int kWgMaxAct = 8192;
 // Waves a launch aims to put in flight (256 CUs x 4 SIMDs x 2).
 constexpr int kTargetWaves = 2048;
 // Shortest source slice of the source-parallel kernel (4 sources per lane).
@@ -204,6 +262,47 @@ int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_
     return best;
 }
 
+// Shape of the whole-workgroup kernel: targets per workgroup and source
+// slices, the cheapest by a price in microseconds fitted to a sweep of both
+// (n 256 to 65536, n_act 1 to n; the priced shape within 10% of the best
+// measured, mostly within 4%). A CU takes c = ceil(workgroups / CUs) of them;
+// one issues for `issue` (two waves a SIMD, 216 cycles a pair step) and waits
+// about 0.7 us a tile, which a second workgroup on the CU hides. With few
+// targets a group, a wave reads more distinct LDS records a step (kWgShare).
+// Slices cost a second launch and their traffic.
+EvalConfig choose_wg(h6_ctx ctx, int order, int n, int n_act) {
+    static const float kWgShare[6] = {1.3f, 1.25f, 1.2f, 1.12f, 1.05f, 1.0f};
+    static const int kSplits[14] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
+    const int ncomp = order == 2 ? 9 : 6;
+    EvalConfig cfg;
+    cfg.kind = 0;
+    cfg.block = kWgThreads;
+    cfg.ipl = 1;
+    cfg.n_split = 1;
+    float best = 3.0e38f;
+    for (int l = 0; l < 6; ++l) {
+        const int tgt = 1 << l, strands = kWgThreads / tgt;
+        const int groups = ceil_div(n_act, tgt);
+        for (int sp : kSplits) {
+            if (sp > 1 && (n / sp < 64 || (int64_t)sp * ncomp * n_act > ctx->partial_cap)) break;
+            const int slice = ceil_div(ceil_div(n, sp), 64) * 64;
+            const int eff = ceil_div(n, slice);
+            const float c = (float)ceil_div((int64_t)groups * eff, ctx->n_cu);
+            const int tiles = ceil_div(slice, kWgThreads);
+            const int steps = slice / kWgThreads * tgt + ceil_div(slice % kWgThreads, strands);
+            const float issue = 0.196f * (float)steps;
+            float cost = std::max(c * issue * kWgShare[l], issue + 0.7f * (float)tiles) + 1.2f * c;
+            if (eff > 1) cost += 1.2f + (float)eff * (float)n_act * 3.6e-5f;
+            if (cost < best) {
+                best = cost;
+                cfg.ipl = tgt;
+                cfg.n_split = eff;
+            }
+        }
+    }
+    return cfg;
+}
+
 EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n_act) {
     EvalConfig cfg;
     if (order == 2 && (precision == H6_EX || precision == H6_SP)) {
@@ -220,6 +319,9 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
         cfg.n_split = split < 1 ? 1 : split;
         return cfg;
     }
+    // a launch shape forced by h6_set_eval_config takes the kernels it names
+    if (precision == H6_FP64 && n_act <= kWgMaxAct && !(order == 2 && eval_shape_forced(ctx)))
+        return choose_wg(ctx, order, n, n_act);
     const int small_max = ctx->cfg_small >= 0 ? ctx->cfg_small : kDefaultSmallMax;
     if (order == 2 && n_act <= small_max) {
         // source-parallel kernel: one wave per TPW targets
@@ -277,8 +379,10 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
     if (n_act <= 0) return hipSuccess;
     EvalConfig cfg = choose_eval_config(ctx, order, precision, n, n_act);
     // equal slices, each a whole number of tiles
+    const bool wg = cfg.kind == 0 && cfg.block == kWgThreads;
+    const int unit = wg ? 64 : cfg.block;  // whole tiles (64 for kind 1 and the workgroup kernel)
     int slice_len = ceil_div(n, cfg.n_split);
-    slice_len = ceil_div(slice_len, cfg.block) * cfg.block;  // whole tiles (64 for kind 1)
+    slice_len = ceil_div(slice_len, unit) * unit;
     cfg.n_split = ceil_div(n, slice_len);
     if (used) *used = cfg;
 
@@ -314,6 +418,17 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
         dim3 g(ceil_div(n_act, cfg.ipl), cfg.n_split);
         e = dispatch_small(cfg.ipl, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
                            slice_len, dst, slice_stride);
+    } else if (wg) {
+        dim3 g(ceil_div(n_act, cfg.ipl), cfg.n_split);
+        if (order == 1)
+            e = dispatch_wg<1>(cfg.ipl, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
+                               slice_len, dst, slice_stride);
+        else if (order == 2)
+            e = dispatch_wg<2>(cfg.ipl, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
+                               slice_len, dst, slice_stride);
+        else
+            e = dispatch_wg<3>(cfg.ipl, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
+                               slice_len, dst, slice_stride);
     } else if (order == 1)
         e = dispatch_shape<1>(cfg, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
                               slice_len, dst, slice_stride);
@@ -332,11 +447,9 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
 hipError_t launch_reduce(h6_ctx ctx, int n_split, int ncomp, int out0, int n_act,
                          const OutPtrs &out, unsigned acc_mask) {
     const int64_t total = (int64_t)ncomp * n_act;
-    if (n_split >= kWaveReduceMinSplit) {
-        int rb = ceil_div(total, 4);
-        if (rb > 8192) rb = 8192;
-        hipLaunchKernelGGL(k_reduce_slices_wave, dim3(rb), dim3(256), 0, ctx->stream, ctx->partial,
-                           (int64_t)n_act, n_split, ncomp, out0, n_act, out, acc_mask);
+    if (n_split >= kManyReduceMinSplit) {
+        hipLaunchKernelGGL(k_reduce_slices_many, dim3(ceil_div(total, 64)), dim3(64 * kRedWaves), 0,
+                           ctx->stream, ctx->partial, n_split, ncomp, out0, n_act, out, acc_mask);
     } else {
         int rb = ceil_div(total, 256);
         if (rb > 4096) rb = 4096;

@@ -67,6 +67,64 @@ __device__ __forceinline__ void pair_acc2(double dx, double dy, double dz, doubl
     acc[8] = fma(mr3, uz, acc[8]);
 }
 
+// Pair terms of order 1 (a, j) accumulated into acc[0..5].
+__device__ __forceinline__ void pair_acc1(double dx, double dy, double dz, double dvx, double dvy,
+                                          double dvz, double r2, double mj, double *acc) {
+    const double rinv = rsqrt_f64(r2);
+    const double rinv2 = rinv * rinv;
+    const double mr3 = (mj * rinv) * rinv2;
+    const double rv = fma(dz, dvz, fma(dy, dvy, dx * dvx));
+    const double a3 = 3.0 * (rv * rinv2);
+    // w = v - 3 alpha r, so that J = mr3 w
+    const double wx = fma(-a3, dx, dvx), wy = fma(-a3, dy, dvy), wz = fma(-a3, dz, dvz);
+    acc[0] = fma(mr3, dx, acc[0]);
+    acc[1] = fma(mr3, dy, acc[1]);
+    acc[2] = fma(mr3, dz, acc[2]);
+    acc[3] = fma(mr3, wx, acc[3]);
+    acc[4] = fma(mr3, wy, acc[4]);
+    acc[5] = fma(mr3, wz, acc[5]);
+}
+
+// Pair terms of order 3 (s, c) accumulated into acc[0..5].
+__device__ __forceinline__ void pair_acc3(double dx, double dy, double dz, double dvx, double dvy,
+                                          double dvz, double dax, double day, double daz,
+                                          double djx, double djy, double djz, double r2, double mj,
+                                          double *acc) {
+    const double rinv = rsqrt_f64(r2);
+    const double rinv2 = rinv * rinv;
+    const double mr3 = (mj * rinv) * rinv2;
+    const double rv = fma(dz, dvz, fma(dy, dvy, dx * dvx));
+    const double alpha = rv * rinv2;
+    const double a3 = 3.0 * alpha;
+    const double wx = fma(-a3, dx, dvx), wy = fma(-a3, dy, dvy), wz = fma(-a3, dz, dvz);
+    // v.v + r.a
+    const double vvra =
+        fma(dz, daz, fma(dy, day, fma(dx, dax, fma(dvz, dvz, fma(dvy, dvy, dvx * dvx)))));
+    const double beta = fma(alpha, alpha, vvra * rinv2);
+    const double b3 = 3.0 * beta;
+    const double a6 = a3 + a3;
+    // u = a - 6 alpha w - 3 beta r, so that S = mr3 u
+    const double ux = fma(-a6, wx, fma(-b3, dx, dax));
+    const double uy = fma(-a6, wy, fma(-b3, dy, day));
+    const double uz = fma(-a6, wz, fma(-b3, dz, daz));
+    const double va = fma(dvz, daz, fma(dvy, day, dvx * dax));
+    const double rj = fma(dz, djz, fma(dy, djy, dx * djx));
+    // gamma = (3 v.a + r.j)/R^2 + alpha (3 beta - 4 alpha^2)
+    const double gamma =
+        fma(alpha, fma(-4.0 * alpha, alpha, b3), fma(3.0, va, rj) * rinv2);
+    const double a9 = 3.0 * a3, b9 = 3.0 * b3, g3 = 3.0 * gamma;
+    // z = jr - 9 alpha u - 9 beta w - 3 gamma r, so that C = mr3 z
+    const double zx = fma(-a9, ux, fma(-b9, wx, fma(-g3, dx, djx)));
+    const double zy = fma(-a9, uy, fma(-b9, wy, fma(-g3, dy, djy)));
+    const double zz = fma(-a9, uz, fma(-b9, wz, fma(-g3, dz, djz)));
+    acc[0] = fma(mr3, ux, acc[0]);
+    acc[1] = fma(mr3, uy, acc[1]);
+    acc[2] = fma(mr3, uz, acc[2]);
+    acc[3] = fma(mr3, zx, acc[3]);
+    acc[4] = fma(mr3, zy, acc[4]);
+    acc[5] = fma(mr3, zz, acc[5]);
+}
+
 // Far, massless padding source: contributes exactly zero.
 constexpr double kPadPos = 1.0e18;
 
@@ -94,6 +152,61 @@ struct PredSrc {
     }
     __device__ __forceinline__ double mass(int p) const { return src.m[p]; }
 };
+
+// Source record of particle jj (NREC double2: x0 x1 | x2 m | v0 v1 | v2 a0 |
+// a1 a2 | j0 j1 | j2 -, order 1 ending with v2 -), and the far, massless
+// padding record.
+template <int ORDER, class SRC>
+__device__ __forceinline__ void load_rec(const SRC &S, int jj, double2 *rec) {
+    double xs[3], vs[3], as[3], js[3];
+    S.template get<ORDER>(jj, xs, vs, as, js);
+    rec[0] = make_double2(xs[0], xs[1]);
+    rec[1] = make_double2(xs[2], S.mass(jj));
+    rec[2] = make_double2(vs[0], vs[1]);
+    if (ORDER == 1) {
+        rec[3] = make_double2(vs[2], 0.0);
+    } else {
+        rec[3] = make_double2(vs[2], as[0]);
+        rec[4] = make_double2(as[1], as[2]);
+    }
+    if (ORDER == 3) {
+        rec[5] = make_double2(js[0], js[1]);
+        rec[6] = make_double2(js[2], 0.0);
+    }
+}
+template <int ORDER>
+__device__ __forceinline__ void pad_rec(double2 *rec) {
+    rec[0] = make_double2(kPadPos, kPadPos);
+    rec[1] = make_double2(kPadPos, 0.0);
+#pragma unroll
+    for (int q = 2; q < Traits<ORDER>::NREC; ++q) rec[q] = make_double2(0.0, 0.0);
+}
+
+// Pair terms of one source record and one target, added to acc; self: the
+// record is the target itself (masked when SKIPSELF).
+template <int ORDER, bool SKIPSELF>
+__device__ __forceinline__ void pair_terms(const double2 *rec, const double *xi, const double *vi,
+                                           const double *ai, const double *ji, double eps2,
+                                           bool self, double *acc) {
+    const double dx = rec[0].x - xi[0], dy = rec[0].y - xi[1], dz = rec[1].x - xi[2];
+    const double dvx = rec[2].x - vi[0], dvy = rec[2].y - vi[1], dvz = rec[3].x - vi[2];
+    double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
+    double m_eff = rec[1].y;
+    if (SKIPSELF) {
+        r2 = self ? 1.0 : r2;
+        m_eff = self ? 0.0 : m_eff;
+    }
+    if constexpr (ORDER == 1) {
+        pair_acc1(dx, dy, dz, dvx, dvy, dvz, r2, m_eff, acc);
+    } else if constexpr (ORDER == 2) {
+        pair_acc2(dx, dy, dz, dvx, dvy, dvz, rec[3].y - ai[0], rec[4].x - ai[1],
+                  rec[4].y - ai[2], r2, m_eff, acc);
+    } else {
+        pair_acc3(dx, dy, dz, dvx, dvy, dvz, rec[3].y - ai[0], rec[4].x - ai[1],
+                  rec[4].y - ai[2], rec[5].x - ji[0], rec[5].y - ji[1], rec[6].x - ji[2], r2,
+                  m_eff, acc);
+    }
+}
 
 // Body of the target-parallel LDS-tiled evaluation for the workgroup that
 // owns target block ib (BLOCK * IPL targets) and source slice sl.
@@ -137,28 +250,10 @@ __device__ __forceinline__ void eval_tile_body(const SRC &S, int n, int n_act, d
     // padding past the slice end)
     auto fetch = [&](int jt, double2 *rec) {
         const int jj = jt + tid;
-        if (jj < je) {
-            double xs[3], vs[3], as[3], js[3];
-            S.template get<ORDER>(jj, xs, vs, as, js);
-            rec[0] = make_double2(xs[0], xs[1]);
-            rec[1] = make_double2(xs[2], S.mass(jj));
-            rec[2] = make_double2(vs[0], vs[1]);
-            if (ORDER == 1) {
-                rec[3] = make_double2(vs[2], 0.0);
-            } else {
-                rec[3] = make_double2(vs[2], as[0]);
-                rec[4] = make_double2(as[1], as[2]);
-            }
-            if (ORDER == 3) {
-                rec[5] = make_double2(js[0], js[1]);
-                rec[6] = make_double2(js[2], 0.0);
-            }
-        } else {
-            rec[0] = make_double2(kPadPos, kPadPos);
-            rec[1] = make_double2(kPadPos, 0.0);
-#pragma unroll
-            for (int q = 2; q < NREC; ++q) rec[q] = make_double2(0.0, 0.0);
-        }
+        if (jj < je)
+            load_rec<ORDER>(S, jj, rec);
+        else
+            pad_rec<ORDER>(rec);
     };
     constexpr bool kAhead = AHEAD && IPL == 1 && ORDER == 2;
     double2 ahead[NREC];
@@ -214,55 +309,12 @@ __device__ __forceinline__ void eval_tile_body(const SRC &S, int n, int n_act, d
                 if constexpr (ORDER == 2) {
                     pair_acc2(dx, dy, dz, dvx, dvy, dvz, aj0 - ai[u][0], aj1 - ai[u][1],
                               aj2 - ai[u][2], r2, m_eff, acc[u]);
+                } else if constexpr (ORDER == 1) {
+                    pair_acc1(dx, dy, dz, dvx, dvy, dvz, r2, m_eff, acc[u]);
                 } else {
-                    const double rinv = rsqrt_f64(r2);
-                    const double rinv2 = rinv * rinv;
-                    const double mr3 = (m_eff * rinv) * rinv2;
-                    const double rv = fma(dz, dvz, fma(dy, dvy, dx * dvx));
-                    const double alpha = rv * rinv2;
-                    const double a3 = 3.0 * alpha;
-                    // w = v - 3 alpha r, so that J = mr3 w
-                    const double wx = fma(-a3, dx, dvx), wy = fma(-a3, dy, dvy),
-                                 wz = fma(-a3, dz, dvz);
-                    if constexpr (ORDER == 1) {
-                        acc[u][0] = fma(mr3, dx, acc[u][0]);
-                        acc[u][1] = fma(mr3, dy, acc[u][1]);
-                        acc[u][2] = fma(mr3, dz, acc[u][2]);
-                        acc[u][3] = fma(mr3, wx, acc[u][3]);
-                        acc[u][4] = fma(mr3, wy, acc[u][4]);
-                        acc[u][5] = fma(mr3, wz, acc[u][5]);
-                    } else {
-                        const double dax = aj0 - ai[u][0], day = aj1 - ai[u][1],
-                                     daz = aj2 - ai[u][2];
-                        const double djx = jj0 - ji[u][0], djy = jj1 - ji[u][1],
-                                     djz = jj2 - ji[u][2];
-                        // v.v + r.a
-                        const double vvra = fma(dz, daz, fma(dy, day, fma(dx, dax,
-                                            fma(dvz, dvz, fma(dvy, dvy, dvx * dvx)))));
-                        const double beta = fma(alpha, alpha, vvra * rinv2);
-                        const double b3 = 3.0 * beta;
-                        const double a6 = a3 + a3;
-                        // u = a - 6 alpha w - 3 beta r, so that S = mr3 u
-                        const double ux = fma(-a6, wx, fma(-b3, dx, dax));
-                        const double uy = fma(-a6, wy, fma(-b3, dy, day));
-                        const double uz = fma(-a6, wz, fma(-b3, dz, daz));
-                        const double va = fma(dvz, daz, fma(dvy, day, dvx * dax));
-                        const double rj = fma(dz, djz, fma(dy, djy, dx * djx));
-                        // gamma = (3 v.a + r.j)/R^2 + alpha (3 beta - 4 alpha^2)
-                        const double gamma = fma(alpha, fma(-4.0 * alpha, alpha, b3),
-                                                 fma(3.0, va, rj) * rinv2);
-                        const double a9 = 3.0 * a3, b9 = 3.0 * b3, g3 = 3.0 * gamma;
-                        // z = jr - 9 alpha u - 9 beta w - 3 gamma r, so that C = mr3 z
-                        const double zx = fma(-a9, ux, fma(-b9, wx, fma(-g3, dx, djx)));
-                        const double zy = fma(-a9, uy, fma(-b9, wy, fma(-g3, dy, djy)));
-                        const double zz = fma(-a9, uz, fma(-b9, wz, fma(-g3, dz, djz)));
-                        acc[u][0] = fma(mr3, ux, acc[u][0]);
-                        acc[u][1] = fma(mr3, uy, acc[u][1]);
-                        acc[u][2] = fma(mr3, uz, acc[u][2]);
-                        acc[u][3] = fma(mr3, zx, acc[u][3]);
-                        acc[u][4] = fma(mr3, zy, acc[u][4]);
-                        acc[u][5] = fma(mr3, zz, acc[u][5]);
-                    }
+                    pair_acc3(dx, dy, dz, dvx, dvy, dvz, aj0 - ai[u][0], aj1 - ai[u][1],
+                              aj2 - ai[u][2], jj0 - ji[u][0], jj1 - ji[u][1], jj2 - ji[u][2], r2,
+                              m_eff, acc[u]);
                 }
             }
         }

@@ -54,6 +54,7 @@ inline bool self_pair_masked(double eps2, int precision) {
 // ---- device-resident block loop (blockloop.hip)
 constexpr int kLevels = kTickBits + 1;  // levels 0..40: step 2^-level
 constexpr int kSmall2Max = 48;          // largest active set of the source-parallel kinds
+constexpr int kWgBlock = 512;     // workgroup of the whole-workgroup kernels (targets: EvalConfig::ipl)
 constexpr int kExtBlock = 64;           // workgroup of the EX and SP kernels (one target per lane)
 
 // Plan of one block, written by the plan of the block before (double
@@ -192,6 +193,10 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
 // bit c of acc_mask adds to the existing value instead of overwriting.
 hipError_t launch_reduce(h6_ctx ctx, int n_split, int ncomp, int out0, int n_act,
                          const OutPtrs &out, unsigned acc_mask);
+// Whether h6_set_eval_config named a launch shape.
+inline bool eval_shape_forced(h6_ctx ctx) {
+    return ctx->cfg_block || ctx->cfg_ipl || ctx->cfg_split || ctx->cfg_small >= 0;
+}
 int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_i);
 // Mixed-precision order-2 kernels (eval_mixed.hip), launched with the shape
 // chosen for the FP64 kernels.
@@ -209,6 +214,13 @@ hipError_t launch_predict(h6_ctx ctx, const h6_state *st, int n, int64_t t_tick,
 hipError_t launch_correct(h6_ctx ctx, h6_state *st, const int32_t *active, int n_act,
                           const h6_force *f, int64_t t_next, double dt, const h6_params *prm,
                           bool shared);
+// One shared step of a small system in one kernel (shared_step.hip): reads
+// the predicted sources src, corrects st, and either predicts the next step
+// into out or, for the last one, writes the forces to f. shared_step_targets:
+// the targets a workgroup takes.
+int shared_step_targets(h6_ctx ctx, int n);
+hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
+                              bool predict, const h6_pred *out, const h6_force *f);
 hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, int lev_min,
                                 int lev_max);
 hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *active);
