@@ -6,6 +6,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <utility>
 
 #include "h6_internal.h"
 
@@ -750,6 +751,39 @@ int h6_run_blocks(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, cons
     return run_blocks_device(ctx, st, n, pred, f, active, prm, t_end, stats);
 }
 
+// Systems up to this size take one kernel a shared step.
+constexpr int64_t kSharedStepMax = 8192;
+
+// Shared steps of a small system, one kernel each after the first prediction.
+// The predicted arrays alternate between the caller's and the context's
+// scratch so that the last step's are the caller's, as with separate kernels.
+static int shared_steps_small(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
+                              const h6_force *f, double dt, int64_t nsteps) {
+    h6_pred other;  // 9 n doubles of the partial sums' 18 n_max
+    for (int c = 0; c < 3; ++c) {
+        other.x[c] = ctx->partial + c * n;
+        other.v[c] = ctx->partial + (3 + c) * n;
+        other.a[c] = ctx->partial + (6 + c) * n;
+    }
+    const h6_pred *cur = (nsteps & 1) ? pred : &other, *next = (nsteps & 1) ? &other : pred;
+    H6_TRY(ctx, launch_predict(ctx, st, (int)n, 0, dt, true, cur), "predict");
+    for (int64_t k = 0; k < nsteps; ++k) {
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        if (ctx->prof) H6_TRY(ctx, prof_begin(ctx, &ev0, &ev1), "profile event");
+        H6_TRY(ctx,
+               launch_shared_step(ctx, st, (int)n, src_from_pred(cur, st->m), dt, k + 1 < nsteps,
+                                  next, f),
+               "shared step");
+        if (ctx->prof) {
+            const EvalConfig cfg = {0, kWgBlock, shared_step_targets(ctx, (int)n), 1};
+            H6_TRY(ctx, prof_end(ctx, ev0, ev1, 2, cfg, H6_FP64, n, (double)n * (double)n),
+                   "profile event");
+        }
+        std::swap(cur, next);
+    }
+    return H6_OK;
+}
+
 int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, const h6_force *f,
                     double dt, int64_t nsteps, int precision) {
     if (!ctx) return H6_EINVAL;
@@ -757,6 +791,8 @@ int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, co
     if (int rc = check_n(ctx, n)) return rc;
     if (!std::isfinite(dt) || dt <= 0.0 || nsteps < 0) return fail_arg(ctx, "bad dt or step count");
     if (!precision_ok(precision)) return fail_arg(ctx, "bad precision");
+    if (nsteps > 0 && precision == H6_FP64 && n <= kSharedStepMax && !eval_shape_forced(ctx))
+        return shared_steps_small(ctx, st, n, pred, f, dt, nsteps);
     for (int64_t k = 0; k < nsteps; ++k) {
         H6_TRY(ctx, launch_predict(ctx, st, (int)n, 0, dt, true, pred), "predict");
         H6_TRY(ctx,

@@ -95,6 +95,20 @@ __device__ __forceinline__ OldState load_old(const h6_state &st, int i) {
     return o;
 }
 
+// Corrected x1, v1 and interpolated crackle c1 of one component over step h,
+// from the derivatives at both ends.
+__device__ __forceinline__ void correct_comp(double h, double h2, double hinv3, double x0,
+                                             double v0, double a0, double j0, double s0, double a1,
+                                             double j1, double s1, double &x1, double &v1,
+                                             double &c1) {
+    // v1 = v0 + h/2 (a0 + a1) - h^2/10 (j1 - j0) + h^3/120 (s0 + s1)
+    v1 = v0 + h * fma(h, fma(h * (1.0 / 120.0), s0 + s1, -0.1 * (j1 - j0)), 0.5 * (a0 + a1));
+    // x1 = x0 + h/2 (v0 + v1) - h^2/10 (a1 - a0) + h^3/120 (j0 + j1)
+    x1 = x0 + h * fma(h, fma(h * (1.0 / 120.0), j0 + j1, -0.1 * (a1 - a0)), 0.5 * (v0 + v1));
+    // third derivative at the end of the quintic through (a, j, s) at both ends
+    c1 = fma(h2, 9.0 * s1 - 3.0 * s0, fma(-h, fma(24.0, j0, 36.0 * j1), 60.0 * (a1 - a0))) * hinv3;
+}
+
 // 6th-order Hermite corrector, quintic interpolation of crackle, pop and
 // the fifth derivative at the step end, and the power-of-two step rule.
 // Computes, for a particle with old state o and the new a1, j1, s1 (fa, fj,
@@ -119,15 +133,9 @@ __device__ __forceinline__ void correct_from(const OldState &o, const double *fa
         const double x0 = o.x[c], v0 = o.v[c];
         const double a0 = o.a[c], j0 = o.j[c], s0 = o.s[c];
         const double a1 = fa[c], j1 = fj[c], s1 = fs[c];
-        // v1 = v0 + h/2 (a0 + a1) - h^2/10 (j1 - j0) + h^3/120 (s0 + s1)
-        const double v1 =
-            v0 + h * fma(h, fma(h * (1.0 / 120.0), s0 + s1, -0.1 * (j1 - j0)), 0.5 * (a0 + a1));
-        // x1 = x0 + h/2 (v0 + v1) - h^2/10 (a1 - a0) + h^3/120 (j0 + j1)
-        const double x1 =
-            x0 + h * fma(h, fma(h * (1.0 / 120.0), j0 + j1, -0.1 * (a1 - a0)), 0.5 * (v0 + v1));
+        double x1, v1, c1;
+        correct_comp(h, h2, hinv3, x0, v0, a0, j0, s0, a1, j1, s1, x1, v1, c1);
         const double da = a1 - a0;
-        // derivatives of the quintic through (a, j, s) at both ends, at the end
-        const double c1 = fma(h2, 9.0 * s1 - 3.0 * s0, fma(-h, fma(24.0, j0, 36.0 * j1), 60.0 * da)) * hinv3;
         x1o[c] = x1;
         v1o[c] = v1;
         c1o[c] = c1;
