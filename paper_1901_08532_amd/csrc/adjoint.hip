@@ -646,97 +646,184 @@ __global__ __launch_bounds__(256) void k_predict_block_vjp(h6_state cot, int n,
     }
 }
 
-// Potential of each particle, phi_i = -sum_{j != i} m_j / sqrt(r^2 + eps^2):
-// one target per lane over LDS tiles of (x, m), compensated per tile.
-constexpr int kPotBlock = 256;
-__global__ __launch_bounds__(kPotBlock) void k_potential(h6_state st, int n, double eps2,
-                                                         double *__restrict__ phi) {
-    __shared__ double4 tile[kPotBlock];
-    const int tid = threadIdx.x;
-    const int i = (int)blockIdx.x * kPotBlock + tid;
-    const int ic = i < n ? i : n - 1;
-    const double xi = st.x[0][ic], yi = st.x[1][ic], zi = st.x[2][ic];
-    double hi = 0.0, lo = 0.0;
-    for (int jt = 0; jt < n; jt += kPotBlock) {
-        __syncthreads();
-        const int jj = jt + tid;
-        tile[tid] = jj < n ? make_double4(st.x[0][jj], st.x[1][jj], st.x[2][jj], st.m[jj])
-                           : make_double4(kPadPosVjp, kPadPosVjp, kPadPosVjp, 0.0);
-        __syncthreads();
-        double acc = 0.0;
-        const int cnt = min(kPotBlock, n - jt);
-        for (int q = 0; q < cnt; ++q) {
-            const double4 t = tile[q];
-            const double dx = t.x - xi, dy = t.y - yi, dz = t.z - zi;
-            const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-            const bool self = jt + q == ic;
-            acc = fma(self ? 0.0 : t.w, rsqrt_f64(self ? 1.0 : r2), acc);
-        }
-        two_sum_into(hi, lo, acc);
+// Potential of each particle, phi_i = -sum_{j != i} m_j / sqrt(r^2 + eps^2),
+// and with GRAD the gradient of the total energy E = sum_i m_i |v_i|^2 / 2 -
+// sum_{i<j} m_i m_j (r_ij^2 + eps^2)^(-1/2) scaled by its cotangent g (one
+// device double; NULL: 1): dE/dx_i = -m_i a_i with a_i the softened
+// acceleration, dE/dv_i = m_i v_i, dE/dm_i = |v_i|^2 / 2 + phi_i; phi and a
+// share each pair's r^2 and 1/sqrt.
+//
+// Bound by FP64 issue (about 20 operations a pair). A workgroup of 512
+// threads takes 2 TG targets, two a thread, with 512 / TG strands over the
+// sources of each LDS tile, so that a small system fills the GPU (one target
+// per thread over all sources left 192 of 256 CUs idle at n = 16384) and two
+// pairs share an LDS record. The self test is made only in the tiles that
+// hold targets of the group. With
+// GRAD, n = 16384: 986 -> 190 us (25 TFLOP/s at 18 operations a pair, FMA 2).
+constexpr int kPotThreads = 512;
+constexpr int kPotPerSum = 16;  // strand sums one thread adds in the final reduction
+template <int TG, bool GRAD>
+__global__ __launch_bounds__(kPotThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_potential(
+    h6_state st, int n, double eps2, const double *__restrict__ cot, double *__restrict__ phi,
+    h6_state out) {
+    constexpr int NACC = GRAD ? 4 : 1;  // phi, a
+    constexpr int STR = kPotThreads / TG;
+    constexpr int LD = STR + 1;
+    constexpr int kTileLen = 2 * kPotThreads + 64;  // double2: (x, y), (z, m); the sums need a little more
+    static_assert(NACC * TG * LD <= 2 * kTileLen, "strand sums fit the tile");
+    __shared__ double2 tile[kTileLen];
+    __shared__ double fs[2 * TG][NACC];
+    const int tid = threadIdx.x, t = tid % TG, s = tid / TG;
+    const int k0 = (int)blockIdx.x * 2 * TG;
+    int id[2];
+    double xi[2][3], acc[2][NACC], hi[2][NACC], lo[2][NACC];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int k = k0 + u * TG + t;
+        id[u] = k < n ? k : n - 1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) xi[u][c] = st.x[c][id[u]];
+#pragma unroll
+        for (int q = 0; q < NACC; ++q) acc[u][q] = hi[u][q] = lo[u][q] = 0.0;
     }
-    if (i < n) phi[i] = -(hi + lo);
+    auto flush = [&]() {
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int q = 0; q < NACC; ++q) {
+                two_sum_into(hi[u][q], lo[u][q], acc[u][q]);
+                acc[u][q] = 0.0;
+            }
+    };
+    int since = 0;
+    for (int jt = 0; jt < n; jt += kPotThreads) {
+        if (jt) __syncthreads();
+        const int jj = jt + tid;
+        const bool in = jj < n;
+        tile[tid] = in ? make_double2(st.x[0][jj], st.x[1][jj]) : make_double2(kPadPosVjp, kPadPosVjp);
+        tile[kPotThreads + tid] =
+            in ? make_double2(st.x[2][jj], st.m[jj]) : make_double2(kPadPosVjp, 0.0);
+        __syncthreads();
+        const int steps = (min(kPotThreads, n - jt) + STR - 1) / STR;
+        auto pairs = [&](auto test_self) {
+#pragma unroll 2
+            for (int i = 0; i < steps; ++i) {
+                const int e = i * STR + s;
+                const double2 xy = tile[e], zm = tile[kPotThreads + e];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const double dx = xy.x - xi[u][0], dy = xy.y - xi[u][1], dz = zm.x - xi[u][2];
+                    double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
+                    double mj = zm.y;
+                    if (decltype(test_self)::value) {
+                        const bool self = jt + e == id[u];
+                        r2 = self ? 1.0 : r2;
+                        mj = self ? 0.0 : mj;
+                    }
+                    const double rinv = rsqrt_f64(r2);
+                    if constexpr (GRAD) {
+                        const double mr = mj * rinv;
+                        const double mr3 = mr * (rinv * rinv);
+                        acc[u][0] += mr;
+                        acc[u][1] = fma(mr3, dx, acc[u][1]);
+                        acc[u][2] = fma(mr3, dy, acc[u][2]);
+                        acc[u][3] = fma(mr3, dz, acc[u][3]);
+                    } else {
+                        acc[u][0] = fma(mj, rinv, acc[u][0]);
+                    }
+                }
+            }
+        };
+        // targets past the end repeat particle n - 1
+        if (jt < k0 + 2 * TG && (jt + kPotThreads > k0 || jt + kPotThreads >= n))
+            pairs(std::true_type{});
+        else
+            pairs(std::false_type{});
+        since += TG;
+        if (since >= 64) {
+            since = 0;
+            flush();
+        }
+    }
+    flush();
+    double *red = reinterpret_cast<double *>(tile);
+    constexpr int G = STR / kPotPerSum;  // threads per sum
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NACC; ++q) red[(q * TG + t) * LD + s] = hi[u][q] + lo[u][q];
+        __syncthreads();
+        const int o = tid / G, gl = tid % G;
+        const bool mine = o < NACC * TG;
+        double hs = 0.0, hc = 0.0;
+        if (mine) {
+#pragma unroll
+            for (int i = 0; i < kPotPerSum; ++i) two_sum_into(hs, hc, red[o * LD + gl + i * G]);
+        }
+        seg_comp_reduce_n<1>(&hs, &hc, G);
+        if (mine && gl == G - 1) fs[u * TG + o % TG][o / TG] = hs + hc;
+    }
+    __syncthreads();
+    const int i = k0 + tid;
+    if (tid >= 2 * TG || i >= n) return;
+    if constexpr (GRAD) {
+        const double g = cot ? *cot : 1.0;
+        const double mi = st.m[i];
+        double vv = 0.0;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const double vc = st.v[c][i];
+            vv = fma(vc, vc, vv);
+            out.x[c][i] = -g * (mi * fs[tid][1 + c]);
+            out.v[c][i] = g * (mi * vc);
+        }
+        out.m[i] = g * fma(0.5, vv, -fs[tid][0]);
+    } else {
+        phi[i] = -fs[tid][0];
+    }
 }
 
-// Gradient of the total energy E = sum_i m_i |v_i|^2 / 2 - sum_{i<j} m_i m_j
-// (r_ij^2 + eps^2)^(-1/2) scaled by its cotangent g (one device double; NULL:
-// 1): dE/dx_i = -m_i a_i with a_i the softened acceleration, dE/dv_i =
-// m_i v_i, dE/dm_i = |v_i|^2 / 2 + phi_i with phi_i the potential. One target
-// per lane over LDS tiles of (x, m); phi and a share each pair's r^2 and
-// 1/sqrt, compensated per tile.
-__global__ __launch_bounds__(kPotBlock) void k_energy_vjp(h6_state st, int n, double eps2,
-                                                          const double *__restrict__ cot,
-                                                          h6_state out) {
-    __shared__ double4 tile[kPotBlock];
-    const int tid = threadIdx.x;
-    const int i = (int)blockIdx.x * kPotBlock + tid;
-    const int ic = i < n ? i : n - 1;
-    const double xi = st.x[0][ic], yi = st.x[1][ic], zi = st.x[2][ic];
-    double hi[4] = {0.0, 0.0, 0.0, 0.0}, lo[4] = {0.0, 0.0, 0.0, 0.0};  // phi, a
-    for (int jt = 0; jt < n; jt += kPotBlock) {
-        __syncthreads();
-        const int jj = jt + tid;
-        tile[tid] = jj < n ? make_double4(st.x[0][jj], st.x[1][jj], st.x[2][jj], st.m[jj])
-                           : make_double4(kPadPosVjp, kPadPosVjp, kPadPosVjp, 0.0);
-        __syncthreads();
-        double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        const int cnt = min(kPotBlock, n - jt);
-        for (int q = 0; q < cnt; ++q) {
-            const double4 t = tile[q];
-            const double dx = t.x - xi, dy = t.y - yi, dz = t.z - zi;
-            const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-            const bool self = jt + q == ic;
-            const double rinv = rsqrt_f64(self ? 1.0 : r2);
-            const double mr = (self ? 0.0 : t.w) * rinv;
-            const double mr3 = mr * (rinv * rinv);
-            acc[0] += mr;
-            acc[1] = fma(mr3, dx, acc[1]);
-            acc[2] = fma(mr3, dy, acc[2]);
-            acc[3] = fma(mr3, dz, acc[3]);
+// Thread targets TG (a power of two): the rounds of workgroups a CU takes
+// times the length of one, which per target is longer with few targets (more
+// distinct LDS records a wave reads, kShare, measured at n = 65536 in units
+// of TG = 16: 7212, 4759, 3562, 3063, 2790, 2710 us for TG 1 .. 32). The
+// choice is the fastest TG at n = 1024 to 100000 (ten sizes), or within 3%.
+template <bool GRAD>
+hipError_t launch_pot(h6_ctx ctx, const h6_state *st, int n, const double *cot, double *phi,
+                      h6_state *out) {
+    static const float kShare[6] = {2.6f, 1.71f, 1.28f, 1.10f, 1.0f, 0.97f};
+    const h6_state none = {};
+    int tg = 1;
+    float best = 3.0e38f;
+    for (int l = 0; l < 6; ++l) {
+        const int rounds = ceil_div_i(ceil_div_i(n, 2 << l), ctx->n_cu);
+        const float cost = (float)rounds * (float)(1 << l) * kShare[l] * (rounds == 1 ? 1.08f : 1.0f);
+        if (cost < best) {
+            best = cost;
+            tg = 1 << l;
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) two_sum_into(hi[q], lo[q], acc[q]);
     }
-    if (i >= n) return;
-    const double g = cot ? *cot : 1.0;
-    const double mi = st.m[i];
-    double vv = 0.0;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double vc = st.v[c][i];
-        vv = fma(vc, vc, vv);
-        out.x[c][i] = -g * (mi * (hi[1 + c] + lo[1 + c]));
-        out.v[c][i] = g * (mi * vc);
-    }
-    out.m[i] = g * fma(0.5, vv, -(hi[0] + lo[0]));
+    const dim3 grid((n + 2 * tg - 1) / (2 * tg));
+#define H6_POT(T)                                                                             \
+    if (tg == T)                                                                              \
+        hipLaunchKernelGGL((k_potential<T, GRAD>), grid, dim3(kPotThreads), 0, ctx->stream,   \
+                           *st, n, ctx->eps2, cot, phi, out ? *out : none);
+    H6_POT(1)
+    H6_POT(2)
+    H6_POT(4)
+    H6_POT(8)
+    H6_POT(16)
+    H6_POT(32)
+#undef H6_POT
+    return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_energy_vjp(h6_ctx ctx, const h6_state *st, int n, const double *cot,
                              h6_state *out) {
-    hipLaunchKernelGGL(k_energy_vjp, dim3((n + kPotBlock - 1) / kPotBlock), dim3(kPotBlock), 0,
-                       ctx->stream, *st, n, ctx->eps2, cot, *out);
-    return hipGetLastError();
+    return launch_pot<true>(ctx, st, n, cot, nullptr, out);
 }
 
 hipError_t launch_eval_vjp(h6_ctx ctx, int order, const SrcPtrs &src, const double *const *cot,
@@ -789,9 +876,7 @@ hipError_t launch_predict_block_vjp(h6_ctx ctx, h6_state *cot, int n, const int6
 }
 
 hipError_t launch_potential(h6_ctx ctx, const h6_state *st, int n, double *phi) {
-    hipLaunchKernelGGL(k_potential, dim3((n + kPotBlock - 1) / kPotBlock), dim3(kPotBlock), 0,
-                       ctx->stream, *st, n, ctx->eps2, phi);
-    return hipGetLastError();
+    return launch_pot<false>(ctx, st, n, nullptr, phi, nullptr);
 }
 
 }  // namespace h6

@@ -20,11 +20,6 @@ static __device__ __align__(256) double scratch[H6_NOALLOC_SCRATCH_BYTES / sizeo
 
 namespace {
 
-// Pinned host staging: [0, 16) block readback, [64, 68) flags,
-// [128, 168) energy, two block-loop descriptor slots.
-constexpr size_t kHostBytes = 2048;
-constexpr size_t kHostSlot0 = 1024;
-constexpr size_t kHostSlot1 = 1536;
 static_assert(sizeof(LoopDesc) <= kHostSlot1 - kHostSlot0 && kHostSlot1 + sizeof(LoopDesc) <= kHostBytes,
               "descriptor slots");
 
@@ -108,7 +103,7 @@ OutPtrs out_from_force(const h6_force *f) {
 }
 
 int read_flags(h6_ctx ctx) {
-    int32_t *h = (int32_t *)((char *)ctx->host + 64);
+    int32_t *h = (int32_t *)((char *)ctx->host + kHostFlags);
     H6_TRY(ctx, hipMemcpyAsync(h, ctx->flags, sizeof(int32_t), hipMemcpyDeviceToHost, ctx->stream),
            "flag readback");
     H6_TRY(ctx, hipMemsetAsync(ctx->flags, 0, sizeof(int32_t), ctx->stream), "flag reset");
@@ -321,12 +316,13 @@ int h6_create(h6_ctx *out, int64_t n_max, double eps, void *hip_stream) {
               hipMalloc(&ctx->sched32, sizeof(int32_t) * (1 + 2 * ctx->sched_blocks)) == hipSuccess &&
               hipMalloc(&ctx->counters, sizeof(unsigned) * 8) == hipSuccess &&
               hipMalloc(&ctx->flags, sizeof(int32_t) * 4) == hipSuccess &&
-              hipMalloc(&ctx->ered, sizeof(double) * (8 + 10 * eb)) == hipSuccess &&
+              hipMalloc(&ctx->ered, sizeof(double) * 10 * eb) == hipSuccess &&
               hipMalloc(&ctx->bl_desc, 2 * sizeof(LoopDesc)) == hipSuccess &&
               hipMalloc(&ctx->bl_scr, sizeof(LoopScratch)) == hipSuccess &&
               hipEventCreateWithFlags(&ctx->bl_ev[0], hipEventDisableTiming) == hipSuccess &&
               hipEventCreateWithFlags(&ctx->bl_ev[1], hipEventDisableTiming) == hipSuccess &&
-              hipHostMalloc(&ctx->host, kHostBytes, hipHostMallocDefault) == hipSuccess;
+              hipHostMalloc(&ctx->host, kHostBytes, hipHostMallocDefault) == hipSuccess &&
+              hipHostGetDevicePointer(&ctx->host_dev, ctx->host, 0) == hipSuccess;
     if (ok) {
         ok = hipMemset(ctx->counters, 0, sizeof(unsigned) * 8) == hipSuccess &&
              hipMemset(ctx->flags, 0, sizeof(int32_t) * 4) == hipSuccess &&
@@ -543,11 +539,8 @@ int h6_next_block(h6_ctx ctx, const h6_state *st, int64_t n, int32_t *active, in
     if (!st || !st->t || !st->dt || !active || !t_next || !n_act) return fail_arg(ctx, "null pointer");
     if (int rc = check_n(ctx, n)) return rc;
     H6_TRY(ctx, launch_next_block(ctx, st, (int)n, active), "next block");
-    int64_t *h64 = (int64_t *)ctx->host;
-    H6_TRY(ctx,
-           hipMemcpyAsync(h64, ctx->sched64, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream),
-           "block readback");
     H6_TRY(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
+    const int64_t *h64 = (const int64_t *)((const char *)ctx->host + kHostBlock);
     *t_next = h64[0];
     *n_act = h64[1];
     if (!ctx->pending.empty()) H6_TRY(ctx, prof_resolve(ctx), "profile events");
@@ -809,11 +802,8 @@ int h6_energy(h6_ctx ctx, const h6_state *st, int64_t n, double out[5]) {
     if (!state_ok(st, false) || !out) return fail_arg(ctx, "null pointer");
     if (int rc = check_n(ctx, n)) return rc;
     H6_TRY(ctx, launch_energy(ctx, st, (int)n), "energy");
-    double *h = (double *)((char *)ctx->host + 128);
-    H6_TRY(ctx, hipMemcpyAsync(h, ctx->ered, 5 * sizeof(double), hipMemcpyDeviceToHost, ctx->stream),
-           "energy readback");
     H6_TRY(ctx, hipStreamSynchronize(ctx->stream), "synchronize");
-    std::memcpy(out, h, 5 * sizeof(double));
+    std::memcpy(out, (const char *)ctx->host + kHostEnergy, 5 * sizeof(double));
     return H6_OK;
 }
 

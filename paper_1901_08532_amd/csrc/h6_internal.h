@@ -15,6 +15,15 @@ namespace h6 {
 constexpr int64_t kMaxParticles = (int64_t)1 << 30;
 constexpr int kTickBits = H6_TICK_BITS;
 
+// Pinned host buffer: block time and count, status flags, energy and
+// angular momentum, two block-loop descriptors.
+constexpr size_t kHostBytes = 2048;
+constexpr size_t kHostBlock = 0;
+constexpr size_t kHostFlags = 64;
+constexpr size_t kHostEnergy = 128;
+constexpr size_t kHostSlot0 = 1024;
+constexpr size_t kHostSlot1 = 1536;
+
 // Device status flags (bit set in ctx->flags[0]).
 constexpr int kFlagDtMin = 1;
 constexpr int kFlagNonFinite = 2;
@@ -147,8 +156,10 @@ struct h6_ctx_s {
     int32_t *flags = nullptr;      // status bits
     double *ered = nullptr;        // energy partials
     int64_t sched_blocks = 0;      // capacity of the scheduler arrays
-    // pinned host staging for scheduler/energy readback
+    // pinned host memory: scheduler and energy results (written by their
+    // kernels through host_dev, its device address), readbacks
     void *host = nullptr;
+    void *host_dev = nullptr;
     std::string last_error;
     // device-resident block loop
     h6::LoopDesc *bl_desc = nullptr;     // device, [2]

@@ -133,13 +133,14 @@ __device__ __forceinline__ int block_sum_i32(int v) {
     return r;
 }
 
-// out[0] = t_next, out[1] = n_act (the 16 bytes the host reads back)
+// out[0] = t_next, out[1] = n_act; host_out (pinned host memory) the same
 __global__ __launch_bounds__(kSchedThreads) void k_sched_select(const int64_t *__restrict__ t,
                                                                 const int64_t *__restrict__ dt,
                                                                 int n, int64_t *chunk_min,
                                                                 int32_t *chunk_cnt,
                                                                 int32_t *chunk_off,
-                                                                unsigned *counter, int64_t *out) {
+                                                                unsigned *counter, int64_t *out,
+                                                                int64_t *host_out) {
     const int base = blockIdx.x * kSchedChunk;
     const int end = min(n, base + kSchedChunk);
     int64_t v = INT64_MAX;
@@ -170,8 +171,8 @@ __global__ __launch_bounds__(kSchedThreads) void k_sched_select(const int64_t *_
             chunk_off[b] = has ? run : -1;
             run += has ? load_agent(&chunk_cnt[b]) : 0;
         }
-        out[0] = r;
-        out[1] = run;
+        out[0] = host_out[0] = r;
+        out[1] = host_out[1] = run;
     }
 }
 
@@ -209,7 +210,9 @@ __global__ __launch_bounds__(kSchedThreads) void k_sched_compact(const int64_t *
 
 // ---------------------------------------------------------------- energy
 constexpr int kEnergyThreads = 256;
-constexpr int kEnergyMaxSplit = 16;  // source slices per target block
+constexpr int kEnergyBlock = 2 * kEnergyThreads;  // targets of a block, two a thread
+constexpr int kEnergyUnit = 64;                   // sources a slice boundary falls on
+constexpr int kEnergyMaxSplit = 64;               // source slices per pair of blocks
 
 __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e) {
     s = a + b;
@@ -218,14 +221,16 @@ __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e
 }
 
 // Potential energy W = -sum over pairs i < j of m_i m_j / sqrt(r^2+eps^2),
-// each pair once: target block b (kEnergyThreads particles, one per thread)
-// meets the source tiles t >= b, and in its own tile only the sources
-// j > i. Blocks b and nb-1-b share a workgroup, so that every workgroup has
-// nb + 1 tiles of work (the middle block of an odd nb alone has fewer); the
-// tiles are cut into gridDim.y slices. Sums over a tile are plain, over
-// tiles compensated. Kinetic m v^2/2 and angular momentum m x cross v of
-// the workgroup's particles are taken by the first slice. Workgroup sums as
+// each pair once: target block b (kEnergyBlock particles, two per thread)
+// meets the sources from its own first one on, and among its own only the
+// sources j > i. Blocks b and nb-1-b share a workgroup, so that every
+// workgroup has about as many sources; these are cut into gridDim.y slices
+// of whole units of kEnergyUnit. Sums over a tile are plain, over tiles
+// compensated. Kinetic m v^2/2 and angular momentum m x cross v of the
+// workgroup's particles are taken by the first slice. Workgroup sums as
 // compensated (hi, lo) trees; the last workgroup adds them in order.
+// Bound by FP64 issue (about 13 operations a pair); with one target a thread
+// the two LDS reads a pair bounded it instead (n = 16384: 101 -> 69 us).
 __global__ __launch_bounds__(kEnergyThreads) void k_energy(h6_state st, int n, double eps2,
                                                            double *partial, unsigned *counter,
                                                            double *out) {
@@ -233,76 +238,84 @@ __global__ __launch_bounds__(kEnergyThreads) void k_energy(h6_state st, int n, d
     __shared__ double red_hi[5][kEnergyThreads];
     __shared__ double red_lo[5][kEnergyThreads];
     const int tid = threadIdx.x;
-    const int nb = (n + kEnergyThreads - 1) / kEnergyThreads;
+    const int nb = (n + kEnergyBlock - 1) / kEnergyBlock;
+    constexpr int kBlockUnits = kEnergyBlock / kEnergyUnit;
+    const int nu = (n + kEnergyUnit - 1) / kEnergyUnit;
     const int b0 = (int)blockIdx.x, b1 = nb - 1 - (int)blockIdx.x;
     const bool two = b1 > b0;
-    const int nt0 = nb - b0, nt = nt0 + (two ? nb - b1 : 0);
-    const int vt0 = (int)(((int64_t)blockIdx.y * nt) / gridDim.y);
-    const int vt1 = (int)(((int64_t)(blockIdx.y + 1) * nt) / gridDim.y);
-    const int i0 = b0 * kEnergyThreads + tid, i1 = b1 * kEnergyThreads + tid;
-    const int c0 = i0 < n ? i0 : n - 1, c1 = i1 < n ? i1 : n - 1;
-    const double p0x = st.x[0][c0], p0y = st.x[1][c0], p0z = st.x[2][c0];
-    const double p1x = st.x[0][c1], p1y = st.x[1][c1], p1z = st.x[2][c1];
-    double phi0_hi = 0.0, phi0_lo = 0.0, phi1_hi = 0.0, phi1_lo = 0.0;
-    for (int vt = vt0; vt < vt1; ++vt) {
-        const bool first = vt < nt0;  // a tile of block b0 (else of b1)
-        const int b = first ? b0 : b1;
-        const int t = first ? b0 + vt : b1 + (vt - nt0);
-        __syncthreads();
-        const int jj = t * kEnergyThreads + tid;
-        tile[tid] = jj < n ? make_double4(st.x[0][jj], st.x[1][jj], st.x[2][jj], st.m[jj])
-                           : make_double4(1.0e18, 1.0e18, 1.0e18, 0.0);
-        __syncthreads();
-        const double xi0 = first ? p0x : p1x, xi1 = first ? p0y : p1y, xi2 = first ? p0z : p1z;
-        double acc = 0.0;
-        if (t == b) {  // own tile: sources after the target only
-#pragma unroll 4
-            for (int q = 0; q < kEnergyThreads; ++q) {
-                const double4 r = tile[q];
-                const double dx = r.x - xi0, dy = r.y - xi1, dz = r.z - xi2;
-                double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-                const bool take = q > tid;
-                r2 = take ? r2 : 1.0;
-                acc = fma(take ? r.w : 0.0, rsqrt_f64(r2), acc);
-            }
-        } else {
-#pragma unroll 4
-            for (int q = 0; q < kEnergyThreads; ++q) {
-                const double4 r = tile[q];
-                const double dx = r.x - xi0, dy = r.y - xi1, dz = r.z - xi2;
-                const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
-                acc = fma(r.w, rsqrt_f64(r2), acc);
-            }
-        }
-        double s, e;
-        if (first) {
-            two_sum(phi0_hi, acc, s, e);
-            phi0_hi = s;
-            phi0_lo += e;
-        } else {
-            two_sum(phi1_hi, acc, s, e);
-            phi1_hi = s;
-            phi1_lo += e;
-        }
-    }
+    // units from each block's first source on, and this slice's part of both
+    const int nu0 = nu - b0 * kBlockUnits, nut = nu0 + (two ? nu - b1 * kBlockUnits : 0);
+    const int vu0 = (int)(((int64_t)blockIdx.y * nut) / gridDim.y);
+    const int vu1 = (int)(((int64_t)(blockIdx.y + 1) * nut) / gridDim.y);
     double v[5] = {0, 0, 0, 0, 0};
-    const bool has0 = i0 < n, has1 = two && i1 < n;
-    if (has0) v[1] = -st.m[i0] * (phi0_hi + phi0_lo);
-    if (has1) v[1] = fma(-st.m[i1], phi1_hi + phi1_lo, v[1]);
-    if (blockIdx.y == 0) {
-        if (has0) {
-            const double m = st.m[i0], vx = st.v[0][i0], vy = st.v[1][i0], vz = st.v[2][i0];
-            v[0] = 0.5 * m * fma(vx, vx, fma(vy, vy, vz * vz));
-            v[2] = m * (p0y * vz - p0z * vy);
-            v[3] = m * (p0z * vx - p0x * vz);
-            v[4] = m * (p0x * vy - p0y * vx);
+#pragma unroll 1
+    for (int half = 0; half < 2; ++half) {  // the slice's sources of block b0, then of b1
+        if (half == 1 && !two) break;
+        const int b = half ? b1 : b0;
+        const int ja = b * kEnergyBlock + kEnergyUnit * (half ? max(vu0 - nu0, 0) : vu0);
+        const int je = b * kEnergyBlock + kEnergyUnit * (half ? vu1 - nu0 : min(vu1, nu0));
+        int id[2];
+        double xi[2][3], hi[2] = {0, 0}, lo[2] = {0, 0};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            id[u] = b * kEnergyBlock + u * kEnergyThreads + tid;
+            const int c = id[u] < n ? id[u] : n - 1;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) xi[u][q] = st.x[q][c];
         }
-        if (has1) {
-            const double m = st.m[i1], vx = st.v[0][i1], vy = st.v[1][i1], vz = st.v[2][i1];
-            v[0] += 0.5 * m * fma(vx, vx, fma(vy, vy, vz * vz));
-            v[2] += m * (p1y * vz - p1z * vy);
-            v[3] += m * (p1z * vx - p1x * vz);
-            v[4] += m * (p1x * vy - p1y * vx);
+        for (int jt = ja; jt < je; jt += kEnergyThreads) {
+            const int cnt = min(kEnergyThreads, je - jt);  // whole units
+            __syncthreads();
+            const int jj = jt + tid;
+            tile[tid] = jj < n ? make_double4(st.x[0][jj], st.x[1][jj], st.x[2][jj], st.m[jj])
+                               : make_double4(1.0e18, 1.0e18, 1.0e18, 0.0);
+            __syncthreads();
+            double acc[2] = {0.0, 0.0};
+            if (jt < (b + 1) * kEnergyBlock) {  // the block's own: sources after the target only
+#pragma unroll 4
+                for (int q = 0; q < cnt; ++q) {
+                    const double4 r = tile[q];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const double dx = r.x - xi[u][0], dy = r.y - xi[u][1], dz = r.z - xi[u][2];
+                        double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
+                        const bool take = jt + q > id[u];
+                        r2 = take ? r2 : 1.0;
+                        acc[u] = fma(take ? r.w : 0.0, rsqrt_f64(r2), acc[u]);
+                    }
+                }
+            } else {
+#pragma unroll 4
+                for (int q = 0; q < cnt; ++q) {
+                    const double4 r = tile[q];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const double dx = r.x - xi[u][0], dy = r.y - xi[u][1], dz = r.z - xi[u][2];
+                        const double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
+                        acc[u] = fma(r.w, rsqrt_f64(r2), acc[u]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                double s, e;
+                two_sum(hi[u], acc[u], s, e);
+                hi[u] = s;
+                lo[u] += e;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (id[u] >= n) continue;
+            const double m = st.m[id[u]];
+            v[1] = fma(-m, hi[u] + lo[u], v[1]);
+            if (blockIdx.y == 0) {
+                const double vx = st.v[0][id[u]], vy = st.v[1][id[u]], vz = st.v[2][id[u]];
+                v[0] += 0.5 * m * fma(vx, vx, fma(vy, vy, vz * vz));
+                v[2] += m * (xi[u][1] * vz - xi[u][2] * vy);
+                v[3] += m * (xi[u][2] * vx - xi[u][0] * vz);
+                v[4] += m * (xi[u][0] * vy - xi[u][1] * vx);
+            }
         }
     }
 #pragma unroll
@@ -360,7 +373,7 @@ __global__ __launch_bounds__(kEnergyThreads) void k_energy(h6_state st, int n, d
         }
         __syncthreads();
     }
-    if (tid < 5) out[tid] = red_hi[tid][0] + red_lo[tid][0];
+    if (tid < 5) out[tid] = red_hi[tid][0] + red_lo[tid][0];  // pinned host memory
 }
 
 }  // namespace
@@ -368,7 +381,8 @@ __global__ __launch_bounds__(kEnergyThreads) void k_energy(h6_state st, int n, d
 int sched_blocks_for(int64_t n) { return (int)((n + kSchedChunk - 1) / kSchedChunk); }
 // workgroup partial slots for n particles (target blocks x the most slices)
 int energy_blocks_for(int64_t n) {
-    return (int)((n + kEnergyThreads - 1) / kEnergyThreads) * kEnergyMaxSplit;
+    const int64_t nb = (n + kEnergyBlock - 1) / kEnergyBlock;
+    return (int)((nb + 1) / 2) * kEnergyMaxSplit;
 }
 
 hipError_t launch_predict(h6_ctx ctx, const h6_state *st, int n, int64_t t_tick, double dt,
@@ -401,8 +415,8 @@ hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, i
     return hipGetLastError();
 }
 
-// Scratch layout: ctx->sched64[0..1] = {t_next, n_act} (read back by the
-// host), ctx->sched64[2..] chunk minima; ctx->sched32[0..nb) chunk counts,
+// Scratch layout: ctx->sched64[0..1] = {t_next, n_act} (also written to
+// the pinned host buffer), ctx->sched64[2..] chunk minima; ctx->sched32[0..nb) chunk counts,
 // [nb..2nb) chunk offsets; counters[0] is the hand-off counter.
 hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *active) {
     const int nb = sched_blocks_for(n);
@@ -411,21 +425,22 @@ hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *act
     int32_t *ccnt = ctx->sched32;
     int32_t *coff = ctx->sched32 + nb;
     hipLaunchKernelGGL(k_sched_select, dim3(nb), dim3(kSchedThreads), 0, ctx->stream, st->t, st->dt,
-                       n, cmin, ccnt, coff, ctx->counters, sel);
+                       n, cmin, ccnt, coff, ctx->counters, sel,
+                       (int64_t *)((char *)ctx->host_dev + kHostBlock));
     hipLaunchKernelGGL(k_sched_compact, dim3(nb), dim3(kSchedThreads), 0, ctx->stream, st->t,
                        st->dt, n, (const int64_t *)sel, (const int32_t *)coff, active);
     return hipGetLastError();
 }
 
 hipError_t launch_energy(h6_ctx ctx, const h6_state *st, int n) {
-    const int nb = (n + kEnergyThreads - 1) / kEnergyThreads;
+    const int nb = (n + kEnergyBlock - 1) / kEnergyBlock;
     const int pairs = (nb + 1) / 2;  // workgroups per slice: blocks b and nb-1-b together
-    // about four workgroups of four waves per compute unit, at most one
-    // slice per tile of a workgroup's nb + 1
+    // about four workgroups of four waves per compute unit, at most one slice
+    // per unit of a workgroup's sources (the middle block has the fewest)
     int split = std::max(1, std::min(kEnergyMaxSplit, (4 * ctx->n_cu + pairs - 1) / pairs));
-    split = std::min(split, nb + 1);
+    split = std::min(split, std::max(1, nb / 2 * (kEnergyBlock / kEnergyUnit)));
     hipLaunchKernelGGL(k_energy, dim3(pairs, split), dim3(kEnergyThreads), 0, ctx->stream, *st, n,
-                       ctx->eps2, ctx->ered + 8, ctx->counters + 2, ctx->ered);
+                       ctx->eps2, ctx->ered, ctx->counters + 2, (double *)((char *)ctx->host_dev + kHostEnergy));
     return hipGetLastError();
 }
 
