@@ -65,6 +65,8 @@ def _kernel_name(rec, mixed):
         return "k_bl_eval<%s, false>" % ("true" if mixed else "false")
     if rec["kind"] == 1:
         return "k_eval_small%s<%d, false>" % ("_mixed" if mixed else "", rec["ipl"])
+    if rec["kind"] == 3:
+        return "k_eval_sym<2, false>"
     if rec["block"] == 512:
         return "k_eval_wg<2, %d, false>" % rec["ipl"]
     if mixed:

@@ -458,10 +458,12 @@ int h6_energy_vjp(h6_ctx ctx, const h6_state *st, int64_t n, const double *cot_e
  */
 typedef struct {
     int order;      /* 2: per-step a/j/s; 1, 3: start-up passes */
-    int kind;       /* 0: LDS-tiled kernel; 1: source-parallel small-set kernel;
+    int kind;       /* 0: LDS-tiled kernel (block 512: whole workgroups, ipl
+                       targets each); 1: source-parallel small-set kernel;
                        2: evaluation kernel of the device-resident loop (its
-                       shape is chosen per block on the device); 4: the
-                       loop's finishing kernel (on = 2) */
+                       shape is chosen per block on the device); 3: all
+                       particles by the third law (its slice sums
+                       included); 4: the loop's finishing kernel (on = 2) */
     int block, ipl; /* launch shape of the instantiation (kind 2: 64, 2;
                        kind 4: 0, 0) */
     int precision;  /* H6_FP64, H6_MIXED, H6_EX or H6_SP */

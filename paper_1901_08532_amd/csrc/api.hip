@@ -744,8 +744,10 @@ int h6_run_blocks(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, cons
     return run_blocks_device(ctx, st, n, pred, f, active, prm, t_end, stats);
 }
 
-// Systems up to this size take one kernel a shared step.
-constexpr int64_t kSharedStepMax = 8192;
+// Systems up to this size take one kernel a shared step; beyond, the
+// evaluation by the third law saves more than the launches (n = 6000: 84
+// against 75 us of evaluation).
+constexpr int64_t kSharedStepMax = 6000;
 
 // Shared steps of a small system, one kernel each after the first prediction.
 // The predicted arrays alternate between the caller's and the context's

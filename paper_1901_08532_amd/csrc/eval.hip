@@ -224,6 +224,9 @@ constexpr int kDefaultSmallMax = 32;
 // the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets
 // 252 against 254 us, all 495 against 468).
 constexpr int kWgMaxAct = 8192;
+// All particles by the third law from this size on (FP64; below, the
+// whole-workgroup kernel: n = 4096 45 against 51 us, 6000 84 against 75).
+constexpr int kSymMin = 5000;
 // Waves a launch aims to put in flight (256 CUs x 4 SIMDs x 2).
 constexpr int kTargetWaves = 2048;
 // Shortest source slice of the source-parallel kernel (4 sources per lane).
@@ -377,6 +380,20 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
 hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src, int n,
                        const int32_t *active, int n_act, const OutPtrs &out, EvalConfig *used) {
     if (n_act <= 0) return hipSuccess;
+    if (!active && n_act == n && precision == H6_FP64 && n >= kSymMin &&
+        !(order == 2 && eval_shape_forced(ctx))) {
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        hipError_t e = ctx->prof ? prof_begin(ctx, &ev0, &ev1) : hipSuccess;
+        bool done = false;
+        if (e == hipSuccess) e = launch_eval_sym(ctx, order, src, n, out, &done);
+        const EvalConfig sym = {3, 256, 2, 1};
+        if (e == hipSuccess && ctx->prof && done)
+            e = prof_end(ctx, ev0, ev1, order, sym, precision, n_act, (double)n * (double)n);
+        if (e != hipSuccess || done) {
+            if (used) *used = sym;
+            return e;
+        }
+    }
     EvalConfig cfg = choose_eval_config(ctx, order, precision, n, n_act);
     // equal slices, each a whole number of tiles
     const bool wg = cfg.kind == 0 && cfg.block == kWgThreads;
