@@ -15,17 +15,21 @@
 // then their adjoints are accumulated in reverse order. The self pair
 // (whose terms cancel in exact arithmetic) is excluded explicitly.
 //
-// Launch structure as the forward kernel: LDS tiles of source records,
-// one target per lane, source slices combined by the compensated slice
-// reduction; no floating-point atomics.
+// Over all pairs the VJP of a pair is taken once for both particles: swapping
+// k and j changes the sign of r, v, a, jr and of m_k g_j - m_j g_k, so the
+// gradient terms of j are those of k with the opposite sign; only the mass
+// terms differ (Q . g_j for k, Q . g_k for j).
+//
 #include <algorithm>
 #include <type_traits>
 
 #include "device_math.h"
-#include "h6_internal.h"
+#include "sym_body.h"
 
 namespace h6 {
 namespace {
+
+using namespace symbody;
 
 template <int ORDER>
 struct VTraits;
@@ -52,13 +56,18 @@ __device__ __forceinline__ double dot3(const double *p, const double *q) {
     return fma(p[2], q[2], fma(p[1], q[1], p[0] * q[0]));
 }
 
-// Reverse-mode pair: accumulates (dQ/dr)^T gh into xb, (dQ/dv)^T gh into vb,
-// (dQ/da)^T gh into ab, (dQ/djr)^T gh into jb, and (MASS) -Q . gj into mb.
-template <int ORDER, bool MASS = true>
+// Reverse-mode pair of the start-up passes (orders 1 and 3): T = (dQ/dr)^T gh,
+// (dQ/dv)^T gh, ... (3 components each, in the order x, v, a, jr), and the mass
+// terms qj = Q . gj and qk = Q . gk.
+template <int ORDER>
 __device__ __forceinline__ void pair_vjp(const double *r, const double *v, const double *a,
-                                         const double *jr, double r2, const double *gh,
-                                         const double *gj, double *xb, double *vb, double *ab,
-                                         double *jb, double &mb) {
+                                         const double *jr, double r2, double mk, double mj,
+                                         const double *gj, const double *gk, double *T, double &qj,
+                                         double &qk) {
+    constexpr int NG = VTraits<ORDER>::NG;
+    double gh[NG];
+#pragma unroll
+    for (int p = 0; p < NG; ++p) gh[p] = fma(mk, gj[p], -mj * gk[p]);
     // ---- forward values
     const double rho = rsqrt_f64(r2);
     const double rho2 = rho * rho;
@@ -87,18 +96,15 @@ __device__ __forceinline__ void pair_vjp(const double *r, const double *v, const
     const double zero3[3] = {0, 0, 0};
     const double *Ab = ORDER == 3 ? zero3 : gh;
     const double *Jb = ORDER == 3 ? zero3 : gh + 3;
-    const double *Sb = ORDER == 2 ? gh + 6 : ORDER == 3 ? gh : zero3;
+    const double *Sb = ORDER == 3 ? gh : zero3;
     const double *Cb = ORDER == 3 ? gh + 3 : zero3;
-    const double *Aj = ORDER == 3 ? zero3 : gj;
-    const double *Jj = ORDER == 3 ? zero3 : gj + 3;
-    const double *Sj = ORDER == 2 ? gj + 6 : ORDER == 3 ? gj : zero3;
-    const double *Cj = ORDER == 3 ? gj + 3 : zero3;
-    // mass: -Q . g_j with Q = R^-3 (r, w, u, z) for (A, J, S, C)
-    if constexpr (MASS) {
-        double qg = dot3(r, Aj) + dot3(w, Jj);
-        if constexpr (ORDER >= 2) qg += dot3(u, Sj);
-        if constexpr (ORDER == 3) qg += dot3(z, Cj);
-        mb = fma(-q3, qg, mb);
+    // mass: Q . g with Q = R^-3 (r, w, u, z) for (A, J, S, C)
+    if constexpr (ORDER == 3) {
+        qj = q3 * (dot3(u, gj) + dot3(z, gj + 3));
+        qk = q3 * (dot3(u, gk) + dot3(z, gk + 3));
+    } else {
+        qj = q3 * (dot3(r, gj) + dot3(w, gj + 3));
+        qk = q3 * (dot3(r, gk) + dot3(w, gk + 3));
     }
     // ---- reverse sweep
     double q3b = dot3(Ab, r) + dot3(Jb, w);
@@ -180,18 +186,20 @@ __device__ __forceinline__ void pair_vjp(const double *r, const double *v, const
     const double r2b = -1.5 * q3b * q3 * rho2 - rho2b * rho2 * rho2;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        xb[c] += fma(2.0 * r2b, r[c], rb[c]);
-        vb[c] += vbl[c];
-        if constexpr (ORDER >= 2) ab[c] += abl[c];
-        if constexpr (ORDER == 3) jb[c] += jrb[c];
+        T[c] = fma(2.0 * r2b, r[c], rb[c]);
+        T[3 + c] = vbl[c];
+        if constexpr (ORDER >= 2) T[6 + c] = abl[c];
+        if constexpr (ORDER == 3) T[9 + c] = jrb[c];
     }
 }
+
+constexpr double kPadPosVjp = 1.0e18;
 
 struct CotPtrs {
     const double *g[9];
 };
 
-constexpr double kPadPosVjp = 1.0e18;
+
 
 // Which pairs and which half of each pair a launch covers. With the
 // cotangents g nonzero only on an active set (block steps), the pair sum
@@ -232,6 +240,148 @@ __device__ __forceinline__ void g_terms(const double *g, const double *r, const 
     const double dSv = dot3(g + 6, v), dSa = dot3(g + 6, a);
     G = fma(c18, dSr, fma(-a6, dSv, fma(-a3, dJr, dAr + dJv) + dSa));
     Ga = fma(a30, dSr, fma(-6.0, dSv, -3.0 * dJr));
+}
+
+// The pair's gradient terms T (x, v, a) of both parts of gh and the mass terms
+// qj = R^-3 G(g_j), qk = R^-3 G(g_k).
+__device__ __forceinline__ void pair_vjp2_both(const double *r, const double *v, const double *a,
+                                               double r2, double mk, double mj, const double *gj,
+                                               const double *gk, double *T, double &qj,
+                                               double &qk) {
+    const double rho = rsqrt_f64(r2);
+    const double rho2 = rho * rho;
+    const double q3 = rho * rho2;
+    const double alpha = dot3(r, v) * rho2;
+    const double bp = (fma(v[2], v[2], fma(v[1], v[1], v[0] * v[0])) + dot3(r, a)) * rho2;
+    const double beta = fma(alpha, alpha, bp);
+    const double a3 = 3.0 * alpha;
+    const double a6 = a3 + a3;
+    const double c18 = fma(6.0 * a3, alpha, -3.0 * beta);
+    const double a30 = 10.0 * a3;
+    double Gj, Gaj, dSj, Gk, Gak, dSk;
+    g_terms(gj, r, v, a, a3, a6, c18, a30, Gj, Gaj, dSj);
+    g_terms(gk, r, v, a, a3, a6, c18, a30, Gk, Gak, dSk);
+    qj = q3 * Gj;
+    qk = q3 * Gk;
+    const double G = fma(mk, Gj, -mj * Gk);
+    const double Ga = fma(mk, Gaj, -mj * Gak);
+    const double dS = fma(mk, dSj, -mj * dSk);
+    const double qr = q3 * rho2;
+    const double sa = qr * Ga;
+    const double sb = (-3.0 * qr) * dS;
+    const double cr = fma(-3.0 * qr, G, fma(-2.0 * alpha, sa, (-2.0 * bp) * sb));
+    const double sb2 = sb + sb;
+    const double mkq = mk * q3, mjq = mj * q3;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        // R^-3 gh
+        const double hA = fma(mkq, gj[c], -mjq * gk[c]);
+        const double hJ = fma(mkq, gj[3 + c], -mjq * gk[3 + c]);
+        const double hS = fma(mkq, gj[6 + c], -mjq * gk[6 + c]);
+        T[c] = fma(sa, v[c], fma(sb, a[c], fma(cr, r[c], fma(-a3, hJ, fma(c18, hS, hA)))));
+        T[3 + c] = fma(sa, r[c], fma(sb2, v[c], fma(-a6, hS, hJ)));
+        T[6 + c] = fma(sb, r[c], hS);
+    }
+}
+
+// Particles and pairs of the all-pairs VJP for sym_body.h's walk: the pair's
+// terms T are added to the target's sums and subtracted from the source's.
+// Bound by FP64 issue: at order 2 about 200 operations an unordered pair
+// (10 of them DPP moves per 10 sums), against 2 x 153 in ordered form.
+template <int ORDER>
+struct VjpOps {
+    using Word = double;
+    using Sum = CompSum;
+    static constexpr int NG = VTraits<ORDER>::NG, NF = VTraits<ORDER>::NF;
+    static constexpr int NREC = (NF + 1) / 2;
+    static constexpr int NI = VTraits<ORDER>::NOUT, NJ = NI, K = 1, kUnroll = 1;
+    static constexpr int kG = NF - NG;  // first cotangent word
+    struct Target {
+        double x[3], v[3], a[3], j[3], m, g[NG];
+    };
+    SrcPtrs src;
+    CotPtrs cot;
+    double eps2;
+    // record order x0 x1 x2 m v0 v1 v2 (a.. (j..)) g..
+    __device__ __forceinline__ const double *field(int f) const {
+        return f < 3    ? src.x[f]
+               : f == 3  ? src.m
+               : f < 7   ? src.v[f - 4]
+               : f >= kG ? cot.g[f - kG]
+               : f < 10  ? src.a[f - 7]
+                         : src.j[f - 10];
+    }
+    static __device__ __forceinline__ double word(double x) { return x; }
+    static __device__ __forceinline__ double pad(int f) { return f < 3 ? kPadPosVjp : 0.0; }
+    __device__ __forceinline__ void load(int k, int n, Target &t) const {
+        const bool in = k < n;
+        const int kc = in ? k : n - 1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            t.x[c] = in ? src.x[c][kc] : -kPadPosVjp;
+            t.v[c] = src.v[c][kc];
+            if constexpr (ORDER >= 2) t.a[c] = src.a[c][kc];
+            if constexpr (ORDER == 3) t.j[c] = src.j[c][kc];
+        }
+        t.m = in ? src.m[kc] : 0.0;
+#pragma unroll
+        for (int q = 0; q < NG; ++q) t.g[q] = in ? cot.g[q][kc] : 0.0;
+    }
+    // self: the self pair is left out explicitly: m_k g_k - m_k g_k is not
+    // exactly zero once the first product is fused (fma keeps its rounding
+    // error), and dQ/dr at r = 0 is of order eps^-3. With both masses zero gh
+    // is exactly zero; r, v, a, jr are zero there, so Q and the mass term are
+    // too (R^2 set to 1 keeps them finite when eps = 0).
+    __device__ __forceinline__ void terms(const Word2<double> *e, const Target &t, bool self,
+                                          double *T, double &qj, double &qk) const {
+        auto f = [&](int q) { return q & 1 ? e[q >> 1].y : e[q >> 1].x; };
+        double r[3], v[3], a[3] = {0, 0, 0}, jr[3] = {0, 0, 0}, gj[NG];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            r[c] = f(c) - t.x[c];
+            v[c] = f(4 + c) - t.v[c];
+            if constexpr (ORDER >= 2) a[c] = f(7 + c) - t.a[c];
+            if constexpr (ORDER == 3) jr[c] = f(10 + c) - t.j[c];
+        }
+#pragma unroll
+        for (int q = 0; q < NG; ++q) gj[q] = f(kG + q);
+        double r2 = fma(r[2], r[2], fma(r[1], r[1], fma(r[0], r[0], eps2)));
+        r2 = self ? 1.0 : r2;
+        const double mj = self ? 0.0 : f(3), mk = self ? 0.0 : t.m;
+        if constexpr (ORDER == 2)
+            pair_vjp2_both(r, v, a, r2, mk, mj, gj, t.g, T, qj, qk);
+        else
+            pair_vjp<ORDER>(r, v, a, jr, r2, mk, mj, gj, t.g, T, qj, qk);
+    }
+    __device__ __forceinline__ void both(const Word2<double> *e, const Target &t, double *acci,
+                                         double *accj) const {
+        double T[NI - 1], qj, qk;
+        terms(e, t, false, T, qj, qk);
+#pragma unroll
+        for (int q = 0; q < NI - 1; ++q) {
+            acci[q] += T[q];
+            accj[q] -= T[q];
+        }
+        acci[NI - 1] -= qj;
+        accj[NI - 1] += qk;
+    }
+    __device__ __forceinline__ void one(const Word2<double> *e, const Target &t, bool self,
+                                        double *acci) const {
+        double T[NI - 1], qj, qk;
+        terms(e, t, self, T, qj, qk);
+#pragma unroll
+        for (int q = 0; q < NI - 1; ++q) acci[q] += T[q];
+        acci[NI - 1] -= qj;
+    }
+    static __device__ __forceinline__ void add(Sum &s, double x) { two_sum_into(s.hi, s.lo, x); }
+    static __device__ __forceinline__ double value(const Sum &s) { return s.hi + s.lo; }
+    static __device__ __forceinline__ double value(double x) { return x; }
+};
+
+template <int ORDER>
+__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_sym(
+    SrcPtrs src, CotPtrs cot, SymPlan P, double eps2, double *__restrict__ partial) {
+    sym_run(VjpOps<ORDER>{src, cot, eps2}, P, partial);
 }
 
 template <int MODE>
@@ -589,10 +739,25 @@ hipError_t launch_vjp_mode(h6_ctx ctx, const SrcPtrs &src, const CotPtrs &cot, i
     }
 }
 
+// VJP of the sums over all pairs, each unordered pair once; in ordered form
+// where the partial sums hold too few slots for that.
 template <int ORDER>
 hipError_t launch_vjp_order(h6_ctx ctx, const SrcPtrs &src, const CotPtrs &cot, int n,
                             const OutPtrs &out, unsigned acc_mask) {
-    return launch_vjp_mode<ORDER, kAll>(ctx, src, cot, n, nullptr, 0, out, acc_mask);
+    constexpr int NOUT = VTraits<ORDER>::NOUT, kBlock = kSymThreads * VjpOps<ORDER>::K;
+    const int runs = 2 * ctx->n_cu;
+    SymPlan P;
+    const bool sym = sym_plan(ctx, n, kBlock, runs, NOUT, 0, &P);
+    if (!sym) P = sym_plan_ordered(n, kBlock);
+    for (bool more = true; more; more = sym && sym_plan(ctx, n, kBlock, runs, NOUT, P.d1, &P)) {
+        hipLaunchKernelGGL((k_vjp_sym<ORDER>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream, src,
+                           cot, P, ctx->eps2, ctx->partial);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess)
+            e = launch_sym_reduce(ctx, P, NOUT, 0, out, P.d0 > 0 ? (1u << NOUT) - 1u : acc_mask);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Transpose of the block-step corrector for the active particles, each over

@@ -307,11 +307,19 @@ int h6_create(h6_ctx *out, int64_t n_max, double eps, void *hip_stream) {
     }
     ctx->n_cu = n_cu > 0 ? n_cu : 256;
     // partial sums: n_split * ncomp * n_act doubles, n_split * n_act <= cap
-    const int64_t cap_pairs = std::max<int64_t>(2 * n_max, (int64_t)1 << 21);
+    // (the third-law kernels need three slots of 13 sums a particle, large
+    // systems included; half of that serves every call too, more slowly)
+    int64_t cap_pairs = std::max<int64_t>(5 * n_max, (int64_t)1 << 21);
+    if (hipMalloc(&ctx->partial, sizeof(double) * 9 * cap_pairs) != hipSuccess) {
+        (void)hipGetLastError();
+        ctx->partial = nullptr;
+        cap_pairs = std::max<int64_t>(2 * n_max, (int64_t)1 << 21);
+    }
     ctx->partial_cap = 9 * cap_pairs;
     ctx->sched_blocks = sched_blocks_for(n_max);
     const int64_t eb = energy_blocks_for(n_max);
-    bool ok = hipMalloc(&ctx->partial, sizeof(double) * ctx->partial_cap) == hipSuccess &&
+    bool ok = (ctx->partial ||
+               hipMalloc(&ctx->partial, sizeof(double) * ctx->partial_cap) == hipSuccess) &&
               hipMalloc(&ctx->sched64, sizeof(int64_t) * (2 + ctx->sched_blocks)) == hipSuccess &&
               hipMalloc(&ctx->sched32, sizeof(int32_t) * (1 + 2 * ctx->sched_blocks)) == hipSuccess &&
               hipMalloc(&ctx->counters, sizeof(unsigned) * 8) == hipSuccess &&
@@ -635,7 +643,8 @@ static int run_blocks_device(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred 
     A.t_end = t_end;
     A.eval_grid = bl_eval_grid(ctx, prm->precision);
     A.one_target_small = prm->precision == H6_MIXED ? 1 : 0;
-    A.pc_pairs = (unsigned)(ctx->partial_cap / 9);
+    A.pc_pairs = (unsigned)std::min<int64_t>(ctx->partial_cap / 9,
+                                             std::max<int64_t>(2 * ctx->n_max, (int64_t)1 << 21));
     A.flags = ctx->flags;
     A.nact_log = ctx->prof_level > 0 ? ctx->bl_log : nullptr;
     A.log_mask = ctx->bl_log_mask;

@@ -2,11 +2,9 @@
 // (sym_plan.h): the a, j, s terms of a pair serve both particles, by Newton's
 // third law.
 //
-// A wave holds 2 x 64 targets in registers, two per lane. The sources of a
-// chunk go round the lanes: at step s lane l takes source (l + s) mod 64, read
-// from LDS, against its targets, and the source's sums, which start and end
-// at the source's home lane, move on one lane a step (18 DPP moves for 128
-// pairs). Per unordered pair that is 63 + 9 VALU operations at order 2
+// The walk is sym_body.h's; a lane holds two targets, so that the 18 DPP moves
+// that take a source's sums to the next lane serve two pairs. Per unordered
+// pair that is 63 + 9 VALU operations at order 2
 // against 2 x 54 in ordered form; the bound stays FP64 issue. Evaluation of
 // all particles, ordered form and this: n = 8192 139 -> 116 us, 16384 493 ->
 // 364 us, 32768 1902 -> 1335 us, 65536 7585 -> 5200 us (64 TFLOP/s at 78
@@ -14,24 +12,13 @@
 #include <algorithm>
 
 #include "eval_body.h"
-#include "sym_plan.h"
+#include "sym_body.h"
 
 namespace h6 {
 namespace {
 
 using namespace evalbody;
-
-constexpr int kSymWaves = 4;
-constexpr int kSymIpl = 2;
-constexpr int kSymThreads = 64 * kSymWaves;
-constexpr int kSymBlock = kSymThreads * kSymIpl;
-
-// A double from the next lane (wave rotate left by one).
-__device__ __forceinline__ double rotate_lane(double v) {
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), 0x134, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), 0x134, 0xF, 0xF, true);
-    return __hiloint2double(hi, lo);
-}
+using namespace symbody;
 
 // Terms of the pair (target i, source j) added to both particles' sums; d* is
 // source minus target. Order 1: a, j; 2: a, j, s; 3: s, c.
@@ -89,190 +76,69 @@ __device__ __forceinline__ void pair_both(const double *r, const double *v, cons
 }
 
 template <int ORDER, bool SKIPSELF>
+struct EvalOps {
+    using Word = double;
+    using Sum = CompSum;
+    static constexpr int NF = ORDER == 1 ? 7 : ORDER == 2 ? 10 : 13;  // x, m, v, a, j
+    static constexpr int NREC = Traits<ORDER>::NREC;
+    static constexpr int NI = Traits<ORDER>::NACC, NJ = NI, K = 2, kUnroll = 2;
+    struct Target {
+        double x[3], v[3], a[3], j[3], m;
+    };
+    SrcPtrs src;
+    double eps2;
+    // record order x0 x1 | x2 m | v0 v1 | v2 a0 | a1 a2 | j0 j1 | j2
+    __device__ __forceinline__ const double *field(int f) const {
+        return f < 3   ? src.x[f]
+               : f == 3 ? src.m
+               : f < 7  ? src.v[f - 4]
+               : f < 10 ? src.a[f - 7]
+                        : src.j[f - 10];
+    }
+    static __device__ __forceinline__ double word(double x) { return x; }
+    static __device__ __forceinline__ double pad(int f) { return f < 3 ? kPadPos : 0.0; }
+    __device__ __forceinline__ void load(int k, int n, Target &t) const {
+        const bool in = k < n;
+        PredSrc{src, nullptr}.template get<ORDER>(in ? k : n - 1, t.x, t.v, t.a, t.j);
+        t.m = in ? src.m[k] : 0.0;
+        // padding: massless, and far from the sources' padding too
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t.x[c] = in ? t.x[c] : -kPadPos;
+    }
+    __device__ __forceinline__ void both(const Word2<double> *e, const Target &t, double *acci,
+                                         double *accj) const {
+        const double r[3] = {e[0].x - t.x[0], e[0].y - t.x[1], e[1].x - t.x[2]};
+        const double v[3] = {e[2].x - t.v[0], e[2].y - t.v[1], e[3].x - t.v[2]};
+        double a[3] = {0, 0, 0}, jr[3] = {0, 0, 0};
+        if constexpr (ORDER >= 2) {
+            a[0] = e[3].y - t.a[0];
+            a[1] = e[4].x - t.a[1];
+            a[2] = e[4].y - t.a[2];
+        }
+        if constexpr (ORDER == 3) {
+            jr[0] = e[5].x - t.j[0];
+            jr[1] = e[5].y - t.j[1];
+            jr[2] = e[6].x - t.j[2];
+        }
+        const double r2 = fma(r[2], r[2], fma(r[1], r[1], fma(r[0], r[0], eps2)));
+        pair_both<ORDER>(r, v, a, jr, r2, t.m, e[1].y, acci, accj);
+    }
+    __device__ __forceinline__ void one(const Word2<double> *e, const Target &t, bool self,
+                                        double *acci) const {
+        double2 d[NREC];
+#pragma unroll
+        for (int q = 0; q < NREC; ++q) d[q] = make_double2(e[q].x, e[q].y);
+        pair_terms<ORDER, SKIPSELF>(d, t.x, t.v, t.a, t.j, eps2, self, acci);
+    }
+    static __device__ __forceinline__ void add(Sum &s, double x) { two_sum_into(s.hi, s.lo, x); }
+    static __device__ __forceinline__ double value(const Sum &s) { return s.hi + s.lo; }
+    static __device__ __forceinline__ double value(double x) { return x; }
+};
+
+template <int ORDER, bool SKIPSELF>
 __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_eval_sym(
     SrcPtrs src, SymPlan P, double eps2, double *__restrict__ partial) {
-    using T = Traits<ORDER>;
-    constexpr int NACC = T::NACC, NREC = T::NREC, K = kSymIpl;
-    constexpr int NF = ORDER == 1 ? 7 : ORDER == 2 ? 10 : 13;  // doubles of a source: x, m, v, a, j
-    constexpr int NLOAD = (NF + kSymWaves - 1) / kSymWaves;
-    // a chunk's records twice over, so that a rotated index needs no wrap
-    __shared__ double2 rec[NREC * 2 * kSymChunk];
-    __shared__ double jsum[kSymWaves][NACC][kSymChunk];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int n = P.n, per_d = P.per_d(), part_steps = kSymChunk / P.sub;
-    const int64_t x0 = (int64_t)blockIdx.x * P.cells / P.runs;
-    const int64_t x1 = (int64_t)(blockIdx.x + 1) * P.cells / P.runs;
-    // the superblock, offset and chunk of the first cell
-    int I;
-    {
-        const int64_t full = (int64_t)(P.d1 - P.d0) * per_d;
-        const int h = P.nsb / 2;
-        if (P.half && x0 >= P.first_cell(h)) {
-            const int64_t part = full - per_d;
-            I = h + (part > 0 ? (int)((x0 - P.first_cell(h)) / part) : 0);
-        } else {
-            I = (int)(x0 / full);
-        }
-    }
-    int local = (int)(x0 - P.first_cell(I));
-    const PredSrc S{src, nullptr};
-
-    double xi[K][3], vi[K][3], ai[K][3], ji[K][3], mi[K];
-    int ki[K];
-    double hi[K][NACC], lo[K][NACC];
-    auto load_targets = [&]() {
-#pragma unroll
-        for (int u = 0; u < K; ++u) {
-            ki[u] = I * kSymBlock + (wave * K + u) * 64 + lane;
-            const bool in = ki[u] < n;
-            S.template get<ORDER>(in ? ki[u] : n - 1, xi[u], vi[u], ai[u], ji[u]);
-            // past the end: far and massless (no term for any source)
-            mi[u] = in ? src.m[ki[u]] : 0.0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) xi[u][c] = in ? xi[u][c] : -kPadPos;
-#pragma unroll
-            for (int q = 0; q < NACC; ++q) hi[u][q] = lo[u][q] = 0.0;
-        }
-    };
-    auto store_targets = [&]() {
-        const int slot = P.slots_j + ((int)blockIdx.x - P.first_run(I));
-#pragma unroll
-        for (int u = 0; u < K; ++u)
-            if (ki[u] < n)
-#pragma unroll
-                for (int q = 0; q < NACC; ++q)
-                    partial[((int64_t)slot * NACC + q) * n + ki[u]] = hi[u][q] + lo[u][q];
-    };
-    // double `f` of source jj in record order (x0 x1 x2 m v0 v1 v2 a.. j..)
-    auto field = [&](int f) {
-        const int c = f < 3 ? f : (f - 4) % 3;
-        return f == 3 ? src.m : f < 3 ? src.x[c] : f < 7 ? src.v[c] : f < 10 ? src.a[c] : src.j[c];
-    };
-    double pre[NLOAD];
-    auto fetch = [&](int Jc) {  // this thread's doubles of the chunk at particle Jc
-#pragma unroll
-        for (int q = 0; q < NLOAD; ++q) {
-            const int f = wave + q * kSymWaves;
-            const int jj = Jc + lane;
-            pre[q] = 0.0;
-            if (f < NF) pre[q] = jj < n ? field(f)[jj] : f < 3 ? kPadPos : 0.0;
-        }
-    };
-    auto chunk_of = [&](int local_cell) {
-        const int d = P.d0 + local_cell / per_d;
-        int J = I + d;
-        J = J >= P.nsb ? J - P.nsb : J;
-        return J * kSymBlock + (local_cell % per_d) / P.sub * kSymChunk;
-    };
-    if (x0 < x1) {
-        load_targets();
-        fetch(chunk_of(local));
-    }
-    for (int64_t x = x0; x < x1; ++x) {
-        const int d = P.d0 + local / per_d;
-        const int part = local % per_d % P.sub;
-        const int sa = part * part_steps, sb = sa + part_steps;  // this part's steps
-        const int Jc = chunk_of(local);
-        double *rd = reinterpret_cast<double *>(rec);
-#pragma unroll
-        for (int q = 0; q < NLOAD; ++q) {
-            const int f = wave + q * kSymWaves;
-            if (f < NF) {
-                const int at = ((f >> 1) * 2 * kSymChunk + lane) * 2 + (f & 1);
-                rd[at] = pre[q];
-                rd[at + 2 * kSymChunk] = pre[q];
-            }
-        }
-        __syncthreads();
-        // the next cell: its sources on their way during this one
-        const bool last_of_I = x + 1 < x1 && x + 1 == P.first_cell(I + 1);
-        if (x + 1 < x1) {
-            if (!last_of_I) fetch(chunk_of(local + 1));
-        }
-        const bool live = Jc < n;
-        double acc[K][NACC], accj[NACC];
-#pragma unroll
-        for (int q = 0; q < NACC; ++q) {
-            accj[q] = 0.0;
-#pragma unroll
-            for (int u = 0; u < K; ++u) acc[u][q] = 0.0;
-        }
-        auto steps = [&](auto both) {
-            constexpr bool BOTH = decltype(both)::value;
-            const double2 *p = rec + lane;
-#pragma unroll 2
-            for (int s = sa; s < sb; ++s) {
-                double2 e[NREC];
-#pragma unroll
-                for (int q = 0; q < NREC; ++q) e[q] = p[q * 2 * kSymChunk + s];
-                // order 1's last record holds v2 alone; the others v2, a0
-#pragma unroll
-                for (int u = 0; u < K; ++u) {
-                    if constexpr (BOTH) {
-                        const double r[3] = {e[0].x - xi[u][0], e[0].y - xi[u][1], e[1].x - xi[u][2]};
-                        const double v[3] = {e[2].x - vi[u][0], e[2].y - vi[u][1], e[3].x - vi[u][2]};
-                        double a[3] = {0, 0, 0}, jr[3] = {0, 0, 0};
-                        if constexpr (ORDER >= 2) {
-                            a[0] = e[3].y - ai[u][0];
-                            a[1] = e[4].x - ai[u][1];
-                            a[2] = e[4].y - ai[u][2];
-                        }
-                        if constexpr (ORDER == 3) {
-                            jr[0] = e[5].x - ji[u][0];
-                            jr[1] = e[5].y - ji[u][1];
-                            jr[2] = e[6].x - ji[u][2];
-                        }
-                        const double r2 = fma(r[2], r[2], fma(r[1], r[1], fma(r[0], r[0], eps2)));
-                        pair_both<ORDER>(r, v, a, jr, r2, mi[u], e[1].y, acc[u], accj);
-                    } else {
-                        const int j = Jc + ((lane + s) & (kSymChunk - 1));
-                        pair_terms<ORDER, SKIPSELF>(e, xi[u], vi[u], ai[u], ji[u], eps2, j == ki[u],
-                                                    acc[u]);
-                    }
-                }
-                if constexpr (BOTH) {
-#pragma unroll
-                    for (int q = 0; q < NACC; ++q) accj[q] = rotate_lane(accj[q]);
-                }
-            }
-        };
-        if (live) {
-            if (d > 0)
-                steps(std::true_type{});
-            else
-                steps(std::false_type{});
-#pragma unroll
-            for (int u = 0; u < K; ++u)
-#pragma unroll
-                for (int q = 0; q < NACC; ++q) two_sum_into(hi[u][q], lo[u][q], acc[u][q]);
-            if (d > 0) {
-#pragma unroll
-                for (int q = 0; q < NACC; ++q)
-                    jsum[wave][q][(lane + sb) & (kSymChunk - 1)] = accj[q];
-            }
-        }
-        __syncthreads();
-        if (live && d > 0) {
-            const int slot = (d - (P.d0 > 0 ? P.d0 : 1)) * P.sub + part;
-            for (int e = tid; e < NACC * kSymChunk; e += kSymThreads) {
-                const int q = e / kSymChunk, l = e % kSymChunk;
-                double hs = jsum[0][q][l], hc = 0.0;
-#pragma unroll
-                for (int w = 1; w < kSymWaves; ++w) two_sum_into(hs, hc, jsum[w][q][l]);
-                if (Jc + l < n) partial[((int64_t)slot * NACC + q) * n + Jc + l] = hs + hc;
-            }
-        }
-        ++local;
-        if (last_of_I) {
-            store_targets();
-            ++I;
-            local = 0;
-            load_targets();
-            fetch(chunk_of(0));
-        }
-    }
-    if (x0 < x1) store_targets();
+    sym_run(EvalOps<ORDER, SKIPSELF>{src, eps2}, P, partial);
 }
 
 // Sum of a batch's slots: the source-side slots that particle k's superblock
@@ -315,36 +181,60 @@ bool sym_plan(h6_ctx ctx, int n, int block, int runs, int ncomp, int d0, SymPlan
     P.block = block;
     P.nsb = (n + block - 1) / block;
     P.d0 = d0;
+    P.ordered = 0;
     const int nd = P.nsb / 2 + 1, dj = d0 > 0 ? d0 : 1;
     const int64_t slots = ctx->partial_cap / ((int64_t)ncomp * n);
-    // target-side slots: the runs a superblock's cells can span (it holds at
-    // most 2 / nsb of a batch's cells, when the batch is d = nsb / 2 alone)
-    const int64_t span = (2 * (int64_t)runs + P.nsb - 1) / P.nsb + 2;
-    const int64_t room = slots - span;
-    if (room < 1 || d0 >= nd) return false;
-    P.d1 = (int)std::min<int64_t>(nd, dj + room);
-    P.half = P.nsb % 2 == 0 && P.nsb > 1 && P.d1 == nd;
+    if (d0 >= nd) return false;
+    // the batch [d0, dj + m) in `sub` parts on r workgroups; false if its
+    // sums need more slots than there are
+    auto fits = [&](int m, int sub, int r) {
+        P.d1 = dj + m;
+        P.half = P.nsb % 2 == 0 && P.nsb > 1 && P.d1 == nd;
+        P.sub = sub;
+        P.runs = 1;
+        P.cells = 1;  // not read by first_cell
+        P.cells = P.first_cell(P.nsb);
+        P.runs = (int)std::min<int64_t>(r, P.cells);
+        P.slots_j = m * sub;
+        // a superblock's cells touch at most this many runs of len or more
+        const int64_t most = (int64_t)(P.d1 - d0) * P.per_d(), len = P.cells / P.runs;
+        return P.slots_j + (most - 1 + len - 1) / len + 1 <= slots;
+    };
+    // as many offsets as fit; for large systems, whose scratch is short, on
+    // fewer workgroups if one offset needs it (then three slots do)
+    int m = (int)std::min<int64_t>(nd - dj, slots);
+    while (m > 1 && !fits(m, 1, runs)) --m;
+    while (runs > 1 && !fits(m, 1, runs)) runs = (runs + 1) / 2;
+    if (!fits(m, 1, runs)) return false;
     // parts: the longest run in chunk times (a part costs about 1/12 more for
     // its staging and sums: n = 16384 in 9 whole chunks a run 352 us, in 17
-    // halves 358; n = 8192 in 3 chunks 116 us, in 5 halves 105), where the slots allow
+    // halves 358; n = 8192 in 3 chunks 116 us, in 5 halves 105)
     float best = 3.0e38f;
-    SymPlan Q = P;
-    for (int sub = 1; sub <= kSymMaxSub; sub *= 2) {
-        if (sub > 1 && (int64_t)(P.d1 - dj) * sub > room) break;
-        Q.sub = sub;
-        Q.runs = 1;
-        Q.cells = 1;
-        Q.cells = Q.first_cell(Q.nsb);
-        Q.runs = (int)std::min<int64_t>(runs, Q.cells);
-        Q.slots_j = (P.d1 - dj) * sub;
-        const float longest = (float)((Q.cells + Q.runs - 1) / Q.runs);
+    for (int sub = 1; sub <= kSymMaxSub && fits(m, sub, runs); sub *= 2) {
+        const float longest = (float)((P.cells + P.runs - 1) / P.runs);
         const float cost = longest * (1.0f / (float)sub + 1.0f / 12.0f);
         if (cost < best) {
             best = cost;
-            *plan = Q;
+            *plan = P;
         }
     }
     return true;
+}
+
+SymPlan sym_plan_ordered(int n, int block) {
+    SymPlan P;
+    P.n = n;
+    P.block = block;
+    P.nsb = (n + block - 1) / block;
+    P.sub = 1;
+    P.d0 = 0;
+    P.d1 = P.nsb;
+    P.ordered = 1;
+    P.half = 0;
+    P.slots_j = 0;
+    P.runs = P.nsb;  // a run is a superblock's cells: one slot
+    P.cells = P.first_cell(P.nsb);
+    return P;
 }
 
 hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
@@ -358,12 +248,13 @@ hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, 
 hipError_t launch_eval_sym(h6_ctx ctx, int order, const SrcPtrs &src, int n, const OutPtrs &out,
                            bool *done) {
     const int ncomp = order == 2 ? 9 : 6, out0 = order == 3 ? 6 : 0;
+    const int block = kSymThreads * EvalOps<2, false>::K;
     const int runs = 2 * ctx->n_cu;  // two workgroups of four waves a CU (two waves a SIMD)
     SymPlan P;
-    *done = sym_plan(ctx, n, kSymBlock, runs, ncomp, 0, &P);
+    *done = sym_plan(ctx, n, block, runs, ncomp, 0, &P);
     if (!*done) return hipSuccess;
     const bool skip = self_pair_masked(ctx->eps2, H6_FP64);
-    for (bool more = true; more; more = sym_plan(ctx, n, kSymBlock, runs, ncomp, P.d1, &P)) {
+    for (bool more = true; more; more = sym_plan(ctx, n, block, runs, ncomp, P.d1, &P)) {
 #define H6_SYM(O, S)                                                                           \
     hipLaunchKernelGGL((k_eval_sym<O, S>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream, src, \
                        P, ctx->eps2, ctx->partial)

@@ -210,10 +210,6 @@ inline bool eval_shape_forced(h6_ctx ctx) {
 }
 // FP64 evaluation over all particles by the third law (eval_sym.hip); *done
 // is false, and nothing launched, where the partial sums hold too few slots.
-struct SymPlan;
-bool sym_plan(h6_ctx ctx, int n, int block, int runs, int ncomp, int d0, SymPlan *plan);
-hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
-                             unsigned acc_mask);
 hipError_t launch_eval_sym(h6_ctx ctx, int order, const SrcPtrs &src, int n, const OutPtrs &out,
                            bool *done);
 int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_i);

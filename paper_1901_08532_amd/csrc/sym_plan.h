@@ -15,7 +15,9 @@
 // Sums leave through slots of the context's partial sums, [slot][component]
 // [particle]: `sub` slots per d >= 1 of the batch for the source side (each
 // cell writes its chunk once), then one per workgroup that touches I for the
-// target side. Batches take as many d as the slots hold.
+// target side. Batches take as many d as the slots hold; very large systems,
+// whose scratch holds no more than a slot or two, take the ordered form, one
+// workgroup a superblock.
 #pragma once
 
 #include "h6_internal.h"
@@ -31,6 +33,7 @@ struct SymPlan {
     int nsb;        // superblocks
     int sub;        // parts of a chunk's 64 steps
     int d0, d1;     // offsets d of this batch
+    int ordered;    // 1: d = 0 .. nsb - 1 in ordered form, no source-side sums
     int half;       // 1: the batch holds d = nsb / 2 of an even nsb
     int runs;       // workgroups
     int slots_j;    // source-side slots (sub for each d >= 1 of the batch)
@@ -60,5 +63,13 @@ struct SymPlan {
         return !(2 * d == nsb && J < nsb / 2);
     }
 };
+
+// The next batch from offset d0 on, for `runs` workgroups and ncomp sums a
+// particle; false at the end, or at d0 = 0 where the slots do not suffice.
+bool sym_plan(h6_ctx ctx, int n, int block, int runs, int ncomp, int d0, SymPlan *plan);
+// The ordered form (one slot).
+SymPlan sym_plan_ordered(int n, int block);
+hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
+                             unsigned acc_mask);
 
 }  // namespace h6

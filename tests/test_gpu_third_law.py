@@ -3,15 +3,18 @@ one less than a superblock (512), odd and even numbers of superblocks, runs
 that cut a superblock, several batches of offsets, with the self mask.
 
 Bounds: 1e-12 relative to the oracle for a, j, s and 1e-11 for the start-up's
-crackle, as for the other evaluation kernels.
+crackle, as for the other evaluation kernels; the gradient 1e-11 of its largest
+component relative to the autograd reference, as in the other adjoint tests.
 """
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
+import oracle.adjoint_ref as ar
 from paper_1901_08532_amd import h6, ics
-from _gpu import gpu_evaluate, plummer_pred, vec_rel_err
+from _gpu import DEV, from_rows, gpu_evaluate, plummer_pred, to_rows, vec_rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +52,22 @@ def test_startup(n, eps):
     want = oracle.startup(x, v, m, eps * eps)
     for name, w in zip("ajsc", want):
         assert vec_rel_err(s.field(name), w).max() <= (1e-11 if name == "c" else 1e-12), name
+
+
+@pytest.mark.parametrize("n,eps", [(1, 1e-2), (2, 0.0), (64, 1e-2), (255, 1e-2), (257, 1e-2), (512, 0.0),
+                                   (769, 1e-2), (1030, 1e-2)])
+def test_gradient(n, eps):
+    rng = np.random.Generator(np.random.PCG64(920 + n))
+    x, v, a = (rng.normal(0, 1, (n, 3)) for _ in range(3))
+    m = rng.uniform(0.5, 1.5, n) / n
+    cot = [rng.normal(0, 1, (n, 3)) for _ in range(3)]
+    GP = torch.full((9, n), np.nan, dtype=torch.float64, device=DEV)
+    gm = torch.full((n,), 0.25, dtype=torch.float64, device=DEV)  # accumulated into
+    h6.Context(n, eps).h6_evaluate_vjp(to_rows(x, v, a), torch.from_numpy(m).to(DEV), to_rows(*cot), GP, gm)
+    if n == 1:  # no pair
+        assert not GP.any() and float(gm) == 0.25
+        return
+    ref = ar.pair_sums_vjp(x, v, m, eps * eps, cot, a=a, order=2)
+    for k, name in enumerate("xva"):
+        assert np.abs(from_rows(GP, k) - ref[name]).max() <= 1e-11 * np.abs(ref[name]).max(), name
+    assert np.abs(gm.cpu().numpy() - 0.25 - ref["m"]).max() <= 1e-11 * np.abs(ref["m"]).max()
