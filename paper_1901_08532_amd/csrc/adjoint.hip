@@ -201,19 +201,6 @@ struct CotPtrs {
 
 
 
-// Which pairs and which half of each pair a launch covers. With the
-// cotangents g nonzero only on an active set (block steps), the pair sum
-// splits into a source half m_k g_j over the active sources j, for every
-// target k (with the mass term), and a target half -m_j g_k over all
-// sources, for the active targets k: 2 n_act n pairs instead of n^2.
-//   kAll:        targets 0..n-1 against sources 0..n-1, both halves;
-//   kSrcHalf:    targets 0..n-1 against the sources list[0..n_list),
-//                their cotangents given by list rank;
-//   kTargetHalf: targets list[0..n_list) (cotangents by rank) against
-//                sources 0..n-1; outputs by rank, without the mass term.
-// Every mode skips the self pair.
-enum VjpMode { kAll = 0, kSrcHalf = 1, kTargetHalf = 2 };
-
 // Order-2 pair VJP, factored. With gh = m_k g_j - m_j g_k and
 //   G(g)  = gA.r + gJ.w + gS.u
 //         = gA.r + gJ.v - 3 alpha gJ.r + gS.a - 6 alpha gS.v + c18 gS.r,
@@ -226,12 +213,7 @@ enum VjpMode { kAll = 0, kSrcHalf = 1, kTargetHalf = 2 };
 //   d/da: R^-3 gS + sb r,
 // with sa = R^-5 Ga(gh), sb = -3 R^-5 gS.r, cr = -3 R^-5 G(gh) - 2 alpha sa
 // - 2 beta' sb, beta' = (v.v + r.a)/R^2. G, Ga and gS.r are linear in g, so
-// they come from six dot products with each of g_j and g_k; the explicit
-// terms of the target's own cotangent, -m_j R^-3 (...)(g_k), are
-// accumulated as three scalar sums (sum m_j R^-3, alpha m_j R^-3,
-// c18 m_j R^-3) and applied to g_k once per slice. MODE drops the g_j
-// part (kTargetHalf) or the g_k part (kSrcHalf); the mass term -R^-3 G(g_j)
-// goes with the g_j part.
+// they come from six dot products with each of g_j and g_k.
 __device__ __forceinline__ void g_terms(const double *g, const double *r, const double *v,
                                         const double *a, double a3, double a6, double c18,
                                         double a30, double &G, double &Ga, double &dSr) {
@@ -242,12 +224,12 @@ __device__ __forceinline__ void g_terms(const double *g, const double *r, const 
     Ga = fma(a30, dSr, fma(-6.0, dSv, -3.0 * dJr));
 }
 
-// The pair's gradient terms T (x, v, a) of both parts of gh and the mass terms
-// qj = R^-3 G(g_j), qk = R^-3 G(g_k).
-__device__ __forceinline__ void pair_vjp2_both(const double *r, const double *v, const double *a,
-                                               double r2, double mk, double mj, const double *gj,
-                                               const double *gk, double *T, double &qj,
-                                               double &qk) {
+// The pair's gradient terms T (x, v, a) and the mass terms qj = R^-3 G(g_j),
+// qk = R^-3 G(g_k); with GK false g_k is zero (gh = m_k g_j, no qk).
+template <bool GK>
+__device__ __forceinline__ void pair_vjp2(const double *r, const double *v, const double *a,
+                                          double r2, double mk, double mj, const double *gj,
+                                          const double *gk, double *T, double &qj, double &qk) {
     const double rho = rsqrt_f64(r2);
     const double rho2 = rho * rho;
     const double q3 = rho * rho2;
@@ -258,14 +240,18 @@ __device__ __forceinline__ void pair_vjp2_both(const double *r, const double *v,
     const double a6 = a3 + a3;
     const double c18 = fma(6.0 * a3, alpha, -3.0 * beta);
     const double a30 = 10.0 * a3;
-    double Gj, Gaj, dSj, Gk, Gak, dSk;
+    double Gj, Gaj, dSj;
     g_terms(gj, r, v, a, a3, a6, c18, a30, Gj, Gaj, dSj);
-    g_terms(gk, r, v, a, a3, a6, c18, a30, Gk, Gak, dSk);
     qj = q3 * Gj;
-    qk = q3 * Gk;
-    const double G = fma(mk, Gj, -mj * Gk);
-    const double Ga = fma(mk, Gaj, -mj * Gak);
-    const double dS = fma(mk, dSj, -mj * dSk);
+    double G = mk * Gj, Ga = mk * Gaj, dS = mk * dSj;
+    if constexpr (GK) {
+        double Gk, Gak, dSk;
+        g_terms(gk, r, v, a, a3, a6, c18, a30, Gk, Gak, dSk);
+        qk = q3 * Gk;
+        G = fma(-mj, Gk, G);
+        Ga = fma(-mj, Gak, Ga);
+        dS = fma(-mj, dSk, dS);
+    }
     const double qr = q3 * rho2;
     const double sa = qr * Ga;
     const double sb = (-3.0 * qr) * dS;
@@ -274,10 +260,12 @@ __device__ __forceinline__ void pair_vjp2_both(const double *r, const double *v,
     const double mkq = mk * q3, mjq = mj * q3;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        // R^-3 gh
-        const double hA = fma(mkq, gj[c], -mjq * gk[c]);
-        const double hJ = fma(mkq, gj[3 + c], -mjq * gk[3 + c]);
-        const double hS = fma(mkq, gj[6 + c], -mjq * gk[6 + c]);
+        double hA = mkq * gj[c], hJ = mkq * gj[3 + c], hS = mkq * gj[6 + c];  // R^-3 gh
+        if constexpr (GK) {
+            hA = fma(-mjq, gk[c], hA);
+            hJ = fma(-mjq, gk[3 + c], hJ);
+            hS = fma(-mjq, gk[6 + c], hS);
+        }
         T[c] = fma(sa, v[c], fma(sb, a[c], fma(cr, r[c], fma(-a3, hJ, fma(c18, hS, hA)))));
         T[3 + c] = fma(sa, r[c], fma(sb2, v[c], fma(-a6, hS, hJ)));
         T[6 + c] = fma(sb, r[c], hS);
@@ -286,8 +274,9 @@ __device__ __forceinline__ void pair_vjp2_both(const double *r, const double *v,
 
 // Particles and pairs of the all-pairs VJP for sym_body.h's walk: the pair's
 // terms T are added to the target's sums and subtracted from the source's.
-// Bound by FP64 issue: at order 2 about 200 operations an unordered pair
-// (10 of them DPP moves per 10 sums), against 2 x 153 in ordered form.
+// Bound by FP64 issue: at order 2 194 operations an unordered pair (20 of them
+// the DPP moves of ten sums), against 2 x 153 in ordered form. All pairs of
+// n = 16384: 1432 -> 870 us; of 420001: 0.92 -> 0.59 s.
 template <int ORDER>
 struct VjpOps {
     using Word = double;
@@ -349,7 +338,7 @@ struct VjpOps {
         r2 = self ? 1.0 : r2;
         const double mj = self ? 0.0 : f(3), mk = self ? 0.0 : t.m;
         if constexpr (ORDER == 2)
-            pair_vjp2_both(r, v, a, r2, mk, mj, gj, t.g, T, qj, qk);
+            pair_vjp2<true>(r, v, a, r2, mk, mj, gj, t.g, T, qj, qk);
         else
             pair_vjp<ORDER>(r, v, a, jr, r2, mk, mj, gj, t.g, T, qj, qk);
     }
@@ -384,232 +373,183 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))
     sym_run(VjpOps<ORDER>{src, cot, eps2}, P, partial);
 }
 
-template <int MODE>
-__device__ __forceinline__ void pair_vjp2(const double *r, const double *v, const double *a,
-                                          double r2, double mk, double mj, const double *gj,
-                                          const double *gk, double *acc, double *sacc) {
-    constexpr bool GJ = MODE != kTargetHalf, GK = MODE != kSrcHalf;
-    const double rho = rsqrt_f64(r2);
-    const double rho2 = rho * rho;
-    const double q3 = rho * rho2;
-    const double alpha = dot3(r, v) * rho2;
-    const double bp = (fma(v[2], v[2], fma(v[1], v[1], v[0] * v[0])) + dot3(r, a)) * rho2;
-    const double beta = fma(alpha, alpha, bp);
-    const double a3 = 3.0 * alpha;
-    const double a6 = a3 + a3;
-    const double c18 = fma(6.0 * a3, alpha, -3.0 * beta);
-    const double a30 = 10.0 * a3;
-    double G = 0.0, Ga = 0.0, dS = 0.0, Gj = 0.0;
-    if constexpr (GJ) {
-        double Gaj, dSj;
-        g_terms(gj, r, v, a, a3, a6, c18, a30, Gj, Gaj, dSj);
-        G = mk * Gj;
-        Ga = mk * Gaj;
-        dS = mk * dSj;
-    }
-    if constexpr (GK) {
-        double Gk, Gak, dSk;
-        g_terms(gk, r, v, a, a3, a6, c18, a30, Gk, Gak, dSk);
-        G = fma(-mj, Gk, G);
-        Ga = fma(-mj, Gak, Ga);
-        dS = fma(-mj, dSk, dS);
-    }
-    const double qr = q3 * rho2;
-    const double sa = qr * Ga;
-    const double sb = (-3.0 * qr) * dS;
-    const double cr = fma(-3.0 * qr, G, fma(-2.0 * alpha, sa, (-2.0 * bp) * sb));
-    const double sb2 = sb + sb;
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        acc[c] = fma(sa, v[c], fma(sb, a[c], fma(cr, r[c], acc[c])));
-        acc[3 + c] = fma(sa, r[c], fma(sb2, v[c], acc[3 + c]));
-        acc[6 + c] = fma(sb, r[c], acc[6 + c]);
-    }
-    if constexpr (GJ) {
-        const double kq = mk * q3;
-        const double kqa = -a3 * kq, kqc = c18 * kq;
-        const double kqa6 = kqa + kqa;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            acc[c] = fma(kq, gj[c], fma(kqa, gj[3 + c], fma(kqc, gj[6 + c], acc[c])));
-            acc[3 + c] = fma(kq, gj[3 + c], fma(kqa6, gj[6 + c], acc[3 + c]));
-            acc[6 + c] = fma(kq, gj[6 + c], acc[6 + c]);
-        }
-        acc[9] = fma(-q3, Gj, acc[9]);
-    }
-    if constexpr (GK) {
-        const double jq = mj * q3;
-        sacc[0] += jq;
-        sacc[1] = fma(jq, alpha, sacc[1]);
-        sacc[2] = fma(jq, c18, sacc[2]);
-    }
+// ---------------------------------------------------------------- active sets
+// VJP of the evaluation of an active set (block steps): the cotangents g are
+// nonzero only on the active particles j, so the pair (k, j), k any particle
+// and j an active one, has gh = m_k g_j. Its terms go to k with one sign and
+// to j with the other, and the mass term -Q . g_j to k: every (k, j) pair is
+// taken once (as two halves, the pairs of each active particle as source and
+// as target, it was visited twice).
+//
+// A wave holds 64 particles k, one a lane; chunks of R active particles go
+// round the lanes as in sym_body.h, in rings of R lanes (R = 4 or 16 for small
+// blocks: a chunk of 64 would be mostly padding). The four waves of a
+// workgroup take four tiles of k (WK = 4), or for small blocks the four
+// quarters of a chunk's steps on one tile (WK = 1), so that the n / 64 tiles
+// of a small system still fill the GPU. Workgroup (x, y) takes tile group x
+// and the y-th part of the chunks. Sums of k are added to the outputs when
+// one part covers all chunks, else they go through the partial sums, as the
+// sums of j do (a slot per tile group).
+//
+// Bound by latency for small blocks, by FP64 issue (150 operations a pair) for
+// large ones. One h6_evaluate_vjp_active call, the two halves before and this:
+// 4 active of 4096 190 -> 11 us, 300 of 4096 270 -> 26 us, 1000 of 16384 322 ->
+// 111 us, 16000 of 65536 10.3 -> 5.8 ms.
+constexpr int kActThreads = 256;
+
+// The value of the next lane of a ring of R lanes.
+template <int R>
+__device__ __forceinline__ double ring_next(double v) {
+    // wave rotate left by one; row rotate right by 15; quad permutation 1 2 3 0
+    constexpr int kCtrl = R == 64 ? 0x134 : R == 16 ? 0x12F : 0x39;
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), kCtrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), kCtrl, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
 }
 
-template <int ORDER, int BLOCK, int MODE = kAll>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(2))) void k_eval_vjp(
-    SrcPtrs src, CotPtrs cot, int n, const int32_t *__restrict__ list, int n_list, double eps2,
-    int slice_len, OutPtrs out, int64_t slice_stride, unsigned acc_mask) {
-    using T = VTraits<ORDER>;
-    constexpr int NG = T::NG, NOUT = T::NOUT, NF = T::NF;
-    constexpr int NFP = (NF + 1) & ~1;  // record padded to whole double2
-    constexpr bool MASS = MODE != kTargetHalf;
-    constexpr bool SKIP = MODE != kAll;  // the list modes identify the self pair by particle
-    __shared__ double2 tile[BLOCK * NFP / 2];
-    const int tid = threadIdx.x;
-    const int k = (int)blockIdx.x * BLOCK + tid;
-    const int n_tgt = MODE == kTargetHalf ? n_list : n;
-    const int n_src = MODE == kSrcHalf ? n_list : n;
-    const int kr = k < n_tgt ? k : n_tgt - 1;                  // target rank
-    const int kc = MODE == kTargetHalf ? list[kr] : kr;        // target particle
-
-    double xk[3], vk[3], ak[3] = {0, 0, 0}, jk[3] = {0, 0, 0}, gk[NG];
+template <int R, int WK>
+__global__ __launch_bounds__(kActThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_active(
+    SrcPtrs src, CotPtrs cot, int n, const int32_t *__restrict__ list, int n_act, double eps2,
+    int group0, int part_chunks, double *__restrict__ part_j, double *__restrict__ part_k,
+    OutPtrs out) {
+    static_assert(R == 4 || R == 16 || R == 64, "ring of a quad, a row or a wave");
+    constexpr int NW = 18;                            // words of a source: x, v, a, g
+    constexpr int kSteps = WK == 4 ? R : R / 4;       // steps of a wave per chunk
+    constexpr int NLOAD = (NW + 3) / 4;
+    __shared__ double2 rec[NW / 2 * 2 * R];           // records twice over (no wrap)
+    __shared__ double sums[4][10][64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int group = group0 + (int)blockIdx.x;
+    const int kt = (group * WK + (WK == 4 ? wave : 0)) * 64;
+    const int k = kt + lane, kc = k < n ? k : n - 1;
+    const int sa = WK == 4 ? 0 : wave * kSteps, sb = sa + kSteps;
+    // lane's place in its ring
+    const int l = lane & (R - 1);
+    double xk[3], vk[3], ak[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        xk[c] = src.x[c][kc];
+        xk[c] = k < n ? src.x[c][kc] : -kPadPosVjp;
         vk[c] = src.v[c][kc];
-        if constexpr (ORDER >= 2) ak[c] = src.a[c][kc];
-        if constexpr (ORDER == 3) jk[c] = src.j[c][kc];
+        ak[c] = src.a[c][kc];
     }
-    const double mk = src.m[kc];
+    const double mk = k < n ? src.m[kc] : 0.0;
+    const double *field[NLOAD] = {};
+    bool by_rank[NLOAD] = {};
 #pragma unroll
-    for (int q = 0; q < NG; ++q) gk[q] = MODE == kSrcHalf ? 0.0 : cot.g[q][kr];
-
-    double acc[NOUT], hi[NOUT], lo[NOUT];
+    for (int f = 0; f < NW; ++f)
+        if (f % 4 == wave) {
+            field[f / 4] = f < 3 ? src.x[f] : f < 6 ? src.v[f - 3] : f < 9 ? src.a[f - 6] : cot.g[f - 9];
+            by_rank[f / 4] = f >= 9;
+        }
+    double hi[10], lo[10];
 #pragma unroll
-    for (int q = 0; q < NOUT; ++q) acc[q] = hi[q] = lo[q] = 0.0;
-    // order 2: scalar sums for the target's own cotangent (pair_vjp2)
-    constexpr bool SK = ORDER == 2 && MODE != kSrcHalf;
-    double sacc[3] = {0, 0, 0}, shi[3] = {0, 0, 0}, slo[3] = {0, 0, 0};
-
-    const int jb0 = (int)blockIdx.y * slice_len;
-    const int je = min(n_src, jb0 + slice_len);
-    __shared__ int tile_id[BLOCK];  // source particle of each record (self test)
-    for (int jt = jb0; jt < je; jt += BLOCK) {
-        __syncthreads();
-        {
-            double f[NFP];
-            const int jj = jt + tid;  // source rank
-            if (jj < je) {
-                const int pj = MODE == kSrcHalf ? list[jj] : jj;
-                if constexpr (SKIP) tile_id[tid] = pj;
-                int o = 0;
+    for (int q = 0; q < 10; ++q) hi[q] = lo[q] = 0.0;
+    const int chunks = (n_act + R - 1) / R;
+    const int c0 = (int)blockIdx.y * part_chunks, c1 = min(chunks, c0 + part_chunks);
+    for (int c = c0; c < c1; ++c) {
+        const int rank = c * R + l;
+        const int id = rank < n_act ? list[rank] : -1;
+        double *rd = reinterpret_cast<double *>(rec);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) f[o++] = src.x[c][pj];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) f[o++] = src.v[c][pj];
-                if constexpr (ORDER >= 2) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) f[o++] = src.a[c][pj];
-                }
-                if constexpr (ORDER == 3) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) f[o++] = src.j[c][pj];
-                }
-                f[o++] = src.m[pj];
-#pragma unroll
-                for (int q = 0; q < NG; ++q) f[o++] = MODE == kTargetHalf ? 0.0 : cot.g[q][jj];
-            } else {
-                if constexpr (SKIP) tile_id[tid] = -1;
-#pragma unroll
-                for (int q = 0; q < NFP; ++q) f[q] = 0.0;
-                f[0] = f[1] = f[2] = kPadPosVjp;  // far and massless, zero cotangent
+        for (int q = 0; q < NLOAD; ++q) {
+            const int f = wave + 4 * q;
+            if (f < NW && lane < R) {
+                const double w = id < 0 ? (f < 3 ? kPadPosVjp : 0.0) : field[q][by_rank[q] ? rank : id];
+                const int at = ((f >> 1) * 2 * R + lane) * 2 + (f & 1);
+                rd[at] = w;
+                rd[at + 2 * R] = w;
             }
-            if (NFP > NF) f[NFP - 1] = 0.0;
-#pragma unroll
-            for (int q = 0; q < NFP / 2; ++q) tile[tid * (NFP / 2) + q] = make_double2(f[2 * q], f[2 * q + 1]);
         }
         __syncthreads();
-        auto tile_pairs = [&](auto test_self) {
-            for (int q = 0; q < BLOCK; ++q) {
-                double f[NFP];
+        double acc[10], accj[9];
 #pragma unroll
-                for (int p = 0; p < NFP / 2; ++p) {
-                    const double2 d = tile[q * (NFP / 2) + p];
-                    f[2 * p] = d.x;
-                    f[2 * p + 1] = d.y;
+        for (int q = 0; q < 10; ++q) acc[q] = 0.0;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) accj[q] = 0.0;
+        auto steps = [&](auto test_self) {
+            int idr = id;
+            if constexpr (decltype(test_self)::value) {
+                // the particle of step sa, one lane on each step
+                idr = __shfl(id, (lane & ~(R - 1)) | ((l + sa) & (R - 1)), 64);
+            }
+#pragma unroll 1
+            for (int s = sa; s < sb; ++s) {
+                double f[NW];
+#pragma unroll
+                for (int q = 0; q < NW / 2; ++q) {
+                    const double2 d = rec[q * 2 * R + l + s];
+                    f[2 * q] = d.x;
+                    f[2 * q + 1] = d.y;
                 }
-                int o = 0;
-                double r[3], v[3], a[3] = {0, 0, 0}, jr[3] = {0, 0, 0};
+                double r[3], v[3], a[3], T[9], qj, qk;
 #pragma unroll
-                for (int c = 0; c < 3; ++c) r[c] = f[o++] - xk[c];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) v[c] = f[o++] - vk[c];
-                if constexpr (ORDER >= 2) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) a[c] = f[o++] - ak[c];
+                for (int cc = 0; cc < 3; ++cc) {
+                    r[cc] = f[cc] - xk[cc];
+                    v[cc] = f[3 + cc] - vk[cc];
+                    a[cc] = f[6 + cc] - ak[cc];
                 }
-                if constexpr (ORDER == 3) {
-#pragma unroll
-                    for (int c = 0; c < 3; ++c) jr[c] = f[o++] - jk[c];
-                }
-                // The self pair is left out explicitly: m_k g_k - m_k g_k is not
-                // exactly zero once the first product is fused (fma keeps its
-                // rounding error), and dQ/dr at r = 0 is of order eps^-3. With
-                // both masses set to zero gh is exactly zero; r, v, a, jr are zero
-                // there, so Q and the mass term are too (R^2 set to 1 keeps them
-                // finite when eps = 0).
-                const bool self = decltype(test_self)::value &&
-                                  (MODE == kAll ? (jt + q) == k : tile_id[q] == kc);
-                const double mj = self ? 0.0 : f[o];
-                const double mkp = self ? 0.0 : mk;
-                ++o;
-                const double *gj = &f[o];
                 double r2 = fma(r[2], r[2], fma(r[1], r[1], fma(r[0], r[0], eps2)));
-                r2 = self ? 1.0 : r2;
-                if constexpr (ORDER == 2) {
-                    pair_vjp2<MODE>(r, v, a, r2, mkp, mj, gj, gk, acc, sacc);
-                } else {
-                    double gh[NG];
-#pragma unroll
-                    for (int p = 0; p < NG; ++p) {
-                        if constexpr (MODE == kAll) gh[p] = fma(mkp, gj[p], -mj * gk[p]);
-                        else if constexpr (MODE == kSrcHalf) gh[p] = mkp * gj[p];
-                        else gh[p] = -mj * gk[p];
-                    }
-                    double *xb = acc, *vb = acc + 3;
-                    double *ab = ORDER >= 2 ? acc + 6 : acc;  // unused for order 1
-                    double *jb = ORDER == 3 ? acc + 9 : acc;  // unused below order 3
-                    pair_vjp<ORDER, MASS>(r, v, a, jr, r2, gh, gj, xb, vb, ab, jb, acc[NOUT - 1]);
+                double m = mk;
+                if constexpr (decltype(test_self)::value) {
+                    // the self pair left out: a zero mass makes every term an
+                    // exact zero (r, v, a vanish in qj)
+                    const bool self = idr == k;
+                    r2 = self ? 1.0 : r2;
+                    m = self ? 0.0 : m;
+                    idr = __shfl(idr, (lane & ~(R - 1)) | ((l + 1) & (R - 1)), 64);
                 }
+                pair_vjp2<false>(r, v, a, r2, m, 0.0, f + 9, nullptr, T, qj, qk);
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    acc[q] += T[q];
+                    accj[q] = ring_next<R>(accj[q] - T[q]);
+                }
+                acc[9] -= qj;
             }
         };
-        // in the all-pairs mode a self pair can only occur in the diagonal
-        // tile (slices are whole tiles aligned with the target blocks)
-        if (MODE != kAll || jt == (int)blockIdx.x * BLOCK)
-            tile_pairs(std::true_type{});
+        if (__any(id >= kt && id < kt + 64))
+            steps(std::true_type{});
         else
-            tile_pairs(std::false_type{});
+            steps(std::false_type{});
 #pragma unroll
-        for (int q = 0; q < NOUT; ++q) {
-            two_sum_into(hi[q], lo[q], acc[q]);
-            acc[q] = 0.0;
-        }
-        if constexpr (SK) {
+        for (int q = 0; q < 10; ++q) two_sum_into(hi[q], lo[q], acc[q]);
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                two_sum_into(shi[q], slo[q], sacc[q]);
-                sacc[q] = 0.0;
-            }
-        }
-    }
-    if constexpr (SK) {
-        // the target's own cotangent: -S0 gA + 3 S1 gJ - S2 gS into xbar,
-        // -S0 gJ + 6 S1 gS into vbar, -S0 gS into abar
-        const double S0 = shi[0] + slo[0], S1 = shi[1] + slo[1], S2 = shi[2] + slo[2];
+        for (int q = 0; q < 9; ++q) sums[wave][q][(lane & ~(R - 1)) | ((l + sb) & (R - 1))] = accj[q];
+        __syncthreads();
+        // the chunk's sums over the waves and rings, in order
+        for (int e = tid; e < 9 * R; e += kActThreads) {
+            const int q = e / R, i = e % R;
+            double hs = 0.0, hc = 0.0;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            two_sum_into(hi[c], lo[c], fma(-S0, gk[c], fma(3.0 * S1, gk[3 + c], -S2 * gk[6 + c])));
-            two_sum_into(hi[3 + c], lo[3 + c], fma(-S0, gk[3 + c], 6.0 * S1 * gk[6 + c]));
-            two_sum_into(hi[6 + c], lo[6 + c], -S0 * gk[6 + c]);
+            for (int w = 0; w < 4; ++w)
+#pragma unroll
+                for (int g = 0; g < 64 / R; ++g) two_sum_into(hs, hc, sums[w][q][g * R + i]);
+            if (c * R + i < n_act)
+                part_j[((int64_t)blockIdx.x * 9 + q) * n_act + c * R + i] = hs + hc;
         }
     }
-    if (k < n_tgt) {
-        const int64_t soff = (int64_t)blockIdx.y * slice_stride;
+    auto put = [&](int q, int kk, double val) {
+        if (part_k)
+            part_k[((int64_t)blockIdx.y * 10 + q) * n + kk] = val;
+        else
+            out.p[q][kk] += val;
+    };
+    if constexpr (WK == 4) {
+        if (k < n)
 #pragma unroll
-        for (int q = 0; q < (MASS ? NOUT : NOUT - 1); ++q) {
-            double *dst = &out.p[q][soff + k];
-            const double val = hi[q] + lo[q];
-            *dst = ((acc_mask >> q) & 1u) ? *dst + val : val;
+            for (int q = 0; q < 10; ++q) put(q, k, hi[q] + lo[q]);
+    } else {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 10; ++q) sums[wave][q][lane] = hi[q] + lo[q];
+        __syncthreads();
+        for (int e = tid; e < 640; e += kActThreads) {
+            const int q = e / 64, i = e % 64;
+            double hs = 0.0, hc = 0.0;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) two_sum_into(hs, hc, sums[w][q][i]);
+            if (kt + i < n) put(q, kt + i, hs + hc);
         }
     }
 }
@@ -674,70 +614,6 @@ __global__ __launch_bounds__(256) void k_predict_dt_vjp(h6_state cot, int n, h6_
 }
 
 int ceil_div_i(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-// Sum of slice partials [slice][comp][rank] (ld = n_list) added to
-// out.p[comp][list[rank]]: the target half's results scattered to the
-// particles (list entries are distinct, so no two ranks meet).
-__global__ __launch_bounds__(256) void k_reduce_scatter(const double *__restrict__ partial,
-                                                        int64_t ld, int n_split, int ncomp,
-                                                        const int32_t *__restrict__ list,
-                                                        int n_list, OutPtrs out) {
-    const int64_t total = (int64_t)ncomp * n_list;
-    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-         idx += (int64_t)gridDim.x * blockDim.x) {
-        const int c = (int)(idx / n_list);
-        const int k = (int)(idx - (int64_t)c * n_list);
-        double hi = 0.0, lo = 0.0;
-        for (int sl = 0; sl < n_split; ++sl)
-            two_sum_into(hi, lo, partial[((int64_t)sl * ncomp + c) * ld + k]);
-        out.p[c][list[k]] += hi + lo;
-    }
-}
-
-template <int ORDER, int MODE>
-hipError_t launch_vjp_mode(h6_ctx ctx, const SrcPtrs &src, const CotPtrs &cot, int n,
-                           const int32_t *list, int n_list, const OutPtrs &out,
-                           unsigned acc_mask) {
-    constexpr int BLOCK = 128;
-    constexpr int NOUT = VTraits<ORDER>::NOUT;
-    constexpr int NW = MODE == kTargetHalf ? NOUT - 1 : NOUT;  // outputs written
-    const int n_tgt = MODE == kTargetHalf ? n_list : n;
-    const int n_src = MODE == kSrcHalf ? n_list : n;
-    if (n_tgt <= 0 || n_src <= 0) return hipSuccess;
-    const int blocks_i = ceil_div_i(n_tgt, BLOCK);
-    int split = balanced_split(ctx, 2, BLOCK, n_src, blocks_i);
-    const int64_t cap = ctx->partial_cap / ((int64_t)NW * n_tgt);
-    if (split > cap) split = (int)std::max<int64_t>(1, cap);
-    int slice_len = ceil_div_i(ceil_div_i(n_src, split), BLOCK) * BLOCK;
-    split = ceil_div_i(n_src, slice_len);
-    // the target half always goes through the partials (scattered after)
-    const bool direct = split == 1 && MODE != kTargetHalf;
-    OutPtrs dst;
-    int64_t slice_stride = 0;
-    unsigned mask = acc_mask;
-    if (direct) {
-        dst = out;
-    } else {
-        for (int c = 0; c < kMaxOut; ++c) dst.p[c] = nullptr;
-        for (int c = 0; c < NW; ++c) dst.p[c] = ctx->partial + (int64_t)c * n_tgt;
-        slice_stride = (int64_t)NW * n_tgt;
-        mask = 0u;  // partials are overwritten; the reduction applies acc_mask
-    }
-    dim3 grid(blocks_i, split);
-    hipLaunchKernelGGL((k_eval_vjp<ORDER, BLOCK, MODE>), grid, dim3(BLOCK), 0, ctx->stream, src,
-                       cot, n, list, n_list, ctx->eps2, slice_len, dst, slice_stride, mask);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || direct) return e;
-    if constexpr (MODE == kTargetHalf) {
-        int rb = ceil_div_i((int64_t)NW * n_tgt, 256);
-        if (rb > 4096) rb = 4096;
-        hipLaunchKernelGGL(k_reduce_scatter, dim3(rb), dim3(256), 0, ctx->stream, ctx->partial,
-                           (int64_t)n_tgt, split, NW, list, n_tgt, out);
-        return hipGetLastError();
-    } else {
-        return launch_reduce(ctx, split, NOUT, 0, n_tgt, out, acc_mask);
-    }
-}
 
 // VJP of the sums over all pairs, each unordered pair once; in ordered form
 // where the partial sums hold too few slots for that.
@@ -1018,11 +894,57 @@ hipError_t launch_eval_vjp_active(h6_ctx ctx, const SrcPtrs &src, const double *
                                   const int32_t *active, int n_act, const OutPtrs &out) {
     CotPtrs cp;
     for (int q = 0; q < 9; ++q) cp.g[q] = cot[q];
-    // source half with the mass term, added to all ten outputs
-    hipError_t e = launch_vjp_mode<2, kSrcHalf>(ctx, src, cp, n, active, n_act, out, 0x3ffu);
-    if (e != hipSuccess) return e;
-    // target half, scattered (added) to the active particles
-    return launch_vjp_mode<2, kTargetHalf>(ctx, src, cp, n, active, n_act, out, 0x3ffu);
+    // ring: the least padding that does not multiply the chunks' fixed cost
+    const int ring = n_act <= 4 ? 4 : n_act <= 48 ? 16 : 64;
+    const int chunks = ceil_div_i(n_act, ring);
+    const int64_t cu = ctx->n_cu;
+    // four tiles a workgroup once they fill the GPU twice over
+    const int wk = ring == 64 && (int64_t)ceil_div_i(n, 256) * chunks >= 4 * cu ? 4 : 1;
+    const int groups = ceil_div_i(n, 64 * wk);
+    // one part of the chunks per workgroup, or more parts to fill the GPU at
+    // the price of a reduction. Times in us: a step 0.27 alone on its SIMD, 0.9
+    // a chunk for staging and sums, 5 a reduction and 1 per 3 MB it reads. The
+    // tile groups go in batches whose sums of j fit the scratch.
+    const double tc = 0.27 * (wk == 4 ? ring : ring / 4) + 0.9;
+    int parts = 1, batch = groups;
+    double best = 1e300;
+    for (int p = 1; p <= chunks && p <= 64; p *= 2) {
+        const int64_t left = ctx->partial_cap - (p > 1 ? (int64_t)p * 10 * n : 0);
+        const int64_t fit = left / ((int64_t)9 * n_act);
+        if (fit < 1) break;
+        const int bt = (int)std::min<int64_t>(groups, fit);
+        const double one = (double)ceil_div_i((int64_t)bt * p, cu) * ceil_div_i(chunks, p) * tc +
+                           5.0 + 2.4e-5 * bt * (double)n_act;
+        const double t = ceil_div_i(groups, bt) * one + (p > 1 ? 5.0 + 2.7e-5 * p * (double)n : 0.0);
+        if (t < best) {
+            best = t;
+            parts = p;
+            batch = bt;
+        }
+    }
+    const int part_chunks = ceil_div_i(chunks, parts);
+    parts = ceil_div_i(chunks, part_chunks);
+    double *part_k = parts > 1 ? ctx->partial : nullptr;
+    double *part_j = ctx->partial + (parts > 1 ? (int64_t)parts * 10 * n : 0);
+    for (int g0 = 0; g0 < groups; g0 += batch) {
+        const int gn = std::min(batch, groups - g0);
+        const dim3 grid(gn, parts);
+#define H6_ACT(R, W)                                                                            \
+    if (ring == R && wk == W)                                                                   \
+        hipLaunchKernelGGL((k_vjp_active<R, W>), grid, dim3(kActThreads), 0, ctx->stream, src,  \
+                           cp, n, active, n_act, ctx->eps2, g0, part_chunks, part_j, part_k,    \
+                           out);
+        H6_ACT(4, 1)
+        H6_ACT(16, 1)
+        H6_ACT(64, 1)
+        H6_ACT(64, 4)
+#undef H6_ACT
+        hipError_t e = hipGetLastError();
+        // the sums of j, added to the active particles
+        if (e == hipSuccess) e = launch_reduce(ctx, part_j, gn, 9, 0, n_act, out, 0x1ffu, active);
+        if (e != hipSuccess) return e;
+    }
+    return parts > 1 ? launch_reduce(ctx, part_k, parts, 10, 0, n, out, 0x3ffu, nullptr) : hipSuccess;
 }
 
 hipError_t launch_correct_block_vjp(h6_ctx ctx, h6_state *cot, const int32_t *active, int n_act,

@@ -66,7 +66,8 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4)))
 // Neumaier sum over the slices with all loads issued up front.
 __global__ __launch_bounds__(256) void k_reduce_slices(const double *__restrict__ partial,
                                                        int64_t ld, int n_split, int ncomp, int out0,
-                                                       int n_act, OutPtrs out, unsigned acc_mask) {
+                                                       int n_act, OutPtrs out, unsigned acc_mask,
+                                                       const int32_t *__restrict__ list) {
     const int64_t total = (int64_t)ncomp * n_act;
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * blockDim.x) {
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const double *__restrict_
                 s = t;
             }
         }
-        double *dst = &out.p[out0 + c][k];
+        double *dst = &out.p[out0 + c][list ? list[k] : k];
         *dst = ((acc_mask >> c) & 1u) ? *dst + (s + comp) : s + comp;
     }
 }
@@ -96,7 +97,7 @@ __global__ __launch_bounds__(256) void k_reduce_slices(const double *__restrict_
 constexpr int kRedWaves = 8;
 __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_slices_many(
     const double *__restrict__ partial, int n_split, int ncomp, int out0, int n_act, OutPtrs out,
-    unsigned acc_mask) {
+    unsigned acc_mask, const int32_t *__restrict__ list) {
     __shared__ double2 part[64 * kRedWaves];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int64_t total = (int64_t)ncomp * n_act;
@@ -123,7 +124,8 @@ __global__ __launch_bounds__(64 * kRedWaves) void k_reduce_slices_many(
 #pragma unroll
     for (int q = 1; q < kRedWaves; ++q) comp_merge(s, comp, part[q * 64 + lane].x, part[q * 64 + lane].y);
     const int c = (int)(idx / n_act);
-    double *dst = &out.p[out0 + c][idx - (int64_t)c * n_act];
+    const int k = (int)(idx - (int64_t)c * n_act);
+    double *dst = &out.p[out0 + c][list ? list[k] : k];
     *dst = ((acc_mask >> c) & 1u) ? *dst + (s + comp) : s + comp;
 }
 
@@ -458,20 +460,20 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
     if (e == hipSuccess && ctx->prof)
         e = prof_end(ctx, ev0, ev1, order, cfg, precision, n_act, (double)n_act * (double)n);
     if (e != hipSuccess || cfg.n_split == 1) return e;
-    return launch_reduce(ctx, cfg.n_split, ncomp, out0, n_act, out, 0u);
+    return launch_reduce(ctx, ctx->partial, cfg.n_split, ncomp, out0, n_act, out, 0u, nullptr);
 }
 
-hipError_t launch_reduce(h6_ctx ctx, int n_split, int ncomp, int out0, int n_act,
-                         const OutPtrs &out, unsigned acc_mask) {
+hipError_t launch_reduce(h6_ctx ctx, const double *partial, int n_split, int ncomp, int out0,
+                         int n_act, const OutPtrs &out, unsigned acc_mask, const int32_t *list) {
     const int64_t total = (int64_t)ncomp * n_act;
     if (n_split >= kManyReduceMinSplit) {
         hipLaunchKernelGGL(k_reduce_slices_many, dim3(ceil_div(total, 64)), dim3(64 * kRedWaves), 0,
-                           ctx->stream, ctx->partial, n_split, ncomp, out0, n_act, out, acc_mask);
+                           ctx->stream, partial, n_split, ncomp, out0, n_act, out, acc_mask, list);
     } else {
         int rb = ceil_div(total, 256);
         if (rb > 4096) rb = 4096;
-        hipLaunchKernelGGL(k_reduce_slices, dim3(rb), dim3(256), 0, ctx->stream, ctx->partial,
-                           (int64_t)n_act, n_split, ncomp, out0, n_act, out, acc_mask);
+        hipLaunchKernelGGL(k_reduce_slices, dim3(rb), dim3(256), 0, ctx->stream, partial,
+                           (int64_t)n_act, n_split, ncomp, out0, n_act, out, acc_mask, list);
     }
     return hipGetLastError();
 }

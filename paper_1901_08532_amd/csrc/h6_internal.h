@@ -200,10 +200,11 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
                        EvalConfig *used);
 EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n_act);
 // Compensated sum over n_split slices of ncomp partial arrays of n_act
-// targets (ctx->partial, [slice][comp][target]) into out.p[out0 + comp];
-// bit c of acc_mask adds to the existing value instead of overwriting.
-hipError_t launch_reduce(h6_ctx ctx, int n_split, int ncomp, int out0, int n_act,
-                         const OutPtrs &out, unsigned acc_mask);
+// targets (partial, [slice][comp][target]) into out.p[out0 + comp], at the
+// target's rank or at list[rank] (distinct entries); bit c of acc_mask adds to
+// the existing value instead of overwriting.
+hipError_t launch_reduce(h6_ctx ctx, const double *partial, int n_split, int ncomp, int out0,
+                         int n_act, const OutPtrs &out, unsigned acc_mask, const int32_t *list);
 // Whether h6_set_eval_config named a launch shape.
 inline bool eval_shape_forced(h6_ctx ctx) {
     return ctx->cfg_block || ctx->cfg_ipl || ctx->cfg_split || ctx->cfg_small >= 0;
