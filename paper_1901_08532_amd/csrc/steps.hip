@@ -62,16 +62,24 @@ __global__ __launch_bounds__(256) void k_initial_steps(h6_state st, int n, doubl
 }
 
 // ---------------------------------------------------------------- scheduler
-// Two passes over fixed chunks of kSchedChunk particles per workgroup:
-//   1. each chunk finds its minimum due time t + dt and how many of its
-//      particles are due then; the last workgroup to finish takes the
+// Up to kSchedSmall particles, one workgroup finds the earliest due time
+// t + dt and writes the particles due then, in index order. Beyond, two passes
+// over fixed chunks of kSchedChunk particles per workgroup:
+//   1. each chunk finds its minimum due time and how many of its particles
+//      are due then; the last workgroup to finish takes the
 //      global minimum t_next, gives every chunk whose minimum equals t_next
 //      an offset (exclusive scan of their counts, in chunk order) and
 //      publishes t_next and n_act;
 //   2. each such chunk writes its due particles, in index order, at its
 //      offset.
+// Both are bound by latency: due times are read once and held in registers,
+// and the scan over chunks is parallel (n = 4096: 15 -> 7 us for both).
 constexpr int kSchedThreads = 256;
-constexpr int kSchedChunk = kSchedThreads * 16;
+constexpr int kSchedPer = 16;  // particles of a chunk per thread
+constexpr int kSchedChunk = kSchedThreads * kSchedPer;
+constexpr int kSchedSmallThreads = 1024;
+constexpr int kSchedSmallPer = 8;
+constexpr int kSchedSmall = kSchedSmallThreads * kSchedSmallPer;
 
 // Ordered hand-off between workgroups of one launch: every workgroup
 // publishes its result, then increments the counter with a device-scope
@@ -107,15 +115,16 @@ __device__ __forceinline__ int64_t wave_min_i64(int64_t v) {
     return v;
 }
 
+template <int THREADS>
 __device__ __forceinline__ int64_t block_min_i64(int64_t v) {
-    __shared__ int64_t wmin[kSchedThreads / 64];
+    __shared__ int64_t wmin[THREADS / 64];
     v = wave_min_i64(v);
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) wmin[w] = v;
     __syncthreads();
     int64_t r = wmin[0];
 #pragma unroll
-    for (int q = 1; q < kSchedThreads / 64; ++q) r = wmin[q] < r ? wmin[q] : r;
+    for (int q = 1; q < THREADS / 64; ++q) r = wmin[q] < r ? wmin[q] : r;
     __syncthreads();
     return r;
 }
@@ -142,15 +151,18 @@ __global__ __launch_bounds__(kSchedThreads) void k_sched_select(const int64_t *_
                                                                 unsigned *counter, int64_t *out,
                                                                 int64_t *host_out) {
     const int base = blockIdx.x * kSchedChunk;
-    const int end = min(n, base + kSchedChunk);
-    int64_t v = INT64_MAX;
-    for (int i = base + threadIdx.x; i < end; i += kSchedThreads) {
-        const int64_t due = t[i] + dt[i];
-        v = due < v ? due : v;
+    int64_t due[kSchedPer], v = INT64_MAX;
+#pragma unroll
+    for (int r = 0; r < kSchedPer; ++r) {
+        const int i = base + r * kSchedThreads + threadIdx.x;
+        due[r] = i < n ? t[i] + dt[i] : INT64_MAX;
+        v = due[r] < v ? due[r] : v;
     }
-    const int64_t cmin = block_min_i64(v);
+    const int64_t cmin = block_min_i64<kSchedThreads>(v);
     int cnt = 0;
-    for (int i = base + threadIdx.x; i < end; i += kSchedThreads) cnt += (t[i] + dt[i] == cmin);
+#pragma unroll
+    for (int r = 0; r < kSchedPer; ++r)
+        cnt += (base + r * kSchedThreads + (int)threadIdx.x < n && due[r] == cmin);
     cnt = block_sum_i32(cnt);
     if (threadIdx.x == 0) {
         chunk_min[blockIdx.x] = cmin;
@@ -162,18 +174,85 @@ __global__ __launch_bounds__(kSchedThreads) void k_sched_select(const int64_t *_
         const int64_t x = load_agent(&chunk_min[b]);
         r = x < r ? x : r;
     }
-    r = block_min_i64(r);
-    if (threadIdx.x == 0) {
-        // exclusive scan over the (few hundred at most) chunks that hold t_next
-        int run = 0;
-        for (int b = 0; b < (int)gridDim.x; ++b) {
-            const bool has = load_agent(&chunk_min[b]) == r;
-            chunk_off[b] = has ? run : -1;
-            run += has ? load_agent(&chunk_cnt[b]) : 0;
+    r = block_min_i64<kSchedThreads>(r);
+    // exclusive scan over the chunks that hold t_next, kSchedThreads at a time
+    __shared__ int wtot[kSchedThreads / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int run = 0;
+    for (int b0 = 0; b0 < (int)gridDim.x; b0 += kSchedThreads) {
+        const int b = b0 + threadIdx.x;
+        const bool has = b < (int)gridDim.x && load_agent(&chunk_min[b]) == r;
+        const int c = has ? load_agent(&chunk_cnt[b]) : 0;
+        int incl = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            incl += lane >= off ? o : 0;
         }
+        if (lane == 63) wtot[w] = incl;
+        __syncthreads();
+        int before = 0, total = 0;
+#pragma unroll
+        for (int q = 0; q < kSchedThreads / 64; ++q) {
+            before += q < w ? wtot[q] : 0;
+            total += wtot[q];
+        }
+        if (b < (int)gridDim.x) chunk_off[b] = has ? run + before + incl - c : -1;
+        run += total;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
         out[0] = host_out[0] = r;
         out[1] = host_out[1] = run;
     }
+}
+
+// Select and compact in one workgroup (n <= kSchedSmall).
+__global__ __launch_bounds__(kSchedSmallThreads) void k_sched_small(const int64_t *__restrict__ t,
+                                                                    const int64_t *__restrict__ dt,
+                                                                    int n, int32_t *active,
+                                                                    int64_t *host_out) {
+    constexpr int kWaves = kSchedSmallThreads / 64, kCounts = kSchedSmallPer * kWaves;
+    static_assert(kCounts == 128, "two counts per lane of the scanning wave");
+    __shared__ int count[kCounts];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    int64_t due[kSchedSmallPer], v = INT64_MAX;
+#pragma unroll
+    for (int r = 0; r < kSchedSmallPer; ++r) {
+        const int i = r * kSchedSmallThreads + tid;
+        due[r] = i < n ? t[i] + dt[i] : INT64_MAX;
+        v = due[r] < v ? due[r] : v;
+    }
+    const int64_t tn = block_min_i64<kSchedSmallThreads>(v);
+    // counts in index order (round, wave), then their exclusive scan
+    int before[kSchedSmallPer];
+#pragma unroll
+    for (int r = 0; r < kSchedSmallPer; ++r) {
+        const bool is = r * kSchedSmallThreads + tid < n && due[r] == tn;
+        const unsigned long long mask = __ballot(is);
+        before[r] = is ? __popcll(mask & ((1ull << lane) - 1ull)) : -1;
+        if (lane == 0) count[r * kWaves + w] = __popcll(mask);
+    }
+    __syncthreads();
+    if (w == 0) {
+        const int c0 = count[2 * lane], c1 = count[2 * lane + 1];
+        int incl = c0 + c1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int o = __shfl_up(incl, off, 64);
+            incl += lane >= off ? o : 0;
+        }
+        count[2 * lane] = incl - c0 - c1;
+        count[2 * lane + 1] = incl - c1;
+        if (lane == 63) {
+            host_out[0] = tn;
+            host_out[1] = incl;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kSchedSmallPer; ++r)
+        if (before[r] >= 0) active[count[r * kWaves + w] + before[r]] = r * kSchedSmallThreads + tid;
 }
 
 __global__ __launch_bounds__(kSchedThreads) void k_sched_compact(const int64_t *__restrict__ t,
@@ -419,14 +498,19 @@ hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, i
 // the pinned host buffer), ctx->sched64[2..] chunk minima; ctx->sched32[0..nb) chunk counts,
 // [nb..2nb) chunk offsets; counters[0] is the hand-off counter.
 hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *active) {
+    int64_t *host_out = (int64_t *)((char *)ctx->host_dev + kHostBlock);
+    if (n <= kSchedSmall) {
+        hipLaunchKernelGGL(k_sched_small, dim3(1), dim3(kSchedSmallThreads), 0, ctx->stream, st->t,
+                           st->dt, n, active, host_out);
+        return hipGetLastError();
+    }
     const int nb = sched_blocks_for(n);
     int64_t *sel = ctx->sched64;
     int64_t *cmin = ctx->sched64 + 2;
     int32_t *ccnt = ctx->sched32;
     int32_t *coff = ctx->sched32 + nb;
     hipLaunchKernelGGL(k_sched_select, dim3(nb), dim3(kSchedThreads), 0, ctx->stream, st->t, st->dt,
-                       n, cmin, ccnt, coff, ctx->counters, sel,
-                       (int64_t *)((char *)ctx->host_dev + kHostBlock));
+                       n, cmin, ccnt, coff, ctx->counters, sel, host_out);
     hipLaunchKernelGGL(k_sched_compact, dim3(nb), dim3(kSchedThreads), 0, ctx->stream, st->t,
                        st->dt, n, (const int64_t *)sel, (const int32_t *)coff, active);
     return hipGetLastError();
