@@ -46,10 +46,9 @@ class _HermiteSharedRun(torch.autograd.Function):
         F = torch.empty((9, n), dtype=torch.float64, device=dev)
         lib_ctx.h6_init_forces(S, mm)
         ckpts = []
-        for step in range(nsteps):
-            if step % checkpoint == 0:
-                ckpts.append(S.clone())
-            lib_ctx.h6_shared_steps(S, mm, P, F, dt, 1)
+        for step in range(0, nsteps, checkpoint):
+            ckpts.append(S.clone())
+            lib_ctx.h6_shared_steps(S, mm, P, F, dt, min(checkpoint, nsteps - step))
         ctx.lib_ctx = lib_ctx
         ctx.dt = dt
         ctx.nsteps = nsteps
@@ -76,9 +75,7 @@ class _HermiteSharedRun(torch.autograd.Function):
             count = min(k, ctx.nsteps - seg * k)
             preds = [torch.empty((9, n), dtype=torch.float64, device=dev) for _ in range(count)]
             for st in range(count):
-                lc.h6_predict_dt(S, mm, dt, preds[st])
-                lc.h6_evaluate(preds[st], mm, None, n, h6.H6_FP64, F)
-                lc.h6_correct_shared(S, mm, F, dt)
+                lc.h6_shared_steps(S, mm, preds[st], F, dt, 1)
             for st in reversed(range(count)):
                 lc.h6_correct_shared_vjp(cot, gm, CF, dt)
                 lc.h6_evaluate_vjp(preds[st], mm, CF, CP, gm)

@@ -15,6 +15,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 
 import numpy as np
 import torch
@@ -159,8 +160,13 @@ def _ptr(t: torch.Tensor):
     return C.c_void_p(t.data_ptr())
 
 
-def _rows(t: torch.Tensor, first: int):
-    return _P3(t[first].data_ptr(), t[first + 1].data_ptr(), t[first + 2].data_ptr())
+def _row_ptrs(t: torch.Tensor, rows: int) -> array:
+    """Addresses of the first `rows` rows of t, from one base and stride: as
+    t[k].data_ptr() for each, which costs over a microsecond a row."""
+    if t.shape[0] < rows:
+        raise IndexError("tensor has %d rows, %d needed" % (t.shape[0], rows))
+    p, step = t.data_ptr(), t.stride(0) * t.element_size()
+    return array("Q", range(p, p + rows * step, step) if step else [p] * rows)
 
 
 def _check_dev(t: torch.Tensor, dtype, name):
@@ -172,27 +178,20 @@ def _check_dev(t: torch.Tensor, dtype, name):
         raise H6Error(H6_EINVAL, name, "tensor must be contiguous")
 
 
+# The structures hold only pointers, in the order of these rows.
 def make_state(S: torch.Tensor, m: torch.Tensor, T: torch.Tensor | None) -> h6_state:
-    st = h6_state()
-    st.x, st.v, st.a = _rows(S, 0), _rows(S, 3), _rows(S, 6)
-    st.j, st.s, st.c = _rows(S, 9), _rows(S, 12), _rows(S, 15)
-    st.m = m.data_ptr()
-    if T is not None:
-        st.t = T[0].data_ptr()
-        st.dt = T[1].data_ptr()
-    return st
+    ptrs = _row_ptrs(S, 18)
+    ptrs.append(m.data_ptr())
+    ptrs.extend(_row_ptrs(T, 2) if T is not None else (0, 0))
+    return h6_state.from_buffer_copy(ptrs)
 
 
 def make_pred(P: torch.Tensor) -> h6_pred:
-    p = h6_pred()
-    p.x, p.v, p.a = _rows(P, 0), _rows(P, 3), _rows(P, 6)
-    return p
+    return h6_pred.from_buffer_copy(_row_ptrs(P, 9))
 
 
 def make_force(F: torch.Tensor) -> h6_force:
-    f = h6_force()
-    f.a, f.j, f.s = _rows(F, 0), _rows(F, 3), _rows(F, 6)
-    return f
+    return h6_force.from_buffer_copy(_row_ptrs(F, 9))
 
 
 class Context:

@@ -62,3 +62,17 @@ def test_shared_steps_one_kernel(n, nsteps):
     # the work arrays end as with separate kernels: the last step's
     for w, g in ((sep.P, one.P), (sep.F, one.F)):
         assert float((g - w).abs().max()) <= 1e-11 * float(w.abs().max())
+
+
+def test_shared_steps_at_once_or_one_by_one():
+    # the backward pass replays single steps and relies on the same values
+    runs = []
+    for counts in ([5], [1] * 5, [2, 3]):
+        s = h6.System(*ics.plummer(777, 4), 1e-3)
+        s.startup()
+        for c in counts:
+            s.shared_steps(1.0 / 256, c)
+        runs.append((s.S, s.P, s.F))
+    for other in runs[1:]:
+        for a, b in zip(runs[0], other):
+            assert torch.equal(a, b)
