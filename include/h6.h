@@ -462,8 +462,7 @@ typedef struct {
                        targets each); 1: source-parallel small-set kernel;
                        2: evaluation kernel of the device-resident loop (its
                        shape is chosen per block on the device); 3: all
-                       particles by the third law (its slice sums
-                       included); 4: the loop's finishing kernel (on = 2) */
+                       particles by the third law; 4: the loop's finishing kernel (on = 2) */
     int block, ipl; /* launch shape of the instantiation (kind 2: 64, 2;
                        kind 4: 0, 0) */
     int precision;  /* H6_FP64, H6_MIXED, H6_EX or H6_SP */

@@ -621,19 +621,17 @@ template <int ORDER>
 hipError_t launch_vjp_order(h6_ctx ctx, const SrcPtrs &src, const CotPtrs &cot, int n,
                             const OutPtrs &out, unsigned acc_mask) {
     constexpr int NOUT = VTraits<ORDER>::NOUT, kBlock = kSymThreads * VjpOps<ORDER>::K;
-    const int runs = 2 * ctx->n_cu;
-    SymPlan P;
-    const bool sym = sym_plan(ctx, n, kBlock, runs, NOUT, 0, &P);
-    if (!sym) P = sym_plan_ordered(n, kBlock);
-    for (bool more = true; more; more = sym && sym_plan(ctx, n, kBlock, runs, NOUT, P.d1, &P)) {
+    auto launch = [&](const SymPlan &P) {
         hipLaunchKernelGGL((k_vjp_sym<ORDER>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream, src,
                            cot, P, ctx->eps2, ctx->partial);
-        hipError_t e = hipGetLastError();
-        if (e == hipSuccess)
-            e = launch_sym_reduce(ctx, P, NOUT, 0, out, P.d0 > 0 ? (1u << NOUT) - 1u : acc_mask);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+        return hipGetLastError();
+    };
+    bool done = false;
+    hipError_t e = sym_batches(ctx, n, kBlock, NOUT, SymCost{48.0f, 3.0f}, 0, out, acc_mask, &done, launch);
+    if (e != hipSuccess || done) return e;
+    const SymPlan P = sym_plan_ordered(n, kBlock);
+    e = launch(P);
+    return e != hipSuccess ? e : launch_sym_reduce(ctx, P, NOUT, 0, out, acc_mask);
 }
 
 // Transpose of the block-step corrector for the active particles, each over

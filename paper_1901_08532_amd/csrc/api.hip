@@ -8,7 +8,7 @@
 #include <new>
 #include <utility>
 
-#include "h6_internal.h"
+#include "sym_plan.h"
 
 using namespace h6;
 
@@ -753,16 +753,11 @@ int h6_run_blocks(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, cons
     return run_blocks_device(ctx, st, n, pred, f, active, prm, t_end, stats);
 }
 
-// Systems up to this size take one kernel a shared step; beyond, the
-// evaluation by the third law saves more than the launches (n = 6000: 84
-// against 75 us of evaluation).
-constexpr int64_t kSharedStepMax = 6000;
-
 // Shared steps of a small system, one kernel each after the first prediction.
 // The predicted arrays alternate between the caller's and the context's
 // scratch so that the last step's are the caller's, as with separate kernels.
 static int shared_steps_small(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
-                              const h6_force *f, double dt, int64_t nsteps) {
+                              const h6_force *f, double dt, int64_t nsteps, int precision) {
     h6_pred other;  // 9 n doubles of the partial sums' 18 n_max
     for (int c = 0; c < 3; ++c) {
         other.x[c] = ctx->partial + c * n;
@@ -775,15 +770,35 @@ static int shared_steps_small(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred
         hipEvent_t ev0 = nullptr, ev1 = nullptr;
         if (ctx->prof) H6_TRY(ctx, prof_begin(ctx, &ev0, &ev1), "profile event");
         H6_TRY(ctx,
-               launch_shared_step(ctx, st, (int)n, src_from_pred(cur, st->m), dt, k + 1 < nsteps,
-                                  next, f),
+               launch_shared_step(ctx, st, (int)n, precision, src_from_pred(cur, st->m), dt,
+                                  k + 1 < nsteps, next, f),
                "shared step");
         if (ctx->prof) {
             const EvalConfig cfg = {0, kWgBlock, shared_step_targets(ctx, (int)n), 1};
-            H6_TRY(ctx, prof_end(ctx, ev0, ev1, 2, cfg, H6_FP64, n, (double)n * (double)n),
+            H6_TRY(ctx, prof_end(ctx, ev0, ev1, 2, cfg, precision, n, (double)n * (double)n),
                    "profile event");
         }
         std::swap(cur, next);
+    }
+    return H6_OK;
+}
+
+// Shared steps whose third-law evaluation is one batch: the pair kernel, then
+// slot sums, corrector and next prediction in one kernel.
+static int shared_steps_sym(h6_ctx ctx, h6_state *st, const SymPlan &P, const h6_pred *pred,
+                            const h6_force *f, double dt, int64_t nsteps, int precision) {
+    const double pairs = (double)P.n * (double)P.n;
+    H6_TRY(ctx, launch_predict(ctx, st, P.n, 0, dt, true, pred), "predict");
+    for (int64_t k = 0; k < nsteps; ++k) {
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        if (ctx->prof) H6_TRY(ctx, prof_begin(ctx, &ev0, &ev1), "profile event");
+        H6_TRY(ctx, launch_eval_sym_pairs(ctx, 2, precision, src_from_pred(pred, st->m), P),
+               "evaluate");
+        if (ctx->prof) {
+            const EvalConfig cfg = {3, 256, precision == H6_EX ? 1 : 2, 1};
+            H6_TRY(ctx, prof_end(ctx, ev0, ev1, 2, cfg, precision, P.n, pairs), "profile event");
+        }
+        H6_TRY(ctx, launch_sym_step(ctx, P, st, dt, k + 1 < nsteps, pred, f), "shared step");
     }
     return H6_OK;
 }
@@ -795,8 +810,13 @@ int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, co
     if (int rc = check_n(ctx, n)) return rc;
     if (!std::isfinite(dt) || dt <= 0.0 || nsteps < 0) return fail_arg(ctx, "bad dt or step count");
     if (!precision_ok(precision)) return fail_arg(ctx, "bad precision");
-    if (nsteps > 0 && precision == H6_FP64 && n <= kSharedStepMax && !eval_shape_forced(ctx))
-        return shared_steps_small(ctx, st, n, pred, f, dt, nsteps);
+    if (nsteps > 0 && (precision == H6_EX || (precision == H6_FP64 && !eval_shape_forced(ctx)))) {
+        if (n <= one_kernel_max(precision))
+            return shared_steps_small(ctx, st, n, pred, f, dt, nsteps, precision);
+        SymPlan P;
+        if (eval_sym_single(ctx, precision, (int)n, &P))
+            return shared_steps_sym(ctx, st, P, pred, f, dt, nsteps, precision);
+    }
     for (int64_t k = 0; k < nsteps; ++k) {
         H6_TRY(ctx, launch_predict(ctx, st, (int)n, 0, dt, true, pred), "predict");
         H6_TRY(ctx,

@@ -41,27 +41,6 @@ __attribute__((amdgpu_waves_per_eu(IPL == 1 ? 4 : 2))) void k_eval_f64(
                                                 slice_stride, blockIdx.x, blockIdx.y);
 }
 
-// Evaluation by whole workgroups (eval_wg_body.h): target group blockIdx.x,
-// source slice blockIdx.y.
-template <int ORDER, int TGT, bool SKIPSELF>
-__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_eval_wg(
-    SrcPtrs src, const int32_t *__restrict__ active, int n, int n_act, double eps2, int slice_len,
-    OutPtrs out, int64_t slice_stride) {
-    using T = Traits<ORDER>;
-    __shared__ double2 pool[wg_pool<ORDER>()];
-    __shared__ double fs[TGT * T::NACC];
-    const int g = blockIdx.x, jb = (int)blockIdx.y * slice_len;
-    wg_sums<ORDER, TGT, SKIPSELF>(PredSrc{src, active}, n_act, eps2, g, jb, min(n, jb + slice_len),
-                                  pool, fs);
-    const int k = g * TGT + (int)threadIdx.x;
-    if ((int)threadIdx.x < TGT && k < n_act) {
-#pragma unroll
-        for (int q = 0; q < T::NACC; ++q)
-            out.p[T::OUT0 + q][(int64_t)blockIdx.y * slice_stride + k] =
-                fs[threadIdx.x * T::NACC + q];
-    }
-}
-
 // Slice reduction, few slices: one thread per (component, target), a
 // Neumaier sum over the slices with all loads issued up front.
 __global__ __launch_bounds__(256) void k_reduce_slices(const double *__restrict__ partial,
@@ -198,24 +177,11 @@ template <int ORDER>
 hipError_t dispatch_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
                        const int32_t *active, int n, int n_act, double eps2, int slice_len,
                        const OutPtrs &out, int64_t slice_stride) {
-#define H6_WG(T)                                                                                \
-    if (tgt == T) {                                                                             \
-        if (skipself)                                                                           \
-            hipLaunchKernelGGL((k_eval_wg<ORDER, T, true>), grid, dim3(kWgThreads), 0, st, src, \
-                               active, n, n_act, eps2, slice_len, out, slice_stride);           \
-        else                                                                                    \
-            hipLaunchKernelGGL((k_eval_wg<ORDER, T, false>), grid, dim3(kWgThreads), 0, st,     \
-                               src, active, n, n_act, eps2, slice_len, out, slice_stride);      \
-        return hipGetLastError();                                                               \
-    }
-    H6_WG(1)
-    H6_WG(2)
-    H6_WG(4)
-    H6_WG(8)
-    H6_WG(16)
-    H6_WG(32)
-#undef H6_WG
-    return hipErrorInvalidValue;
+    constexpr int OUT0 = Traits<ORDER>::OUT0;
+    return skipself ? launch_wg(tgt, grid, st, EvalOps<ORDER, true>{src, eps2}, active, n, n_act,
+                                slice_len, OUT0, out, slice_stride)
+                    : launch_wg(tgt, grid, st, EvalOps<ORDER, false>{src, eps2}, active, n, n_act,
+                                slice_len, OUT0, out, slice_stride);
 }
 
 // From this many slices the reduction splits them over waves.
@@ -226,9 +192,6 @@ constexpr int kDefaultSmallMax = 32;
 // the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets
 // 252 against 254 us, all 495 against 468).
 constexpr int kWgMaxAct = 8192;
-// All particles by the third law from this size on (FP64; below, the
-// whole-workgroup kernel: n = 4096 45 against 51 us, 6000 84 against 75).
-constexpr int kSymMin = 5000;
 // Waves a launch aims to put in flight (256 CUs x 4 SIMDs x 2).
 constexpr int kTargetWaves = 2048;
 // Shortest source slice of the source-parallel kernel (4 sources per lane).
@@ -275,7 +238,8 @@ int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_
 // about 0.7 us a tile, which a second workgroup on the CU hides. With few
 // targets a group, a wave reads more distinct LDS records a step (kWgShare).
 // Slices cost a second launch and their traffic.
-EvalConfig choose_wg(h6_ctx ctx, int order, int n, int n_act) {
+// EX pairs cost 13 times the operations.
+EvalConfig choose_wg(h6_ctx ctx, int order, int precision, int n, int n_act) {
     static const float kWgShare[6] = {1.3f, 1.25f, 1.2f, 1.12f, 1.05f, 1.0f};
     static const int kSplits[14] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64, 96, 128};
     const int ncomp = order == 2 ? 9 : 6;
@@ -295,7 +259,7 @@ EvalConfig choose_wg(h6_ctx ctx, int order, int n, int n_act) {
             const float c = (float)ceil_div((int64_t)groups * eff, ctx->n_cu);
             const int tiles = ceil_div(slice, kWgThreads);
             const int steps = slice / kWgThreads * tgt + ceil_div(slice % kWgThreads, strands);
-            const float issue = 0.196f * (float)steps;
+            const float issue = (precision == H6_EX ? 2.6f : 0.196f) * (float)steps;
             float cost = std::max(c * issue * kWgShare[l], issue + 0.7f * (float)tiles) + 1.2f * c;
             if (eff > 1) cost += 1.2f + (float)eff * (float)n_act * 3.6e-5f;
             if (cost < best) {
@@ -310,15 +274,14 @@ EvalConfig choose_wg(h6_ctx ctx, int order, int n, int n_act) {
 
 EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n_act) {
     EvalConfig cfg;
-    if (order == 2 && (precision == H6_EX || precision == H6_SP)) {
+    if (precision == H6_EX) return choose_wg(ctx, order, precision, n, n_act);
+    if (precision == H6_SP) {
         cfg.kind = 0;
-        cfg.block = kExtBlock;
+        cfg.block = kSpBlock;
         cfg.ipl = 1;
-        // slices down to one tile: a double-single pair costs ~20x an FP64
-        // one, so even small active sets need many workgroups
-        const int blocks_i = ceil_div(n_act, kExtBlock);
+        const int blocks_i = ceil_div(n_act, kSpBlock);
         int split = std::max(1, ceil_div(4 * ctx->n_cu, blocks_i));
-        split = std::min(split, ceil_div(n, kExtBlock));
+        split = std::min(split, ceil_div(n, kSpBlock));
         const int64_t cap_split = ctx->partial_cap / ((int64_t)9 * n_act);
         if (split > cap_split) split = (int)(cap_split < 1 ? 1 : cap_split);
         cfg.n_split = split < 1 ? 1 : split;
@@ -326,7 +289,7 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
     }
     // a launch shape forced by h6_set_eval_config takes the kernels it names
     if (precision == H6_FP64 && n_act <= kWgMaxAct && !(order == 2 && eval_shape_forced(ctx)))
-        return choose_wg(ctx, order, n, n_act);
+        return choose_wg(ctx, order, precision, n, n_act);
     const int small_max = ctx->cfg_small >= 0 ? ctx->cfg_small : kDefaultSmallMax;
     if (order == 2 && n_act <= small_max) {
         // source-parallel kernel: one wave per TPW targets
@@ -382,17 +345,20 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
 hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src, int n,
                        const int32_t *active, int n_act, const OutPtrs &out, EvalConfig *used) {
     if (n_act <= 0) return hipSuccess;
-    if (!active && n_act == n && precision == H6_FP64 && n >= kSymMin &&
-        !(order == 2 && eval_shape_forced(ctx))) {
+    // (EX and SP have no forced shapes)
+    const bool sym = (precision == H6_EX ||
+                      (precision == H6_FP64 && !(order == 2 && eval_shape_forced(ctx)))) &&
+                     n >= sym_min(precision);
+    if (!active && n_act == n && sym) {
         hipEvent_t ev0 = nullptr, ev1 = nullptr;
         hipError_t e = ctx->prof ? prof_begin(ctx, &ev0, &ev1) : hipSuccess;
         bool done = false;
-        if (e == hipSuccess) e = launch_eval_sym(ctx, order, src, n, out, &done);
-        const EvalConfig sym = {3, 256, 2, 1};
+        if (e == hipSuccess) e = launch_eval_sym(ctx, order, precision, src, n, out, &done);
+        const EvalConfig shape = {3, 256, precision == H6_EX ? 1 : 2, 1};
         if (e == hipSuccess && ctx->prof && done)
-            e = prof_end(ctx, ev0, ev1, order, sym, precision, n_act, (double)n * (double)n);
+            e = prof_end(ctx, ev0, ev1, order, shape, precision, n_act, (double)n * (double)n);
         if (e != hipSuccess || done) {
-            if (used) *used = sym;
+            if (used) *used = shape;
             return e;
         }
     }
@@ -426,8 +392,12 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
         if (pe != hipSuccess) return pe;
     }
     hipError_t e;
-    if (order == 2 && (precision == H6_EX || precision == H6_SP)) {
-        e = dispatch_ext(precision, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
+    if (precision == H6_EX) {
+        e = dispatch_ex_wg(cfg.ipl, skipself, dim3(ceil_div(n_act, cfg.ipl), cfg.n_split),
+                           ctx->stream, src, active, n, n_act, ctx->eps2, slice_len, dst,
+                           slice_stride);
+    } else if (precision == H6_SP) {
+        e = dispatch_sp(skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
                          slice_len, dst, slice_stride);
     } else if (order == 2 && precision == H6_MIXED) {
         dim3 g = cfg.kind == 1 ? dim3(ceil_div(n_act, cfg.ipl), cfg.n_split) : grid;

@@ -31,14 +31,19 @@
 // SP rounds the staged inputs to float and does every operation of the pair
 // terms and the per-slice sums in float.
 //
-// Both use the FP64 kernel's launch structure: a tile of source records in
-// LDS, one target per lane, the source sum split into slices across
-// workgroups; the slices (at most a few dozen partial sums per target) are
-// combined by the common compensated FP64 slice reduction.
-#include "h6_internal.h"
+// EX runs in the FP64 evaluation's kernels with its own particles and pairs:
+// all particles by the third law (sym_body.h), active sets by whole workgroups
+// (eval_wg_body.h). Its sums are double-single within a slice: 64 to 128
+// sources of a strand, the steps of a cell, the targets a travelling source
+// meets in a wave; slices are combined in FP64. SP keeps one target per lane
+// over LDS tiles, its slices combined by the common FP64 reduction.
+#include "shared_step_body.h"
 
 namespace h6 {
 namespace {
+
+using namespace evalbody;
+using namespace symbody;
 
 // ---------------------------------------------------------------- EX
 struct fpair {
@@ -153,8 +158,6 @@ __device__ __forceinline__ fpair ds_from(double d) {
     return {h, (float)(d - (double)h)};
 }
 
-__device__ __forceinline__ double ds_to_double(fpair x) { return (double)x.h + (double)x.l; }
-
 // 1/sqrt(r2): single-precision estimate y0 (relative error d of a few
 // 2^-24), then y = y0 (1 + e/2 + 3 e^2/8) with e = 1 - r2 y0^2 formed in
 // double-single; the step leaves a relative error of about (5/2) d^3, below
@@ -175,18 +178,16 @@ __device__ __forceinline__ fpair ds_dot3(const fpair *p, const fpair *q) {
                          ds_mul_raw(p[2], q[2]));
 }
 
-// Pair terms of order 2 in double-single, added to acc[0..8]: with
+// The vectors of an order-2 pair in double-single: r, w, u and R^-3, with
 // R^2 = |r|^2 + eps^2, alpha = r.v/R^2, beta = (v.v + r.a)/R^2 + alpha^2,
-//   A = m r/R^3, J = m w/R^3 with w = v - 3 alpha r,
-//   S = m u/R^3 with u = a - 6 alpha w - 3 beta r.
-__device__ __forceinline__ void pair_ex(const fpair *r, const fpair *v, const fpair *a, fpair r2,
-                                        fpair mj, fpair *acc) {
+// w = v - 3 alpha r, u = a - 6 alpha w - 3 beta r: A = m r/R^3, J = m w/R^3,
+// S = m u/R^3.
+__device__ __forceinline__ fpair pair_ex(const fpair *r, const fpair *v, const fpair *a, fpair r2,
+                                         fpair *w, fpair *u) {
     const fpair rinv = ds_rsqrt(r2);
     const fpair rinv2 = ds_sqr(rinv);
-    const fpair mr3 = ds_mul(ds_mul(mj, rinv), rinv2);
     const fpair alpha = ds_mul(ds_dot3(r, v), rinv2);
     const fpair a3 = ds_mul_f(alpha, 3.0f);
-    fpair w[3], u[3];
 #pragma unroll
     for (int c = 0; c < 3; ++c) w[c] = ds_sub_sloppy(v[c], ds_mul_raw(a3, r[c]));
     const fpair vvra = ds_add_sloppy(ds_dot3(v, v), ds_dot3(r, a));
@@ -196,98 +197,104 @@ __device__ __forceinline__ void pair_ex(const fpair *r, const fpair *v, const fp
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         u[c] = ds_sub_sloppy(ds_sub_sloppy(a[c], ds_mul_raw(a6, w[c])), ds_mul_raw(b3, r[c]));
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        acc[c] = ds_add_sloppy(acc[c], ds_mul_raw(mr3, r[c]));
-        acc[3 + c] = ds_add_sloppy(acc[3 + c], ds_mul_raw(mr3, w[c]));
-        acc[6 + c] = ds_add_sloppy(acc[6 + c], ds_mul_raw(mr3, u[c]));
-    }
+    return ds_mul(rinv, rinv2);
 }
 
 // Far, massless padding source: contributes exactly zero.
 constexpr float kPadPosF = 1.0e18f;
 
-// LDS record of one source: x, v, a and m as (h, l) pairs, five float4.
-template <int BLOCK, bool SKIPSELF>
-__global__ __launch_bounds__(BLOCK) void k_eval_ex(SrcPtrs src, const int32_t *__restrict__ active,
-                                                   int n, int n_act, double eps2_d, int slice_len,
-                                                   OutPtrs out, int64_t slice_stride) {
-    __shared__ float4 tile[BLOCK * 5];
-    const int tid = threadIdx.x;
-    const int k = (int)blockIdx.x * BLOCK + tid;
-    const int kc = k < n_act ? k : n_act - 1;
-    const int p = active ? active[kc] : kc;
-    fpair xi[3], vi[3], ai[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        xi[c] = ds_from(src.x[c][p]);
-        vi[c] = ds_from(src.v[c][p]);
-        ai[c] = ds_from(src.a[c][p]);
+// Particles and pairs of the EX evaluation (sym_body.h, eval_wg_body.h).
+// Bound by FP32 issue: about 720 operations for the terms of one particle and
+// 150 more for both. All particles of n = 4096: 335 -> 222 us.
+template <bool SKIPSELF>
+struct ExOps {
+    using Word = float2;  // high and low part
+    using Sum = CompSum;  // slices: FP64
+    static constexpr int NF = 10, NREC = 5, NI = 9, NJ = 9, K = 1, kUnroll = 1;
+    struct Target {
+        fpair x[3], v[3], a[3], m;
+    };
+    SrcPtrs src;
+    double eps2;
+    // record order x0 x1 | x2 m | v0 v1 | v2 a0 | a1 a2
+    __device__ __forceinline__ const double *field(int f) const {
+        return f < 3 ? src.x[f] : f == 3 ? src.m : f < 7 ? src.v[f - 4] : src.a[f - 7];
     }
-    const fpair eps2 = ds_from(eps2_d);
-    fpair acc[9];
+    static __device__ __forceinline__ float2 word(double d) {
+        const fpair p = ds_from(d);
+        return make_float2(p.h, p.l);
+    }
+    static __device__ __forceinline__ float2 pad(int f) {
+        return make_float2(f < 3 ? kPadPosF : 0.0f, 0.0f);
+    }
+    __device__ __forceinline__ void load(int k, int n, Target &t) const {
+        const bool in = k < n;
+        const int kc = in ? k : n - 1;
 #pragma unroll
-    for (int q = 0; q < 9; ++q) acc[q] = {0.0f, 0.0f};
+        for (int c = 0; c < 3; ++c) {
+            t.x[c] = in ? ds_from(src.x[c][kc]) : fpair{-kPadPosF, 0.0f};
+            t.v[c] = ds_from(src.v[c][kc]);
+            t.a[c] = ds_from(src.a[c][kc]);
+        }
+        t.m = in ? ds_from(src.m[kc]) : fpair{0.0f, 0.0f};
+    }
+    // the pair's r, w, u and R^-3
+    __device__ __forceinline__ fpair pair(const Word2<float2> *e, const Target &t, bool self,
+                                          fpair *r, fpair *w, fpair *u, fpair &mj) const {
+        auto f = [&](int q) {
+            const float2 d = q & 1 ? e[q >> 1].y : e[q >> 1].x;
+            return fpair{d.x, d.y};
+        };
+        fpair v[3], a[3];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            r[c] = ds_sub(f(c), t.x[c]);
+            v[c] = ds_sub(f(4 + c), t.v[c]);
+            a[c] = ds_sub(f(7 + c), t.a[c]);
+        }
+        fpair r2 = ds_add_sloppy(
+            ds_add_sloppy(ds_add_sloppy(ds_from(eps2), ds_sqr_raw(r[0])), ds_sqr_raw(r[1])),
+            ds_sqr_raw(r[2]));
+        mj = f(3);
+        if (self) {  // r, v, a are zero: mask the 1/0
+            r2 = {1.0f, 0.0f};
+            mj = {0.0f, 0.0f};
+        }
+        return pair_ex(r, v, a, r2, w, u);
+    }
+    static __device__ __forceinline__ void accumulate(float2 *acc, fpair p, const fpair *r,
+                                                      const fpair *w, const fpair *u) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            const fpair x = q < 3 ? r[q] : q < 6 ? w[q - 3] : u[q - 6];
+            const fpair s = ds_add_sloppy({acc[q].x, acc[q].y}, ds_mul_raw(p, x));
+            acc[q] = make_float2(s.h, s.l);
+        }
+    }
+    __device__ __forceinline__ void both(const Word2<float2> *e, const Target &t, float2 *acci,
+                                         float2 *accj) const {
+        fpair r[3], w[3], u[3], mj;
+        const fpair r3 = pair(e, t, false, r, w, u, mj);
+        accumulate(acci, ds_mul(mj, r3), r, w, u);
+        accumulate(accj, ds_neg(ds_mul(t.m, r3)), r, w, u);
+    }
+    __device__ __forceinline__ void one(const Word2<float2> *e, const Target &t, bool self,
+                                        float2 *acci) const {
+        fpair r[3], w[3], u[3], mj;
+        const fpair r3 = pair(e, t, SKIPSELF && self, r, w, u, mj);
+        accumulate(acci, ds_mul(mj, r3), r, w, u);
+    }
+    static __device__ __forceinline__ double value(float2 x) { return (double)x.x + (double)x.y; }
+    static __device__ __forceinline__ void add(Sum &s, float2 x) {
+        two_sum_into(s.hi, s.lo, value(x));
+    }
+    static __device__ __forceinline__ double value(const Sum &s) { return s.hi + s.lo; }
+};
 
-    const int jb = (int)blockIdx.y * slice_len;
-    const int je = min(n, jb + slice_len);
-    for (int jt = jb; jt < je; jt += BLOCK) {
-        __syncthreads();
-        {
-            const int jj = jt + tid;
-            float4 *rec = &tile[tid * 5];
-            if (jj < je) {
-                fpair f[10];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    f[c] = ds_from(src.x[c][jj]);
-                    f[3 + c] = ds_from(src.v[c][jj]);
-                    f[6 + c] = ds_from(src.a[c][jj]);
-                }
-                f[9] = ds_from(src.m[jj]);
-#pragma unroll
-                for (int q = 0; q < 5; ++q)
-                    rec[q] = make_float4(f[2 * q].h, f[2 * q].l, f[2 * q + 1].h, f[2 * q + 1].l);
-            } else {
-                rec[0] = make_float4(kPadPosF, 0.0f, kPadPosF, 0.0f);
-                rec[1] = make_float4(kPadPosF, 0.0f, 0.0f, 0.0f);
-#pragma unroll
-                for (int q = 2; q < 5; ++q) rec[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-        }
-        __syncthreads();
-        for (int q = 0; q < BLOCK; ++q) {
-            const float4 *rec = &tile[q * 5];
-            fpair f[10];
-#pragma unroll
-            for (int t = 0; t < 5; ++t) {
-                const float4 d = rec[t];
-                f[2 * t] = {d.x, d.y};
-                f[2 * t + 1] = {d.z, d.w};
-            }
-            fpair r[3], v[3], a[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                r[c] = ds_sub(f[c], xi[c]);
-                v[c] = ds_sub(f[3 + c], vi[c]);
-                a[c] = ds_sub(f[6 + c], ai[c]);
-            }
-            fpair r2 = ds_add_sloppy(
-                ds_add_sloppy(ds_add_sloppy(eps2, ds_sqr_raw(r[0])), ds_sqr_raw(r[1])),
-                ds_sqr_raw(r[2]));
-            fpair mj = f[9];
-            if (SKIPSELF && (jt + q) == p) {  // r, v, a are zero: mask the 1/0
-                r2 = {1.0f, 0.0f};
-                mj = {0.0f, 0.0f};
-            }
-            pair_ex(r, v, a, r2, mj, acc);
-        }
-    }
-    if (k < n_act) {
-        const int64_t soff = (int64_t)blockIdx.y * slice_stride;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) out.p[q][soff + k] = ds_to_double(acc[q]);
-    }
+template <bool SKIPSELF>
+__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_ex_sym(
+    SrcPtrs src, SymPlan P, double eps2, double *__restrict__ partial) {
+    sym_run(ExOps<SKIPSELF>{src, eps2}, P, partial);
 }
 
 // ---------------------------------------------------------------- SP
@@ -377,35 +384,46 @@ __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *_
     }
 }
 
-template <bool EX, bool SKIPSELF>
-hipError_t launch_one(dim3 grid, hipStream_t st, const SrcPtrs &src, const int32_t *active, int n,
-                      int n_act, double eps2, int slice_len, const OutPtrs &out,
-                      int64_t slice_stride) {
-    if constexpr (EX)
-        hipLaunchKernelGGL((k_eval_ex<kExtBlock, SKIPSELF>), grid, dim3(kExtBlock), 0, st, src,
-                           active, n, n_act, eps2, slice_len, out, slice_stride);
-    else
-        hipLaunchKernelGGL((k_eval_sp<kExtBlock, SKIPSELF>), grid, dim3(kExtBlock), 0, st, src,
-                           active, n, n_act, eps2, slice_len, out, slice_stride);
-    return hipGetLastError();
-}
-
 }  // namespace
 
-hipError_t dispatch_ext(int precision, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
-                        const int32_t *active, int n, int n_act, double eps2, int slice_len,
-                        const OutPtrs &out, int64_t slice_stride) {
-    if (precision == H6_EX)
-        return skipself ? launch_one<true, true>(grid, st, src, active, n, n_act, eps2, slice_len,
-                                                 out, slice_stride)
-                        : launch_one<true, false>(grid, st, src, active, n, n_act, eps2, slice_len,
-                                                  out, slice_stride);
-    if (precision == H6_SP)
-        return skipself ? launch_one<false, true>(grid, st, src, active, n, n_act, eps2, slice_len,
-                                                  out, slice_stride)
-                        : launch_one<false, false>(grid, st, src, active, n, n_act, eps2,
-                                                   slice_len, out, slice_stride);
-    return hipErrorInvalidValue;
+void launch_ex_sym_pairs(h6_ctx ctx, const SrcPtrs &src, const SymPlan &P) {
+    static_assert(ExOps<false>::K == 1, "superblocks of kSymThreads particles");
+    if (self_pair_masked(ctx->eps2, H6_EX))
+        hipLaunchKernelGGL((k_ex_sym<true>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream, src,
+                           P, ctx->eps2, ctx->partial);
+    else
+        hipLaunchKernelGGL((k_ex_sym<false>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream, src,
+                           P, ctx->eps2, ctx->partial);
+}
+
+hipError_t launch_ex_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
+                                 bool predict, const h6_pred *out, const h6_force *f) {
+    return self_pair_masked(ctx->eps2, H6_EX)
+               ? stepbody::launch_shared_step_ops(ctx, ExOps<true>{src, ctx->eps2}, st, n, dt,
+                                                  predict, out, f)
+               : stepbody::launch_shared_step_ops(ctx, ExOps<false>{src, ctx->eps2}, st, n, dt,
+                                                  predict, out, f);
+}
+
+hipError_t dispatch_ex_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                          const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                          const OutPtrs &out, int64_t slice_stride) {
+    return skipself ? launch_wg(tgt, grid, st, ExOps<true>{src, eps2}, active, n, n_act, slice_len,
+                                0, out, slice_stride)
+                    : launch_wg(tgt, grid, st, ExOps<false>{src, eps2}, active, n, n_act, slice_len,
+                                0, out, slice_stride);
+}
+
+hipError_t dispatch_sp(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                       const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                       const OutPtrs &out, int64_t slice_stride) {
+    if (skipself)
+        hipLaunchKernelGGL((k_eval_sp<kSpBlock, true>), grid, dim3(kSpBlock), 0, st, src, active, n,
+                           n_act, eps2, slice_len, out, slice_stride);
+    else
+        hipLaunchKernelGGL((k_eval_sp<kSpBlock, false>), grid, dim3(kSpBlock), 0, st, src, active, n,
+                           n_act, eps2, slice_len, out, slice_stride);
+    return hipGetLastError();
 }
 
 }  // namespace h6

@@ -64,7 +64,7 @@ inline bool self_pair_masked(double eps2, int precision) {
 constexpr int kLevels = kTickBits + 1;  // levels 0..40: step 2^-level
 constexpr int kSmall2Max = 48;          // largest active set of the source-parallel kinds
 constexpr int kWgBlock = 512;     // workgroup of the whole-workgroup kernels (targets: EvalConfig::ipl)
-constexpr int kExtBlock = 64;           // workgroup of the EX and SP kernels (one target per lane)
+constexpr int kSpBlock = 64;            // workgroup of the SP kernel (one target per lane)
 
 // Plan of one block, written by the plan of the block before (double
 // buffered by block parity) and read by the kernels of the block.
@@ -209,34 +209,53 @@ hipError_t launch_reduce(h6_ctx ctx, const double *partial, int n_split, int nco
 inline bool eval_shape_forced(h6_ctx ctx) {
     return ctx->cfg_block || ctx->cfg_ipl || ctx->cfg_split || ctx->cfg_small >= 0;
 }
-// FP64 evaluation over all particles by the third law (eval_sym.hip); *done
-// is false, and nothing launched, where the partial sums hold too few slots.
-hipError_t launch_eval_sym(h6_ctx ctx, int order, const SrcPtrs &src, int n, const OutPtrs &out,
-                           bool *done);
+// FP64 or (order 2) EX evaluation over all particles by the third law
+// (eval_sym.hip, eval_ex.hip); *done is false, and nothing launched, where the
+// partial sums hold too few slots.
+hipError_t launch_eval_sym(h6_ctx ctx, int order, int precision, const SrcPtrs &src, int n,
+                           const OutPtrs &out, bool *done);
+// From these sizes on the third law is the faster evaluation of all particles
+// (whole workgroups and this, us: FP64 n = 4096 45 and 51, 6000 84 and 75; EX
+// n = 1500 42 and 56, 4096 222 and 207); up to the second ones a shared step is
+// one kernel (the last whole round of 16 or 8 targets a workgroup on 256 CUs:
+// FP64 n = 4096 52 us a step and 5000 67 by the third law; EX 2048 77 and 2200
+// 98, in one kernel 135).
+constexpr int kSymMinF64 = 5000, kSymMinEx = 2200;
+constexpr int kOneKernelMaxF64 = 4096, kOneKernelMaxEx = 2048;
+inline int sym_min(int precision) { return precision == H6_EX ? kSymMinEx : kSymMinF64; }
+inline int one_kernel_max(int precision) {
+    return precision == H6_EX ? kOneKernelMaxEx : kOneKernelMaxF64;
+}
 int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_i);
 // Mixed-precision order-2 kernels (eval_mixed.hip), launched with the shape
 // chosen for the FP64 kernels.
 hipError_t dispatch_mixed(const EvalConfig &cfg, bool skipself, dim3 grid, hipStream_t st,
                           const SrcPtrs &src, const int32_t *active, int n, int n_act, double eps2,
                           int slice_len, const OutPtrs &out, int64_t slice_stride);
-// Double-single (H6_EX) and single-precision (H6_SP) order-2 kernels
-// (eval_ex.hip): kExtBlock threads, one target per lane.
-hipError_t dispatch_ext(int precision, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
-                        const int32_t *active, int n, int n_act, double eps2, int slice_len,
-                        const OutPtrs &out, int64_t slice_stride);
+// Double-single (H6_EX) order-2 kernel by whole workgroups (tgt targets each),
+// and the single-precision (H6_SP) one: kSpBlock threads, one target per lane
+// (eval_ex.hip).
+hipError_t dispatch_ex_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                          const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                          const OutPtrs &out, int64_t slice_stride);
+hipError_t dispatch_sp(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                       const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                       const OutPtrs &out, int64_t slice_stride);
 
 hipError_t launch_predict(h6_ctx ctx, const h6_state *st, int n, int64_t t_tick, double dt,
                           bool shared, const h6_pred *out);
 hipError_t launch_correct(h6_ctx ctx, h6_state *st, const int32_t *active, int n_act,
                           const h6_force *f, int64_t t_next, double dt, const h6_params *prm,
                           bool shared);
-// One shared step of a small system in one kernel (shared_step.hip): reads
-// the predicted sources src, corrects st, and either predicts the next step
-// into out or, for the last one, writes the forces to f. shared_step_targets:
-// the targets a workgroup takes.
+// One shared step of a small system in one kernel (shared_step.hip), FP64 or
+// EX: reads the predicted sources src, corrects st, and either predicts the
+// next step into out or, for the last one, writes the forces to f.
+// shared_step_targets: the targets a workgroup takes.
 int shared_step_targets(h6_ctx ctx, int n);
-hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
-                              bool predict, const h6_pred *out, const h6_force *f);
+hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, int precision, const SrcPtrs &src,
+                              double dt, bool predict, const h6_pred *out, const h6_force *f);
+hipError_t launch_ex_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
+                                 bool predict, const h6_pred *out, const h6_force *f);
 hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, int lev_min,
                                 int lev_max);
 hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *active);

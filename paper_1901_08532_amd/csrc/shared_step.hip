@@ -1,67 +1,50 @@
-// One shared step of a small system in one kernel: evaluation, corrector and
-// the prediction to the next step.
-//
-// Bound by latency at these sizes: as separate kernels (predict, evaluate,
-// reduce, correct) a step paid four launches and their memory round trips,
-// 4.5 to 5 us each, beside 62 us of evaluation on 32 waves at n = 1024
-// (70 us a step; 9.2 us with this kernel). Here a workgroup sums its targets over all sources
-// (eval_wg_body.h: no slice sums in memory), corrects them and predicts them
-// to the next step. Other workgroups still read the sources' predicted
-// arrays, so the predictions go to a second set; the caller alternates them.
-#include "eval_wg_body.h"
-#include "steps_body.h"
+// Shared steps in one or two kernels a step: small systems in one
+// (shared_step_body.h), larger ones that the third-law evaluation takes in one
+// batch with its slot sums, corrector and next prediction in the second.
+#include "shared_step_body.h"
+#include "sym_plan.h"
 
 namespace h6 {
 namespace {
 
-using namespace evalbody;
 using namespace stepbody;
 
-// PREDICT: predict the next step into `out`; otherwise (the last step) write
-// the forces to f.
-template <int TGT, bool SKIPSELF>
-__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_shared_step(
-    h6_state st, SrcPtrs src, int n, double eps2, double h, bool predict, h6_pred out, h6_force f,
-    int32_t *flags) {
-    constexpr int kOld = 15;  // x, v, a, j, s of each target
-    __shared__ double2 pool[wg_pool<2>()];
-    __shared__ double fs[TGT * 9];
-    __shared__ double old[kOld][TGT];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int k0 = (int)blockIdx.x * TGT;
-    // the old state on its way while the sums run, a component per wave
-    for (int q = __builtin_amdgcn_readfirstlane(tid >> 6); q < kOld; q += kWgThreads / 64) {
-        const int c = q % 3;
-        const double *p = q < 3 ? st.x[c] : q < 6 ? st.v[c] : q < 9 ? st.a[c] : q < 12 ? st.j[c] : st.s[c];
-        if (lane < TGT && k0 + lane < n) old[q][lane] = p[k0 + lane];
-    }
-    wg_sums<2, TGT, SKIPSELF>(PredSrc{src, nullptr}, n, eps2, (int)blockIdx.x, 0, n, pool, fs);
-    // one component of one target per thread
-    const int t = tid % TGT, c = tid / TGT, i = k0 + t;
-    if (c >= 3 || i >= n) return;
-    const double a1 = fs[t * 9 + c], j1 = fs[t * 9 + 3 + c], s1 = fs[t * 9 + 6 + c];
+// Sums of a third-law evaluation's slots (as k_sym_reduce), corrector, and the
+// prediction of the next step, or after the last one the forces: one component
+// of one particle per thread. Bound by memory latency and the slots' traffic;
+// as three kernels (reduce, correct, predict) 9.2 + 4.8 + 4.7 us at n = 16384,
+// in one 11 us.
+__global__ __launch_bounds__(256) void k_sym_step(const double *__restrict__ partial, SymPlan P,
+                                                  h6_state st, double h, bool predict, h6_pred out,
+                                                  h6_force f, int32_t *flags) {
+    const int n = P.n;
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)3 * n) return;
+    const int c = (int)(idx / n), k = (int)(idx - (int64_t)c * n);
+    const double x0 = st.x[c][k], v0 = st.v[c][k], a0 = st.a[c][k], j0 = st.j[c][k],
+                 s0 = st.s[c][k];
+    double F[3];
+    sym_sums<3>(partial, P, 9, c, k, F);  // components c, 3 + c, 6 + c: a, j, s
     const double hinv = 1.0 / h;
-    const double hinv3 = hinv * hinv * hinv;
     double x1, v1, c1;
-    correct_comp(h, h * h, hinv3, old[c][t], old[3 + c][t], old[6 + c][t], old[9 + c][t],
-                 old[12 + c][t], a1, j1, s1, x1, v1, c1);
+    correct_comp(h, h * h, hinv * hinv * hinv, x0, v0, a0, j0, s0, F[0], F[1], F[2], x1, v1, c1);
     if (!(isfinite(x1) && isfinite(v1) && isfinite(c1))) atomicOr(flags, kFlagNonFinite);
-    st.x[c][i] = x1;
-    st.v[c][i] = v1;
-    st.a[c][i] = a1;
-    st.j[c][i] = j1;
-    st.s[c][i] = s1;
-    st.c[c][i] = c1;
+    st.x[c][k] = x1;
+    st.v[c][k] = v1;
+    st.a[c][k] = F[0];
+    st.j[c][k] = F[1];
+    st.s[c][k] = F[2];
+    st.c[c][k] = c1;
     if (predict) {
         double xp, vp, ap;
-        predict_comp(x1, v1, a1, j1, s1, c1, h, xp, vp, ap);
-        out.x[c][i] = xp;
-        out.v[c][i] = vp;
-        out.a[c][i] = ap;
+        predict_comp(x1, v1, F[0], F[1], F[2], c1, h, xp, vp, ap);
+        out.x[c][k] = xp;
+        out.v[c][k] = vp;
+        out.a[c][k] = ap;
     } else {
-        f.a[c][i] = a1;
-        f.j[c][i] = j1;
-        f.s[c][i] = s1;
+        f.a[c][k] = F[0];
+        f.j[c][k] = F[1];
+        f.s[c][k] = F[2];
     }
 }
 
@@ -73,31 +56,21 @@ int shared_step_targets(h6_ctx ctx, int n) {
     return tgt;
 }
 
-hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
-                              bool predict, const h6_pred *out, const h6_force *f) {
-    const int tgt = shared_step_targets(ctx, n);
-    const bool skip = self_pair_masked(ctx->eps2, H6_FP64);
-    const dim3 grid((n + tgt - 1) / tgt);
-#define H6_STEP(T)                                                                             \
-    if (tgt == T) {                                                                            \
-        if (skip)                                                                              \
-            hipLaunchKernelGGL((k_shared_step<T, true>), grid, dim3(kWgThreads), 0,            \
-                               ctx->stream, *st, src, n, ctx->eps2, dt, predict, *out, *f,     \
-                               ctx->flags);                                                    \
-        else                                                                                   \
-            hipLaunchKernelGGL((k_shared_step<T, false>), grid, dim3(kWgThreads), 0,           \
-                               ctx->stream, *st, src, n, ctx->eps2, dt, predict, *out, *f,     \
-                               ctx->flags);                                                    \
-        return hipGetLastError();                                                              \
-    }
-    H6_STEP(1)
-    H6_STEP(2)
-    H6_STEP(4)
-    H6_STEP(8)
-    H6_STEP(16)
-    H6_STEP(32)
-#undef H6_STEP
-    return hipErrorInvalidValue;
+hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, int precision, const SrcPtrs &src,
+                              double dt, bool predict, const h6_pred *out, const h6_force *f) {
+    if (precision == H6_EX) return launch_ex_shared_step(ctx, st, n, src, dt, predict, out, f);
+    return self_pair_masked(ctx->eps2, H6_FP64)
+               ? launch_shared_step_ops(ctx, EvalOps<2, true>{src, ctx->eps2}, st, n, dt, predict,
+                                        out, f)
+               : launch_shared_step_ops(ctx, EvalOps<2, false>{src, ctx->eps2}, st, n, dt, predict,
+                                        out, f);
+}
+
+hipError_t launch_sym_step(h6_ctx ctx, const SymPlan &P, h6_state *st, double dt, bool predict,
+                           const h6_pred *out, const h6_force *f) {
+    hipLaunchKernelGGL(k_sym_step, dim3((unsigned)(((int64_t)3 * P.n + 255) / 256)), dim3(256), 0,
+                       ctx->stream, ctx->partial, P, *st, dt, predict, *out, *f, ctx->flags);
+    return hipGetLastError();
 }
 
 }  // namespace h6

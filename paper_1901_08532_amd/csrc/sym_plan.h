@@ -20,12 +20,13 @@
 // workgroup a superblock.
 #pragma once
 
+#include "device_math.h"
 #include "h6_internal.h"
 
 namespace h6 {
 
 constexpr int kSymChunk = 64;  // sources of a cell
-constexpr int kSymMaxSub = 4;
+constexpr int kSymMaxSub = 16;
 
 struct SymPlan {
     int n;
@@ -64,12 +65,84 @@ struct SymPlan {
     }
 };
 
-// The next batch from offset d0 on, for `runs` workgroups and ncomp sums a
-// particle; false at the end, or at d0 = 0 where the slots do not suffice.
-bool sym_plan(h6_ctx ctx, int n, int block, int runs, int ncomp, int d0, SymPlan *plan);
+// Price of a cell in microseconds, two workgroups on a CU: a whole chunk's
+// steps, and the fixed part (staging, barriers, sums).
+struct SymCost {
+    float chunk, part;
+};
+
+// Sums of a batch's slots for particle k, components c, c + ncomp / N, ... (N of
+// them): the source-side slots that its superblock has, then the target-side
+// ones of the runs that touched it (compensated).
+template <int N>
+__device__ __forceinline__ void sym_sums(const double *__restrict__ partial, const SymPlan &P,
+                                         int ncomp, int c, int k, double *out) {
+    const int J = k / P.block;
+    const int64_t ld = (int64_t)ncomp * P.n;
+    const int64_t cs = (int64_t)(ncomp / N) * P.n;
+    const double *__restrict__ p = partial + (int64_t)c * P.n + k;
+    int nj = P.slots_j;
+    // the batch's last slots are d = nsb / 2, which only half the superblocks have
+    if (P.half && nj > 0 && !P.has_source_sum(J, P.nsb / 2)) nj -= P.sub;
+    const int ni = P.run_count(J);
+    double s[N], comp[N];
+#pragma unroll
+    for (int q = 0; q < N; ++q) s[q] = comp[q] = 0.0;
+    constexpr int U = N == 1 ? 8 : 4;  // slots whose loads are in flight together
+    for (int part = 0; part < 2; ++part) {
+        const int cnt = part ? ni : nj;
+        const double *__restrict__ b = p + (part ? P.slots_j * ld : 0);
+        for (int s0 = 0; s0 < cnt; s0 += U) {
+            double x[U][N];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < N; ++q)
+                    x[u][q] = s0 + u < cnt ? b[(int64_t)(s0 + u) * ld + q * cs] : 0.0;
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < N; ++q) two_sum_into(s[q], comp[q], x[u][q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) out[q] = s[q] + comp[q];
+}
+
+// The next batch from offset d0 on, for ncomp sums a particle; false at the
+// end, or at d0 = 0 where the slots do not suffice.
+bool sym_plan(h6_ctx ctx, int n, int block, int ncomp, SymCost cost, int d0, SymPlan *plan);
 // The ordered form (one slot).
 SymPlan sym_plan_ordered(int n, int block);
 hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
                              unsigned acc_mask);
+
+// An order-2 evaluation over all particles (FP64 or EX) whose sums fit one
+// batch: the plan (false: more than one, or none), the pair kernel, and a
+// shared step's remainder on its slots.
+bool eval_sym_single(h6_ctx ctx, int precision, int n, SymPlan *plan);
+hipError_t launch_eval_sym_pairs(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
+                                 const SymPlan &P);
+void launch_ex_sym_pairs(h6_ctx ctx, const SrcPtrs &src, const SymPlan &P);
+hipError_t launch_sym_step(h6_ctx ctx, const SymPlan &P, h6_state *st, double dt, bool predict,
+                           const h6_pred *out, const h6_force *f);
+
+// All batches of a third-law sum over n particles: launch(plan) enqueues the
+// pair kernel, the slots are then summed into (bits of acc_mask: added to)
+// out.p[out0 ..]. *done is false, and nothing launched, where the slots do not
+// suffice.
+template <class LAUNCH>
+hipError_t sym_batches(h6_ctx ctx, int n, int block, int ncomp, SymCost cost, int out0,
+                       const OutPtrs &out, unsigned acc_mask, bool *done, LAUNCH launch) {
+    SymPlan P;
+    *done = sym_plan(ctx, n, block, ncomp, cost, 0, &P);
+    for (bool more = *done; more; more = sym_plan(ctx, n, block, ncomp, cost, P.d1, &P)) {
+        hipError_t e = launch(P);
+        if (e == hipSuccess)
+            e = launch_sym_reduce(ctx, P, ncomp, out0, out, P.d0 > 0 ? (1u << ncomp) - 1u : acc_mask);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 }  // namespace h6

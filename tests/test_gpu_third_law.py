@@ -71,3 +71,17 @@ def test_gradient(n, eps):
     for k, name in enumerate("xva"):
         assert np.abs(from_rows(GP, k) - ref[name]).max() <= 1e-11 * np.abs(ref[name]).max(), name
     assert np.abs(gm.cpu().numpy() - 0.25 - ref["m"]).max() <= 1e-11 * np.abs(ref["m"]).max()
+
+
+@pytest.mark.parametrize("eps", [1e-2, 0.0])
+@pytest.mark.parametrize("n,n_act", [(2, 1), (300, 33), (513, 513), (2199, 2199), (2200, 2200), (2305, 2305)])
+def test_double_single(n, n_act, eps):
+    # the bounds of the EX tests: 2e-12, 4e-12, 1e-11 for a, j, s
+    x, v, m = ics.plummer(n, 930 + n)
+    a = np.ascontiguousarray(-x / ((x * x).sum(axis=1, keepdims=True) + 0.35) ** 1.5)
+    act = np.arange(n - n_act, n, dtype=np.int32) if n_act < n else None
+    got = gpu_evaluate(h6.Context(n, eps), x, v, a, m, active=act, precision=h6.H6_EX)
+    idx = None if act is None else act.astype(np.int64)
+    want = oracle.forces(x, v, m, eps * eps, a=a, idx=idx, order=2)[:3]
+    for g, w, tol in zip(got, want, (2e-12, 4e-12, 1e-11)):
+        assert vec_rel_err(g, w).max() <= tol

@@ -3,7 +3,8 @@ of their shapes: tile (512 sources), slice (64) and target-group remainders,
 one target to a part-filled last group, with and without the self mask.
 
 Evaluation bound: 1e-12 relative to the oracle, as for the other kernels.
-Shared steps: the one-kernel steps and the separate kernels (a forced launch
+Shared steps: the one-kernel steps (and from 4097 particles on the two-kernel
+ones) and the separate kernels (a forced launch
 shape) do the same arithmetic but for the order of the pair sums, which
 differ by about 1e-15 relative; over the 3 steps of 1/1024 of a Plummer
 sphere at softening 1/64 that stays below 1e-12 of the largest component.
@@ -38,7 +39,7 @@ def test_evaluation_edges(n, n_act, eps):
         assert vec_rel_err(g, w).max() <= 1e-12
 
 
-@pytest.mark.parametrize("n", [1, 2, 255, 257, 513, 2049, 6000])
+@pytest.mark.parametrize("n", [1, 2, 255, 257, 513, 2049, 4096, 4097])
 @pytest.mark.parametrize("nsteps", [1, 3])
 def test_shared_steps_one_kernel(n, nsteps):
     h, eps = 1.0 / 1024, 1.0 / 64
@@ -64,11 +65,12 @@ def test_shared_steps_one_kernel(n, nsteps):
         assert float((g - w).abs().max()) <= 1e-11 * float(w.abs().max())
 
 
-def test_shared_steps_at_once_or_one_by_one():
+@pytest.mark.parametrize("n", [777, 6001])
+def test_shared_steps_at_once_or_one_by_one(n):
     # the backward pass replays single steps and relies on the same values
     runs = []
     for counts in ([5], [1] * 5, [2, 3]):
-        s = h6.System(*ics.plummer(777, 4), 1e-3)
+        s = h6.System(*ics.plummer(n, 4), 1e-3)
         s.startup()
         for c in counts:
             s.shared_steps(1.0 / 256, c)
