@@ -116,6 +116,35 @@ __global__ __launch_bounds__(64) void k_eval_small(SrcPtrs src, const int32_t *_
                                    blockIdx.x, blockIdx.y);
 }
 
+// Slice reduction, many slices of few outputs: one wave per output, its lanes
+// over the slices (eight loads each in flight), merged by the row butterfly.
+constexpr int kRedOutWaves = 4;
+__global__ __launch_bounds__(64 * kRedOutWaves) void k_reduce_slices_wave(
+    const double *__restrict__ partial, int n_split, int ncomp, int out0, int n_act, OutPtrs out,
+    unsigned acc_mask, const int32_t *__restrict__ list) {
+    const int lane = threadIdx.x & 63;
+    const int total = ncomp * n_act;
+    const int idx = (int)blockIdx.x * kRedOutWaves + (int)(threadIdx.x >> 6);
+    if (idx >= total) return;
+    const double *__restrict__ p = partial + idx;
+    double s = 0.0, comp = 0.0;
+    for (int s0 = lane; s0 < n_split; s0 += 8 * 64) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int sl = s0 + u * 64;
+            x[u] = sl < n_split ? p[(int64_t)sl * total] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) two_sum_into(s, comp, x[u]);
+    }
+    seg_comp_reduce_n<1>(&s, &comp, 64);  // valid in lane 63
+    if (lane != 63) return;
+    const int c = idx / n_act, k = idx - c * n_act;
+    double *dst = &out.p[out0 + c][list ? list[k] : k];
+    *dst = ((acc_mask >> c) & 1u) ? *dst + (s + comp) : s + comp;
+}
+
 template <int ORDER, int BLOCK, int IPL>
 hipError_t dispatch_f64(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
                         const int32_t *active, int n, int n_act, double eps2, int slice_len,
@@ -184,6 +213,12 @@ hipError_t dispatch_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const 
                                 slice_len, OUT0, out, slice_stride);
 }
 
+// Up to this many outputs, each has a wave: 64 coalesced outputs a workgroup
+// would leave all but total / 64 CUs idle. Single precision over 65536 sources
+// (1024 slices), evaluation and reduction, many / wave: 1 target 23.3 / 14.3
+// us, 40 targets 26.1 / 18.2, 200 (1800 outputs) 43.4 / 43.5, 700 98.6 / 100.9,
+// 1000 137 / 175 us.
+constexpr int64_t kWaveReduceMaxOut = 2048;
 // From this many slices the reduction splits them over waves.
 constexpr int kManyReduceMinSplit = 16;
 // Active sets up to this size use the source-parallel kernel by default.
@@ -436,7 +471,11 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
 hipError_t launch_reduce(h6_ctx ctx, const double *partial, int n_split, int ncomp, int out0,
                          int n_act, const OutPtrs &out, unsigned acc_mask, const int32_t *list) {
     const int64_t total = (int64_t)ncomp * n_act;
-    if (n_split >= kManyReduceMinSplit) {
+    if (n_split >= kManyReduceMinSplit && total <= kWaveReduceMaxOut) {
+        hipLaunchKernelGGL(k_reduce_slices_wave, dim3(ceil_div(total, kRedOutWaves)),
+                           dim3(64 * kRedOutWaves), 0, ctx->stream, partial, n_split, ncomp, out0,
+                           n_act, out, acc_mask, list);
+    } else if (n_split >= kManyReduceMinSplit) {
         hipLaunchKernelGGL(k_reduce_slices_many, dim3(ceil_div(total, 64)), dim3(64 * kRedWaves), 0,
                            ctx->stream, partial, n_split, ncomp, out0, n_act, out, acc_mask, list);
     } else {

@@ -340,6 +340,10 @@ __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *_
             }
         }
         __syncthreads();
+        // by four, so that a record's LDS reads overlap the previous pairs (the
+        // lone wave of a small set waited for each: 2048 of 2048 targets 23.8
+        // -> 14.5 us, 1000 of 10007 41.5 -> 30.8 us, 10007 of 10007 unchanged)
+#pragma unroll 4
         for (int q = 0; q < BLOCK; ++q) {
             const float4 r0 = tile[q * 3], r1 = tile[q * 3 + 1], r2v = tile[q * 3 + 2];
             const float dx = r0.x - xi[0], dy = r0.y - xi[1], dz = r0.z - xi[2];
