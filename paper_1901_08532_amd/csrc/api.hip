@@ -810,11 +810,11 @@ int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, co
     if (int rc = check_n(ctx, n)) return rc;
     if (!std::isfinite(dt) || dt <= 0.0 || nsteps < 0) return fail_arg(ctx, "bad dt or step count");
     if (!precision_ok(precision)) return fail_arg(ctx, "bad precision");
-    if (nsteps > 0 && (precision == H6_EX || (precision == H6_FP64 && !eval_shape_forced(ctx)))) {
+    if (nsteps > 0 && (precision == H6_EX || (precision != H6_SP && !eval_shape_forced(ctx)))) {
         if (n <= one_kernel_max(precision))
             return shared_steps_small(ctx, st, n, pred, f, dt, nsteps, precision);
         SymPlan P;
-        if (eval_sym_single(ctx, precision, (int)n, &P))
+        if (precision != H6_MIXED && eval_sym_single(ctx, precision, (int)n, &P))
             return shared_steps_sym(ctx, st, P, pred, f, dt, nsteps, precision);
     }
     for (int64_t k = 0; k < nsteps; ++k) {

@@ -221,8 +221,12 @@ hipError_t dispatch_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const 
 constexpr int64_t kWaveReduceMaxOut = 2048;
 // From this many slices the reduction splits them over waves.
 constexpr int kManyReduceMinSplit = 16;
-// Active sets up to this size use the source-parallel kernel by default.
-constexpr int kDefaultSmallMax = 32;
+// Mixed evaluations of up to this many pairs take the whole-workgroup kernel.
+// Beyond, its third of converted positions a pair more than the tile kernel's
+// two targets a lane tells. Tile / whole workgroups: 33 of 1024 41 / 9.2 us, 300
+// of 10007 42.6 / 15.2, 6000 of 20000 230 / 212, 1000 of 65536 168 / 130, 2000 of
+// 65536 235 / 240, 8192 of 65536 772 / 835 us.
+constexpr int64_t kWgMaxPairsMixed = 120000000;
 // Active sets up to this size use the whole-workgroup kernel (FP64); beyond,
 // the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets
 // 252 against 254 us, all 495 against 468).
@@ -284,8 +288,10 @@ EvalConfig choose_wg(h6_ctx ctx, int order, int precision, int n, int n_act) {
     cfg.ipl = 1;
     cfg.n_split = 1;
     float best = 3.0e38f;
+    const int run = precision == H6_MIXED ? 8 : 1;  // consecutive sources of a strand
     for (int l = 0; l < 6; ++l) {
         const int tgt = 1 << l, strands = kWgThreads / tgt;
+        if (precision == H6_MIXED && tgt < kMixedWgMinTgt) continue;
         const int groups = ceil_div(n_act, tgt);
         for (int sp : kSplits) {
             if (sp > 1 && (n / sp < 64 || (int64_t)sp * ncomp * n_act > ctx->partial_cap)) break;
@@ -293,7 +299,7 @@ EvalConfig choose_wg(h6_ctx ctx, int order, int precision, int n, int n_act) {
             const int eff = ceil_div(n, slice);
             const float c = (float)ceil_div((int64_t)groups * eff, ctx->n_cu);
             const int tiles = ceil_div(slice, kWgThreads);
-            const int steps = slice / kWgThreads * tgt + ceil_div(slice % kWgThreads, strands);
+            const int steps = slice / kWgThreads * tgt + ceil_div(slice % kWgThreads, strands * run) * run;
             const float issue = (precision == H6_EX ? 2.6f : 0.196f) * (float)steps;
             float cost = std::max(c * issue * kWgShare[l], issue + 0.7f * (float)tiles) + 1.2f * c;
             if (eff > 1) cost += 1.2f + (float)eff * (float)n_act * 3.6e-5f;
@@ -323,7 +329,13 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
         return cfg;
     }
     // a launch shape forced by h6_set_eval_config takes the kernels it names
-    if (precision == H6_FP64 && n_act <= kWgMaxAct && !(order == 2 && eval_shape_forced(ctx)))
+    // (the mixed source-parallel kernel of the smallest sets sums other sources
+    // together in FP32, and is as fast)
+    const bool forced = order == 2 && eval_shape_forced(ctx);
+    if (precision == H6_FP64 && n_act <= kWgMaxAct && !forced)
+        return choose_wg(ctx, order, precision, n, n_act);
+    if (precision == H6_MIXED && order == 2 && n_act > kDefaultSmallMax &&
+        (int64_t)n * n_act <= kWgMaxPairsMixed && !forced)
         return choose_wg(ctx, order, precision, n, n_act);
     const int small_max = ctx->cfg_small >= 0 ? ctx->cfg_small : kDefaultSmallMax;
     if (order == 2 && n_act <= small_max) {
@@ -434,6 +446,10 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
     } else if (precision == H6_SP) {
         e = dispatch_sp(skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
                          slice_len, dst, slice_stride);
+    } else if (precision == H6_MIXED && wg) {
+        e = dispatch_mixed_wg(cfg.ipl, skipself, dim3(ceil_div(n_act, cfg.ipl), cfg.n_split),
+                              ctx->stream, src, active, n, n_act, ctx->eps2, slice_len, dst,
+                              slice_stride);
     } else if (order == 2 && precision == H6_MIXED) {
         dim3 g = cfg.kind == 1 ? dim3(ceil_div(n_act, cfg.ipl), cfg.n_split) : grid;
         e = dispatch_mixed(cfg, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,

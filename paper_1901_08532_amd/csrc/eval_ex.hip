@@ -209,6 +209,8 @@ constexpr float kPadPosF = 1.0e18f;
 template <bool SKIPSELF>
 struct ExOps {
     using Word = float2;  // high and low part
+    using Acc = float2;
+    static constexpr int kRun = 1, kMinTgt = 1;
     using Sum = CompSum;  // slices: FP64
     static constexpr int NF = 10, NREC = 5, NI = 9, NJ = 9, K = 1, kUnroll = 1;
     struct Target {
@@ -227,6 +229,10 @@ struct ExOps {
     static __device__ __forceinline__ float2 pad(int f) {
         return make_float2(f < 3 ? kPadPosF : 0.0f, 0.0f);
     }
+    __device__ __forceinline__ void load_rec(int jj, Word2<float2> *rec) const {
+        rec_from_fields(*this, jj, rec);
+    }
+    static __device__ __forceinline__ void pad_rec(Word2<float2> *rec) { rec_padding<ExOps>(rec); }
     __device__ __forceinline__ void load(int k, int n, Target &t) const {
         const bool in = k < n;
         const int kc = in ? k : n - 1;

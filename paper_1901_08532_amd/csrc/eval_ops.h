@@ -66,9 +66,27 @@ __device__ __forceinline__ void pair_both(const double *r, const double *v, cons
     }
 }
 
+// Whole records from an OPS with one array per word.
+template <class OPS>
+__device__ __forceinline__ void rec_from_fields(const OPS &ops, int jj,
+                                                Word2<typename OPS::Word> *rec) {
+    auto *w = reinterpret_cast<typename OPS::Word *>(rec);
+#pragma unroll
+    for (int f = 0; f < 2 * OPS::NREC; ++f)
+        w[f] = f < OPS::NF ? OPS::word(ops.field(f)[jj]) : typename OPS::Word{};
+}
+template <class OPS>
+__device__ __forceinline__ void rec_padding(Word2<typename OPS::Word> *rec) {
+    auto *w = reinterpret_cast<typename OPS::Word *>(rec);
+#pragma unroll
+    for (int f = 0; f < 2 * OPS::NREC; ++f) w[f] = f < OPS::NF ? OPS::pad(f) : typename OPS::Word{};
+}
+
 template <int ORDER, bool SKIPSELF>
 struct EvalOps {
     using Word = double;
+    using Acc = double;
+    static constexpr int kRun = 1, kMinTgt = 1;
     using Sum = CompSum;
     static constexpr int NF = ORDER == 1 ? 7 : ORDER == 2 ? 10 : 13;  // x, m, v, a, j
     static constexpr int NREC = Traits<ORDER>::NREC;
@@ -88,6 +106,12 @@ struct EvalOps {
     }
     static __device__ __forceinline__ double word(double x) { return x; }
     static __device__ __forceinline__ double pad(int f) { return f < 3 ? kPadPos : 0.0; }
+    __device__ __forceinline__ void load_rec(int jj, Word2<double> *rec) const {
+        rec_from_fields(*this, jj, rec);
+    }
+    static __device__ __forceinline__ void pad_rec(Word2<double> *rec) {
+        rec_padding<EvalOps>(rec);
+    }
     __device__ __forceinline__ void load(int k, int n, Target &t) const {
         const bool in = k < n;
         PredSrc{src, nullptr}.template get<ORDER>(in ? k : n - 1, t.x, t.v, t.a, t.j);

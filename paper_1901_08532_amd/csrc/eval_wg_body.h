@@ -13,7 +13,9 @@
 // busy at n = n_act = 1024). h6_evaluate, this kernel and any slice
 // reduction, before and after: n = n_act = 1024 63 -> 7.8 us, 40 of 4096
 // 41.7 -> 8.6 us, 4096 of 4096 67 -> 40 us, 300 of 65536 73 -> 53 us, 1000 of
-// 65536 137 -> 134 us, 7 of 1024 8.3 -> 6.2 us.
+// 65536 137 -> 134 us, 7 of 1024 8.3 -> 6.2 us. The mixed form: 33 of 1024
+// 41 -> 9.2 us, 1024 of 1024 67 -> 9.8 us, 4096 of 4096 75 -> 37 us, 1000 of
+// 65536 168 -> 128 us.
 #pragma once
 
 #include "eval_ops.h"
@@ -27,20 +29,26 @@ constexpr int kWgFlush = 64;   // sources per strand between compensated flushes
 constexpr int kWgPerSum = 16;  // strand sums one thread adds in the final reduction
 
 // Workgroup memory of wg_sums, in bytes: a tile, or the strand sums.
-template <class OPS>
+template <int TGT, class OPS>
 constexpr int wg_pool_bytes() {
-    return OPS::NREC * kWgThreads * (int)sizeof(Word2<typename OPS::Word>);
+    constexpr int tile = OPS::NREC * kWgThreads * (int)sizeof(Word2<typename OPS::Word>);
+    constexpr int sums = OPS::NI * (kWgThreads + TGT) * (int)sizeof(double);
+    return tile > sums ? tile : sums;
 }
 
 // Sums of the targets g * TGT .. g * TGT + TGT - 1 (of list; NULL: particles)
 // over the sources [jb, je), into fs[t * NI + q] (workgroup memory, TGT * NI
-// doubles). OPS as in sym_body.h (one(), add(), value()). Every thread of the
+// doubles). OPS as in sym_body.h (one(), add(), value()), with load_rec() and
+// pad_rec() for whole records, Acc the type of a strand's running sums, and
+// kRun: a strand takes kRun consecutive sources in a row (1, or 8 for the mixed
+// form, whose FP32 sums cover 8 consecutive sources). Every thread of the
 // workgroup calls it; it ends with a barrier.
 template <int TGT, class OPS>
 __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restrict__ list, int n,
                                         int n_act, int g, int jb, int je, void *pool, double *fs) {
     using W = typename OPS::Word;
-    constexpr int NREC = OPS::NREC, NF = OPS::NF, NACC = OPS::NI;
+    using A = typename OPS::Acc;
+    constexpr int NREC = OPS::NREC, NACC = OPS::NI, RUN = OPS::kRun;
     constexpr int STR = kWgThreads / TGT;  // strands
     const int tid = threadIdx.x;
     const int t = tid % TGT, s = tid / TGT;
@@ -48,11 +56,11 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
     const int pid = list ? list[kc] : kc;
     typename OPS::Target tgt;
     ops.load(pid, n, tgt);
-    W acc[NACC];
+    A acc[NACC];
     typename OPS::Sum sum[NACC];
 #pragma unroll
     for (int q = 0; q < NACC; ++q) {
-        acc[q] = W{};
+        acc[q] = A{};
         sum[q] = {};
     }
     auto *tile = static_cast<Word2<W> *>(pool);
@@ -60,33 +68,53 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
     int since = 0;
     for (int jt = jb; jt < je; jt += kWgThreads) {
         const int cnt = min(kWgThreads, je - jt);
+        // the target's own entry (never the padding past a slice's end: a mixed
+        // term overflows where a mask makes the radius of 1e15 one)
+        const int own = pid - jt < cnt ? pid - jt : -1;
         if (jt != jb) __syncthreads();  // previous tile fully consumed
         {
             Word2<W> rec[NREC];
-            W *w = reinterpret_cast<W *>(rec);
+            if (tid < cnt)
+                ops.load_rec(jt + tid, rec);
+            else
+                OPS::pad_rec(rec);
+            // slots in the order the strands read them: step by step, the
+            // strands of a step side by side
+            const int run = tid / RUN;
+            const int slot = (run / STR * RUN + tid % RUN) * STR + run % STR;
 #pragma unroll
-            for (int f = 0; f < 2 * NREC; ++f)
-                w[f] = f >= NF ? W{} : tid < cnt ? OPS::word(ops.field(f)[jt + tid]) : OPS::pad(f);
-#pragma unroll
-            for (int q = 0; q < NREC; ++q) tile[q * kWgThreads + tid] = rec[q];
+            for (int q = 0; q < NREC; ++q) tile[q * kWgThreads + slot] = rec[q];
         }
         __syncthreads();
-        const int steps = (cnt + STR - 1) / STR;
-#pragma unroll OPS::kUnroll
-        for (int i = 0; i < steps; ++i) {
-            const int e = i * STR + s;
+        const int steps = (cnt + STR * RUN - 1) / (STR * RUN) * RUN;
+        auto step = [&](int i) {
             Word2<W> rec[NREC];
 #pragma unroll
-            for (int q = 0; q < NREC; ++q) rec[q] = tile[q * kWgThreads + e];
-            ops.one(rec, tgt, jt + e == pid, acc);
-        }
-        since += TGT;
-        if (since >= kWgFlush) {
-            since = 0;
+            for (int q = 0; q < NREC; ++q) rec[q] = tile[q * kWgThreads + i * STR + s];
+            const int e = RUN == 1 ? i * STR + s : (i / RUN * STR + s) * RUN + i % RUN;
+            ops.one(rec, tgt, e == own, acc);
+        };
+        auto flush = [&]() {
 #pragma unroll
             for (int q = 0; q < NACC; ++q) {
                 OPS::add(sum[q], acc[q]);
-                acc[q] = W{};
+                acc[q] = A{};
+            }
+        };
+        if constexpr (RUN == 1) {
+#pragma unroll OPS::kUnroll
+            for (int i = 0; i < steps; ++i) step(i);
+            since += TGT;
+            if (since >= kWgFlush) {
+                since = 0;
+                flush();
+            }
+        } else {
+#pragma unroll 1
+            for (int i = 0; i < steps; i += RUN) {
+#pragma unroll
+                for (int r = 0; r < RUN; ++r) step(i + r);
+                flush();
             }
         }
     }
@@ -95,11 +123,9 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
     // wave's rows fall on different banks
     double *red = static_cast<double *>(pool);
     constexpr int LD = STR + 1;
-    static_assert(NACC * TGT * LD * (int)sizeof(double) <= wg_pool_bytes<OPS>(),
-                  "strand sums fit the tile");
 #pragma unroll
     for (int q = 0; q < NACC; ++q) {
-        OPS::add(sum[q], acc[q]);
+        if constexpr (RUN == 1) OPS::add(sum[q], acc[q]);
         red[(q * TGT + t) * LD + s] = OPS::value(sum[q]);
     }
     __syncthreads();
@@ -118,6 +144,15 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
     __syncthreads();
 }
 
+// f(integral_constant of 1, 2, .. kWgMaxTgt) until one returns true.
+template <class F>
+bool for_each_tgt(F f) {
+    static_assert(kWgMaxTgt == 32, "the list below");
+    return f(std::integral_constant<int, 1>{}) || f(std::integral_constant<int, 2>{}) ||
+           f(std::integral_constant<int, 4>{}) || f(std::integral_constant<int, 8>{}) ||
+           f(std::integral_constant<int, 16>{}) || f(std::integral_constant<int, 32>{});
+}
+
 // Evaluation by whole workgroups: target group blockIdx.x, source slice
 // blockIdx.y.
 template <int TGT, class OPS>
@@ -125,7 +160,7 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4)))
     OPS ops, const int32_t *__restrict__ active, int n, int n_act, int slice_len, int out0,
     OutPtrs out, int64_t slice_stride) {
     constexpr int NACC = OPS::NI;
-    __shared__ double2 pool[wg_pool_bytes<OPS>() / sizeof(double2)];
+    __shared__ double2 pool[wg_pool_bytes<TGT, OPS>() / sizeof(double2)];
     __shared__ double fs[TGT * NACC];
     const int g = blockIdx.x, jb = (int)blockIdx.y * slice_len;
     wg_sums<TGT>(ops, active, n, n_act, g, jb, min(n, jb + slice_len), pool, fs);
@@ -137,25 +172,23 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4)))
     }
 }
 
-// Launch for tgt targets a workgroup (a power of two up to kWgMaxTgt).
+// Launch for tgt targets a workgroup (a power of two from OPS::kMinTgt to
+// kWgMaxTgt).
 template <class OPS>
 hipError_t launch_wg(int tgt, dim3 grid, hipStream_t st, const OPS &ops, const int32_t *active,
                      int n, int n_act, int slice_len, int out0, const OutPtrs &out,
                      int64_t slice_stride) {
-#define H6_WG(T)                                                                              \
-    if (tgt == T) {                                                                           \
-        hipLaunchKernelGGL((k_eval_wg<T, OPS>), grid, dim3(kWgThreads), 0, st, ops, active, n, \
-                           n_act, slice_len, out0, out, slice_stride);                        \
-        return hipGetLastError();                                                             \
-    }
-    H6_WG(1)
-    H6_WG(2)
-    H6_WG(4)
-    H6_WG(8)
-    H6_WG(16)
-    H6_WG(32)
-#undef H6_WG
-    return hipErrorInvalidValue;
+    auto launch = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        if constexpr (T >= OPS::kMinTgt) {
+            if (tgt != T) return false;
+            hipLaunchKernelGGL((k_eval_wg<T, OPS>), grid, dim3(kWgThreads), 0, st, ops, active, n,
+                               n_act, slice_len, out0, out, slice_stride);
+            return true;
+        }
+        return false;
+    };
+    return for_each_tgt(launch) ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 }  // namespace evalbody

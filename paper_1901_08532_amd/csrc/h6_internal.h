@@ -221,6 +221,8 @@ hipError_t launch_eval_sym(h6_ctx ctx, int order, int precision, const SrcPtrs &
 // FP64 n = 4096 52 us a step and 5000 67 by the third law; EX 2048 77 and 2200
 // 98, in one kernel 135).
 constexpr int kSymMinF64 = 5000, kSymMinEx = 2200;
+// Active sets up to this size use the source-parallel kernel by default.
+constexpr int kDefaultSmallMax = 32;
 constexpr int kOneKernelMaxF64 = 4096, kOneKernelMaxEx = 2048;
 inline int sym_min(int precision) { return precision == H6_EX ? kSymMinEx : kSymMinF64; }
 inline int one_kernel_max(int precision) {
@@ -232,6 +234,12 @@ int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_
 hipError_t dispatch_mixed(const EvalConfig &cfg, bool skipself, dim3 grid, hipStream_t st,
                           const SrcPtrs &src, const int32_t *active, int n, int n_act, double eps2,
                           int slice_len, const OutPtrs &out, int64_t slice_stride);
+// The mixed form by whole workgroups. From 16 targets each: 32 strands of 8
+// consecutive sources are half a tile, 64 strands the whole of it.
+constexpr int kMixedWgMinTgt = 16;
+hipError_t dispatch_mixed_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+                             const int32_t *active, int n, int n_act, double eps2, int slice_len,
+                             const OutPtrs &out, int64_t slice_stride);
 // Double-single (H6_EX) order-2 kernel by whole workgroups (tgt targets each),
 // and the single-precision (H6_SP) one: kSpBlock threads, one target per lane
 // (eval_ex.hip).
@@ -247,13 +255,15 @@ hipError_t launch_predict(h6_ctx ctx, const h6_state *st, int n, int64_t t_tick,
 hipError_t launch_correct(h6_ctx ctx, h6_state *st, const int32_t *active, int n_act,
                           const h6_force *f, int64_t t_next, double dt, const h6_params *prm,
                           bool shared);
-// One shared step of a small system in one kernel (shared_step.hip), FP64 or
-// EX: reads the predicted sources src, corrects st, and either predicts the
+// One shared step of a small system in one kernel (shared_step.hip), FP64,
+// mixed or EX: reads the predicted sources src, corrects st, and either predicts the
 // next step into out or, for the last one, writes the forces to f.
 // shared_step_targets: the targets a workgroup takes.
 int shared_step_targets(h6_ctx ctx, int n);
 hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, int precision, const SrcPtrs &src,
                               double dt, bool predict, const h6_pred *out, const h6_force *f);
+hipError_t launch_mixed_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
+                                    bool predict, const h6_pred *out, const h6_force *f);
 hipError_t launch_ex_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
                                  bool predict, const h6_pred *out, const h6_force *f);
 hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, int lev_min,

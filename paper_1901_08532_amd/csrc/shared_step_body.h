@@ -4,9 +4,10 @@
 // Bound by latency at these sizes: as separate kernels (predict, evaluate,
 // reduce, correct) a step paid four launches and their memory round trips,
 // 4.5 to 5 us each, beside 62 us of evaluation on 32 waves at n = 1024
-// (70 us a step; 9.2 us with this kernel). Here a workgroup sums its targets over all sources
-// (eval_wg_body.h: no slice sums in memory), corrects them and predicts them
-// to the next step. Other workgroups still read the sources' predicted
+// (70 us a step; 9.2 us with this kernel). The mixed form: n = 32 11.1 -> 5.0 us
+// a step, 256 46 -> 7.9, 1024 75 -> 14, 4096 82 -> 45. Here a workgroup sums its
+// targets over all sources (eval_wg_body.h: no slice sums in memory), corrects
+// them and predicts them to the next step. Other workgroups still read the sources' predicted
 // arrays, so the predictions go to a second set; the caller alternates them.
 #pragma once
 
@@ -24,7 +25,7 @@ template <int TGT, class OPS>
 __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_shared_step(
     h6_state st, OPS ops, int n, double h, bool predict, h6_pred out, h6_force f, int32_t *flags) {
     constexpr int kOld = 15;  // x, v, a, j, s of each target
-    __shared__ double2 pool[wg_pool_bytes<OPS>() / sizeof(double2)];
+    __shared__ double2 pool[wg_pool_bytes<TGT, OPS>() / sizeof(double2)];
     __shared__ double fs[TGT * 9];
     __shared__ double old[kOld][TGT];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -69,22 +70,19 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(4)))
 template <class OPS>
 hipError_t launch_shared_step_ops(h6_ctx ctx, const OPS &ops, h6_state *st, int n, double dt,
                                   bool predict, const h6_pred *out, const h6_force *f) {
-    const int tgt = shared_step_targets(ctx, n);
-    const dim3 grid((n + tgt - 1) / tgt);
-#define H6_STEP(T)                                                                              \
-    if (tgt == T) {                                                                             \
-        hipLaunchKernelGGL((k_shared_step<T, OPS>), grid, dim3(kWgThreads), 0, ctx->stream, *st, \
-                           ops, n, dt, predict, *out, *f, ctx->flags);                          \
-        return hipGetLastError();                                                               \
-    }
-    H6_STEP(1)
-    H6_STEP(2)
-    H6_STEP(4)
-    H6_STEP(8)
-    H6_STEP(16)
-    H6_STEP(32)
-#undef H6_STEP
-    return hipErrorInvalidValue;
+    int tgt = shared_step_targets(ctx, n);
+    if (tgt < OPS::kMinTgt) tgt = OPS::kMinTgt;
+    auto launch = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        if constexpr (T >= OPS::kMinTgt) {
+            if (tgt != T) return false;
+            hipLaunchKernelGGL((k_shared_step<T, OPS>), dim3((n + T - 1) / T), dim3(kWgThreads), 0,
+                               ctx->stream, *st, ops, n, dt, predict, *out, *f, ctx->flags);
+            return true;
+        }
+        return false;
+    };
+    return for_each_tgt(launch) ? hipGetLastError() : hipErrorInvalidValue;
 }
 
 }  // namespace stepbody
