@@ -205,7 +205,8 @@ constexpr float kPadPosF = 1.0e18f;
 
 // Particles and pairs of the EX evaluation (sym_body.h, eval_wg_body.h).
 // Bound by FP32 issue: about 720 operations for the terms of one particle and
-// 150 more for both. All particles of n = 4096: 335 -> 222 us.
+// 150 more for both. All particles of n = 4096: 335 -> 200 us
+// (155 registers: three waves per SIMD).
 template <bool SKIPSELF>
 struct ExOps {
     using Word = float2;  // high and low part
@@ -298,7 +299,7 @@ struct ExOps {
 };
 
 template <bool SKIPSELF>
-__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_ex_sym(
+__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_ex_sym(
     SrcPtrs src, SymPlan P, double eps2, double *__restrict__ partial) {
     sym_run(ExOps<SKIPSELF>{src, eps2}, P, partial);
 }

@@ -39,12 +39,13 @@ __global__ __launch_bounds__(256) void k_sym_reduce(const double *__restrict__ p
 }
 
 // Particles of a superblock and the price of a cell. FP64: n = 16384 in 9
-// whole chunks a run takes 352 us, in 17 halves 358; EX: n = 4096 in 17
-// sixteenths 190 us.
+// whole chunks a run takes 352 us, in 17 halves 358; EX, whose FP32 operations
+// issue faster the more waves there are: a shared step of n = 4096 on two
+// workgroups a CU 243 us, on three 220, 8192 769 and 708.
 constexpr int kEvalBlock = kSymThreads * EvalOps<2, false>::K;
 int block_of(int precision) { return precision == H6_EX ? kSymThreads : kEvalBlock; }
 SymCost cost_of(int precision) {
-    return precision == H6_EX ? SymCost{180.0f, 1.0f} : SymCost{36.0f, 3.0f};
+    return precision == H6_EX ? SymCost{180.0f, 1.0f, 260.0f} : SymCost{36.0f, 3.0f};
 }
 
 }  // namespace
@@ -84,14 +85,18 @@ bool sym_plan(h6_ctx ctx, int n, int block, int ncomp, SymCost cost, int d0, Sym
     // parts: the longest run, and the sum over slots (their loads go in
     // batches of 8, about 0.55 us each, and at about 3 TB/s)
     float best = 3.0e38f;
-    for (int sub = 1; sub <= kSymMaxSub && fits(m, sub, runs); sub *= 2) {
-        const float longest = (float)((P.cells + P.runs - 1) / P.runs);
-        const float used = (float)(P.slots_j + P.run_count(0));
-        const float t = longest * (cost.chunk / (float)sub + cost.part) +
-                        used * (0.07f + (float)ncomp * (float)n * 2.7e-6f);
-        if (t < best) {
-            best = t;
-            *plan = P;
+    for (int three = 0; three < (cost.chunk3 > 0.0f ? 2 : 1); ++three) {
+        const int r = three ? 3 * ctx->n_cu : runs;
+        const float chunk = three ? cost.chunk3 : cost.chunk;
+        for (int sub = 1; sub <= kSymMaxSub && fits(m, sub, r); sub *= 2) {
+            const float longest = (float)((P.cells + P.runs - 1) / P.runs);
+            const float used = (float)(P.slots_j + P.run_count(0));
+            const float t = longest * (chunk / (float)sub + cost.part) +
+                            used * (0.07f + (float)ncomp * (float)n * 2.7e-6f);
+            if (t < best) {
+                best = t;
+                *plan = P;
+            }
         }
     }
     return true;

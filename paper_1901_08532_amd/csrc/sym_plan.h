@@ -66,9 +66,10 @@ struct SymPlan {
 };
 
 // Price of a cell in microseconds, two workgroups on a CU: a whole chunk's
-// steps, and the fixed part (staging, barriers, sums).
+// steps, and the fixed part (staging, barriers, sums); chunk3: the steps with
+// three on a CU (0: the kernel's registers allow two).
 struct SymCost {
-    float chunk, part;
+    float chunk, part, chunk3 = 0.0f;
 };
 
 // Sums of a batch's slots for particle k, components c, c + ncomp / N, ... (N of
