@@ -823,6 +823,114 @@ __global__ __launch_bounds__(kPotThreads) __attribute__((amdgpu_waves_per_eu(4))
     }
 }
 
+// Particles and pairs of the third-law form for sym_body.h's walk: sums m/R (the
+// potential's negative) and, with GRAD, a. Bound by FP64 issue: 24 operations an
+// unordered pair and 8 / K DPP moves, against 2 x 19 in ordered form. Ordered
+// form and this, GRAD: n = 16384 205 -> 161 us, 65536 2819 -> 1903 us; potential
+// alone: 141 -> 100 and 1962 -> 1212 us. With GRAD four targets a lane (16384
+// with two 165 us, 65536 2182 us), without two (105 and 1114 us with four).
+template <bool GRAD>
+struct PotOps {
+    using Word = double;
+    using Sum = CompSum;
+    static constexpr int NF = 4, NREC = 2, NI = GRAD ? 4 : 1, NJ = NI, K = GRAD ? 4 : 2, kUnroll = 2;
+    struct Target {
+        double x[3], m;
+    };
+    h6_state st;
+    double eps2;
+    __device__ __forceinline__ const double *field(int f) const { return f < 3 ? st.x[f] : st.m; }
+    static __device__ __forceinline__ double word(double x) { return x; }
+    static __device__ __forceinline__ double pad(int f) { return f < 3 ? kPadPosVjp : 0.0; }
+    __device__ __forceinline__ void load(int k, int n, Target &t) const {
+        const bool in = k < n;
+        const int kc = in ? k : n - 1;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) t.x[c] = in ? st.x[c][kc] : -kPadPosVjp;
+        t.m = in ? st.m[kc] : 0.0;
+    }
+    template <bool BOTH>
+    __device__ __forceinline__ void terms(const Word2<double> *e, const Target &t, bool self,
+                                          double *acci, double *accj) const {
+        const double r[3] = {e[0].x - t.x[0], e[0].y - t.x[1], e[1].x - t.x[2]};
+        double r2 = fma(r[2], r[2], fma(r[1], r[1], fma(r[0], r[0], eps2)));
+        double mj = e[1].y;
+        if (!BOTH) {
+            r2 = self ? 1.0 : r2;
+            mj = self ? 0.0 : mj;
+        }
+        const double rinv = rsqrt_f64(r2);
+        if constexpr (GRAD) {
+            const double rinv2 = rinv * rinv;
+            const double pj = mj * rinv, fj = pj * rinv2;
+            acci[0] += pj;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) acci[1 + c] = fma(fj, r[c], acci[1 + c]);
+            if (BOTH) {
+                const double pi = t.m * rinv, fi = pi * rinv2;
+                accj[0] += pi;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) accj[1 + c] = fma(-fi, r[c], accj[1 + c]);
+            }
+        } else {
+            acci[0] = fma(mj, rinv, acci[0]);
+            if (BOTH) accj[0] = fma(t.m, rinv, accj[0]);
+        }
+    }
+    __device__ __forceinline__ void both(const Word2<double> *e, const Target &t, double *acci,
+                                         double *accj) const {
+        terms<true>(e, t, false, acci, accj);
+    }
+    __device__ __forceinline__ void one(const Word2<double> *e, const Target &t, bool self,
+                                        double *acci) const {
+        terms<false>(e, t, self, acci, nullptr);
+    }
+    static __device__ __forceinline__ void add(Sum &s, double x) { two_sum_into(s.hi, s.lo, x); }
+    static __device__ __forceinline__ double value(const Sum &s) { return s.hi + s.lo; }
+    static __device__ __forceinline__ double value(double x) { return x; }
+};
+
+template <bool GRAD>
+__global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_pot_sym(
+    h6_state st, SymPlan P, double eps2, double *__restrict__ partial) {
+    sym_run(PotOps<GRAD>{st, eps2}, P, partial);
+}
+
+// The slots' sums and, with GRAD, the gradient's components from them: one sum
+// of one particle per thread.
+template <bool GRAD>
+__global__ __launch_bounds__(256) void k_pot_sums(const double *__restrict__ partial, SymPlan P,
+                                                  h6_state st, const double *__restrict__ cot,
+                                                  double *__restrict__ phi, h6_state out) {
+    const int n = P.n;
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (int64_t)PotOps<GRAD>::NI * n) return;
+    const int q = (int)(idx / n), i = (int)(idx - (int64_t)q * n);
+    double s;
+    sym_sums<1>(partial, P, PotOps<GRAD>::NI, q, i, &s);
+    if constexpr (GRAD) {
+        const double g = cot ? *cot : 1.0;
+        if (q == 0) {
+            double vv = 0.0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) vv = fma(st.v[c][i], st.v[c][i], vv);
+            out.m[i] = g * fma(0.5, vv, -s);
+        } else {
+            const int c = q - 1;
+            const double mi = st.m[i];
+            out.x[c][i] = -g * (mi * s);
+            out.v[c][i] = g * (mi * st.v[c][i]);
+        }
+    } else {
+        phi[i] = -s;
+    }
+}
+
+// From this size on each pair once, where one batch of slots holds the sums. The
+// ordered and the third-law form, us: GRAD n = 4096 23 and 34, 6000 48 and 47,
+// 8192 67 and 64; potential 4096 18 and 22, 6000 33 and 30.
+constexpr int kPotSymMin = 6000;
+
 // Thread targets TG (a power of two): the rounds of workgroups a CU takes
 // times the length of one, which per target is longer with few targets (more
 // distinct LDS records a wave reads, kShare, measured at n = 65536 in units
@@ -833,6 +941,20 @@ hipError_t launch_pot(h6_ctx ctx, const h6_state *st, int n, const double *cot, 
                       h6_state *out) {
     static const float kShare[6] = {2.6f, 1.71f, 1.28f, 1.10f, 1.0f, 0.97f};
     const h6_state none = {};
+    if (n >= kPotSymMin) {
+        using Ops = PotOps<GRAD>;
+        constexpr int kBlock = kSymThreads * Ops::K;
+        SymPlan P;
+        if (sym_plan(ctx, n, kBlock, Ops::NI, GRAD ? SymCost{28.0f, 3.0f} : SymCost{20.0f, 3.0f}, 0, &P) &&
+            P.d1 == P.nsb / 2 + 1) {
+            hipLaunchKernelGGL((k_pot_sym<GRAD>), dim3(P.runs), dim3(kSymThreads), 0, ctx->stream,
+                               *st, P, ctx->eps2, ctx->partial);
+            hipLaunchKernelGGL((k_pot_sums<GRAD>),
+                               dim3((unsigned)(((int64_t)Ops::NI * n + 255) / 256)), dim3(256), 0,
+                               ctx->stream, ctx->partial, P, *st, cot, phi, out ? *out : none);
+            return hipGetLastError();
+        }
+    }
     int tg = 1;
     float best = 3.0e38f;
     for (int l = 0; l < 6; ++l) {
