@@ -444,7 +444,7 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
                            ctx->stream, src, active, n, n_act, ctx->eps2, slice_len, dst,
                            slice_stride);
     } else if (precision == H6_SP) {
-        e = dispatch_sp(skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
+        e = dispatch_sp(ctx->n_cu, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
                          slice_len, dst, slice_stride);
     } else if (precision == H6_MIXED && wg) {
         e = dispatch_mixed_wg(cfg.ipl, skipself, dim3(ceil_div(n_act, cfg.ipl), cfg.n_split),

@@ -305,7 +305,92 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(3))
 }
 
 // ---------------------------------------------------------------- SP
-// LDS record of one source: x, v, a, m as floats (plus padding), three float4.
+// Bound by FP32 issue (54 operations a pair). A target's sum over a slice is one
+// serial chain, so a small set has about one chain a SIMD, and one wave alone
+// issues an operation in 4.8 clocks where two take 3.05 each.
+struct SpTarget {
+    float x[3], v[3], a[3];
+    int id;
+};
+// What a pair adds to its target: m / R^3 times r, w and u.
+struct SpTerms {
+    float m, r[3], w[3], u[3];
+};
+
+__device__ __forceinline__ SpTarget sp_target(const SrcPtrs &src, int p) {
+    SpTarget t;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        t.x[c] = (float)src.x[c][p];
+        t.v[c] = (float)src.v[c][p];
+        t.a[c] = (float)src.a[c][p];
+    }
+    t.id = p;
+    return t;
+}
+
+// LDS record of source jj: x, m, v, a as floats (plus padding), three float4;
+// far, massless padding from je on.
+struct SpSource {
+    double x[3], v[3], a[3], m;
+};
+__device__ __forceinline__ SpSource sp_load(const SrcPtrs &src, int jj, int je) {
+    SpSource s;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        s.x[c] = jj < je ? src.x[c][jj] : (double)kPadPosF;
+        s.v[c] = jj < je ? src.v[c][jj] : 0.0;
+        s.a[c] = jj < je ? src.a[c][jj] : 0.0;
+    }
+    s.m = jj < je ? src.m[jj] : 0.0;
+    return s;
+}
+__device__ __forceinline__ void sp_store(const SpSource &s, float4 *rec) {
+    rec[0] = make_float4((float)s.x[0], (float)s.x[1], (float)s.x[2], (float)s.m);
+    rec[1] = make_float4((float)s.v[0], (float)s.v[1], (float)s.v[2], (float)s.a[0]);
+    rec[2] = make_float4((float)s.a[1], (float)s.a[2], 0.0f, 0.0f);
+}
+
+template <bool SKIPSELF>
+__device__ __forceinline__ SpTerms sp_pair(const float4 *rec, const SpTarget &t, float eps2,
+                                           int j) {
+    const float4 r0 = rec[0], r1 = rec[1], r2v = rec[2];
+    const float dx = r0.x - t.x[0], dy = r0.y - t.x[1], dz = r0.z - t.x[2];
+    const float dvx = r1.x - t.v[0], dvy = r1.y - t.v[1], dvz = r1.z - t.v[2];
+    const float dax = r1.w - t.a[0], day = r2v.x - t.a[1], daz = r2v.y - t.a[2];
+    float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, eps2)));
+    float mj = r0.w;
+    if (SKIPSELF && j == t.id) {
+        r2 = 1.0f;
+        mj = 0.0f;
+    }
+    // hardware estimate refined by one Newton step
+    const float y0 = __builtin_amdgcn_rsqf(r2);
+    const float rinv = y0 * fmaf(-0.5f * r2 * y0, y0, 1.5f);
+    const float rinv2 = rinv * rinv;
+    const float mr3 = mj * rinv * rinv2;
+    const float alpha = fmaf(dz, dvz, fmaf(dy, dvy, dx * dvx)) * rinv2;
+    const float a3 = 3.0f * alpha;
+    const float wx = fmaf(-a3, dx, dvx), wy = fmaf(-a3, dy, dvy), wz = fmaf(-a3, dz, dvz);
+    const float vvra =
+        fmaf(dz, daz, fmaf(dy, day, fmaf(dx, dax, fmaf(dvz, dvz, fmaf(dvy, dvy, dvx * dvx)))));
+    const float beta = fmaf(alpha, alpha, vvra * rinv2);
+    const float b3 = 3.0f * beta, a6 = a3 + a3;
+    return {mr3,
+            {dx, dy, dz},
+            {wx, wy, wz},
+            {fmaf(-a6, wx, fmaf(-b3, dx, dax)), fmaf(-a6, wy, fmaf(-b3, dy, day)),
+             fmaf(-a6, wz, fmaf(-b3, dz, daz))}};
+}
+__device__ __forceinline__ void sp_add(float *acc, const SpTerms &s) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        acc[c] = fmaf(s.m, s.r[c], acc[c]);
+        acc[3 + c] = fmaf(s.m, s.w[c], acc[3 + c]);
+        acc[6 + c] = fmaf(s.m, s.u[c], acc[6 + c]);
+    }
+}
+
 template <int BLOCK, bool SKIPSELF>
 __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *__restrict__ active,
                                                    int n, int n_act, double eps2_d, int slice_len,
@@ -314,14 +399,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *_
     const int tid = threadIdx.x;
     const int k = (int)blockIdx.x * BLOCK + tid;
     const int kc = k < n_act ? k : n_act - 1;
-    const int p = active ? active[kc] : kc;
-    float xi[3], vi[3], ai[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        xi[c] = (float)src.x[c][p];
-        vi[c] = (float)src.v[c][p];
-        ai[c] = (float)src.a[c][p];
-    }
+    const SpTarget t = sp_target(src, active ? active[kc] : kc);
     const float eps2 = (float)eps2_d;
     float acc[9];
 #pragma unroll
@@ -331,67 +409,97 @@ __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *_
     const int je = min(n, jb + slice_len);
     for (int jt = jb; jt < je; jt += BLOCK) {
         __syncthreads();
-        {
-            const int jj = jt + tid;
-            float4 *rec = &tile[tid * 3];
-            if (jj < je) {
-                rec[0] = make_float4((float)src.x[0][jj], (float)src.x[1][jj], (float)src.x[2][jj],
-                                     (float)src.m[jj]);
-                rec[1] = make_float4((float)src.v[0][jj], (float)src.v[1][jj], (float)src.v[2][jj],
-                                     (float)src.a[0][jj]);
-                rec[2] = make_float4((float)src.a[1][jj], (float)src.a[2][jj], 0.0f, 0.0f);
-            } else {
-                rec[0] = make_float4(kPadPosF, kPadPosF, kPadPosF, 0.0f);
-                rec[1] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                rec[2] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            }
-        }
+        sp_store(sp_load(src, jt + tid, je), &tile[tid * 3]);
         __syncthreads();
         // by four, so that a record's LDS reads overlap the previous pairs (the
         // lone wave of a small set waited for each: 2048 of 2048 targets 23.8
         // -> 14.5 us, 1000 of 10007 41.5 -> 30.8 us, 10007 of 10007 unchanged)
 #pragma unroll 4
-        for (int q = 0; q < BLOCK; ++q) {
-            const float4 r0 = tile[q * 3], r1 = tile[q * 3 + 1], r2v = tile[q * 3 + 2];
-            const float dx = r0.x - xi[0], dy = r0.y - xi[1], dz = r0.z - xi[2];
-            const float dvx = r1.x - vi[0], dvy = r1.y - vi[1], dvz = r1.z - vi[2];
-            const float dax = r1.w - ai[0], day = r2v.x - ai[1], daz = r2v.y - ai[2];
-            float r2 = fmaf(dz, dz, fmaf(dy, dy, fmaf(dx, dx, eps2)));
-            float mj = r0.w;
-            if (SKIPSELF && (jt + q) == p) {
-                r2 = 1.0f;
-                mj = 0.0f;
-            }
-            // hardware estimate refined by one Newton step
-            const float y0 = __builtin_amdgcn_rsqf(r2);
-            const float rinv = y0 * fmaf(-0.5f * r2 * y0, y0, 1.5f);
-            const float rinv2 = rinv * rinv;
-            const float mr3 = mj * rinv * rinv2;
-            const float alpha = fmaf(dz, dvz, fmaf(dy, dvy, dx * dvx)) * rinv2;
-            const float a3 = 3.0f * alpha;
-            const float wx = fmaf(-a3, dx, dvx), wy = fmaf(-a3, dy, dvy), wz = fmaf(-a3, dz, dvz);
-            const float vvra =
-                fmaf(dz, daz, fmaf(dy, day, fmaf(dx, dax, fmaf(dvz, dvz, fmaf(dvy, dvy, dvx * dvx)))));
-            const float beta = fmaf(alpha, alpha, vvra * rinv2);
-            const float b3 = 3.0f * beta, a6 = a3 + a3;
-            const float ux = fmaf(-a6, wx, fmaf(-b3, dx, dax));
-            const float uy = fmaf(-a6, wy, fmaf(-b3, dy, day));
-            const float uz = fmaf(-a6, wz, fmaf(-b3, dz, daz));
-            acc[0] = fmaf(mr3, dx, acc[0]);
-            acc[1] = fmaf(mr3, dy, acc[1]);
-            acc[2] = fmaf(mr3, dz, acc[2]);
-            acc[3] = fmaf(mr3, wx, acc[3]);
-            acc[4] = fmaf(mr3, wy, acc[4]);
-            acc[5] = fmaf(mr3, wz, acc[5]);
-            acc[6] = fmaf(mr3, ux, acc[6]);
-            acc[7] = fmaf(mr3, uy, acc[7]);
-            acc[8] = fmaf(mr3, uz, acc[8]);
-        }
+        for (int q = 0; q < BLOCK; ++q) sp_add(acc, sp_pair<SKIPSELF>(&tile[q * 3], t, eps2, jt + q));
     }
     if (k < n_act) {
         const int64_t soff = (int64_t)blockIdx.y * slice_stride;
 #pragma unroll
         for (int q = 0; q < 9; ++q) out.p[q][soff + k] = (double)acc[q];
+    }
+}
+
+// The same chains by two waves: of every 8 sources the first wave takes 4 from
+// record to sum, and the other's four, whose terms come through LDS a batch
+// later. The sums' operations and their order are the one-wave kernel's; 57
+// issued a pair instead of 54, but by two waves, and the CUs' shares are even
+// where 1099 lone waves on 1024 SIMDs were not. Bound by LDS now: 40 clocks of
+// its reads and writes a source and chain, four or five chains a CU. One wave and
+// this: n = 8192 142 -> 126 us, 10007 212 -> 191, 16384 509 -> 437, 65536 8.17 ->
+// 6.45 ms (26 to 42 TFLOP/s at 42 operations a pair). Three or five of eight by
+// the second wave: 10007 197 and 208 us; batches of four 199, of sixteen 271.
+// While all chains are resident, six workgroups a CU: 1536 chains (n = 98304)
+// 15.0 -> 13.4 ms, 2048 20.1 -> 27.6 ms.
+constexpr int kSpPairPerCu = 6;
+constexpr int kSpBatch = 8, kSpHalf = 4, kSpOwn = kSpBatch - kSpHalf, kSpTile = 64;
+template <bool SKIPSELF>
+__global__ __launch_bounds__(128) void k_eval_sp_pair(SrcPtrs src,
+                                                      const int32_t *__restrict__ active, int n,
+                                                      int n_act, double eps2_d, int slice_len,
+                                                      OutPtrs out, int64_t slice_stride) {
+    __shared__ float4 tile[2][kSpTile * 3];
+    __shared__ float4 ring4[2][kSpHalf][2][64];  // m r | w u0
+    __shared__ float2 ring2[2][kSpHalf][64];     // u1 u2
+    const int lane = threadIdx.x & 63;
+    const bool adds = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) == 0;
+    const int k = (int)blockIdx.x * 64 + lane;
+    const int kc = k < n_act ? k : n_act - 1;
+    const SpTarget t = sp_target(src, active ? active[kc] : kc);
+    const float eps2 = (float)eps2_d;
+    float acc[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) acc[q] = 0.0f;
+    const int jb = (int)blockIdx.y * slice_len;
+    const int je = min(n, jb + slice_len);
+    auto add_ring = [&](int par) {
+#pragma unroll
+        for (int q = 0; q < kSpHalf; ++q) {
+            const float4 a = ring4[par][q][0][lane], b = ring4[par][q][1][lane];
+            const float2 c = ring2[par][q][lane];
+            sp_add(acc, {a.x, {a.y, a.z, a.w}, {b.x, b.y, b.z}, {b.w, c.x, c.y}});
+        }
+    };
+    SpSource next;
+    if (!adds && jb < je) sp_store(sp_load(src, jb + lane, je), &tile[0][lane * 3]);
+    __syncthreads();
+    int buf = 0;
+    for (int jt = jb; jt < je; jt += kSpTile, buf ^= 1) {
+        if (!adds && jt + kSpTile < je) next = sp_load(src, jt + kSpTile + lane, je);
+#pragma unroll 2
+        for (int b = 0; b < kSpTile / kSpBatch; ++b) {
+            const int j0 = b * kSpBatch;
+            if (adds) {
+                if (b > 0 || jt > jb) add_ring((b + 1) & 1);
+#pragma unroll
+                for (int q = 0; q < kSpOwn; ++q)
+                    sp_add(acc, sp_pair<SKIPSELF>(&tile[buf][(j0 + q) * 3], t, eps2, jt + j0 + q));
+            } else {
+#pragma unroll
+                for (int q = 0; q < kSpHalf; ++q) {
+                    const int j = j0 + kSpOwn + q;
+                    const SpTerms s = sp_pair<SKIPSELF>(&tile[buf][j * 3], t, eps2, jt + j);
+                    ring4[b & 1][q][0][lane] = make_float4(s.m, s.r[0], s.r[1], s.r[2]);
+                    ring4[b & 1][q][1][lane] = make_float4(s.w[0], s.w[1], s.w[2], s.u[0]);
+                    ring2[b & 1][q][lane] = make_float2(s.u[1], s.u[2]);
+                }
+                if (b == kSpTile / kSpBatch - 1 && jt + kSpTile < je)
+                    sp_store(next, &tile[buf ^ 1][lane * 3]);
+            }
+            __syncthreads();
+        }
+    }
+    if (adds) {
+        if (jb < je) add_ring((kSpTile / kSpBatch - 1) & 1);
+        if (k < n_act) {
+            const int64_t soff = (int64_t)blockIdx.y * slice_stride;
+#pragma unroll
+            for (int q = 0; q < 9; ++q) out.p[q][soff + k] = (double)acc[q];
+        }
     }
 }
 
@@ -425,15 +533,19 @@ hipError_t dispatch_ex_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, con
                                 0, out, slice_stride);
 }
 
-hipError_t dispatch_sp(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+hipError_t dispatch_sp(int n_cu, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
                        const int32_t *active, int n, int n_act, double eps2, int slice_len,
                        const OutPtrs &out, int64_t slice_stride) {
-    if (skipself)
-        hipLaunchKernelGGL((k_eval_sp<kSpBlock, true>), grid, dim3(kSpBlock), 0, st, src, active, n,
-                           n_act, eps2, slice_len, out, slice_stride);
-    else
-        hipLaunchKernelGGL((k_eval_sp<kSpBlock, false>), grid, dim3(kSpBlock), 0, st, src, active, n,
-                           n_act, eps2, slice_len, out, slice_stride);
+    auto launch = [&](auto skip) {
+        constexpr bool S = decltype(skip)::value;
+        if ((int64_t)grid.x * grid.y <= (int64_t)kSpPairPerCu * n_cu)
+            hipLaunchKernelGGL((k_eval_sp_pair<S>), grid, dim3(128), 0, st, src, active, n, n_act,
+                               eps2, slice_len, out, slice_stride);
+        else
+            hipLaunchKernelGGL((k_eval_sp<kSpBlock, S>), grid, dim3(kSpBlock), 0, st, src, active, n,
+                               n_act, eps2, slice_len, out, slice_stride);
+    };
+    if (skipself) launch(std::true_type{}); else launch(std::false_type{});
     return hipGetLastError();
 }
 

@@ -246,7 +246,7 @@ hipError_t dispatch_mixed_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, 
 hipError_t dispatch_ex_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
                           const int32_t *active, int n, int n_act, double eps2, int slice_len,
                           const OutPtrs &out, int64_t slice_stride);
-hipError_t dispatch_sp(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
+hipError_t dispatch_sp(int n_cu, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,
                        const int32_t *active, int n, int n_act, double eps2, int slice_len,
                        const OutPtrs &out, int64_t slice_stride);
 
