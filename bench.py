@@ -605,7 +605,7 @@ ADJ_METRIC = "pair-sum passes x N^2 per second, forward sums and their vector-Ja
 
 
 VJP_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "eval_vjp_hbm_traffic.txt")
-VJP_SOURCES = ("adjoint.hip", "device_math.h")
+VJP_SOURCES = ("adjoint.hip", "sym_body.h", "sym_plan.h", "device_math.h")
 
 
 def _vjp_record():
@@ -824,8 +824,8 @@ def run_adjoint(args):
         "peak": FP64_PEAK_TFLOPS,
         "unit": "TFLOP/s",
         "frac": achieved / FP64_PEAK_TFLOPS,
-        "traffic": _vjp_traffic_per_launch(),  # of the k_eval_vjp dispatch alone
-        "kernel": "k_eval_vjp<2, 128, 0> + slice reduction (one h6_evaluate_vjp call)",
+        "traffic": _vjp_traffic_per_launch(),  # of the pair kernel's dispatch alone
+        "kernel": "k_vjp_sym<2> + slot sums (one h6_evaluate_vjp call)",
         "flops_per_pair": VJP_FLOPS_PER_PAIR,
         "flops_convention": "algorithmic: the operations of the factored reverse sweep of one "
                             "pair (forward recompute 44, six dot products and G, G_alpha per "

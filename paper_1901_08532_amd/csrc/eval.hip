@@ -222,10 +222,10 @@ constexpr int64_t kWaveReduceMaxOut = 2048;
 // From this many slices the reduction splits them over waves.
 constexpr int kManyReduceMinSplit = 16;
 // Mixed evaluations of up to this many pairs take the whole-workgroup kernel.
-// Beyond, its third of converted positions a pair more than the tile kernel's
-// two targets a lane tells. Tile / whole workgroups: 33 of 1024 41 / 9.2 us, 300
-// of 10007 42.6 / 15.2, 6000 of 20000 230 / 212, 1000 of 65536 168 / 130, 2000 of
-// 65536 235 / 240, 8192 of 65536 772 / 835 us.
+// Beyond, the tile kernel's two targets a lane, which share each record's LDS
+// reads, tell. Tile / whole workgroups: 33 of 1024 41 / 9.2 us, 300 of 10007
+// 42.6 / 15.2, 6000 of 20000 230 / 212, 1000 of 65536 168 / 130, 2000 of 65536
+// 235 / 240, 8192 of 65536 772 / 835 us.
 constexpr int64_t kWgMaxPairsMixed = 120000000;
 // Active sets up to this size use the whole-workgroup kernel (FP64); beyond,
 // the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets

@@ -42,7 +42,7 @@ CSRC = os.path.join(ROOT, "paper_1901_08532_amd", "csrc")
 # the evaluation VJP kernel's
 EVAL_SOURCES = ("eval_body.h", "eval_mixed_body.h", "device_math.h", "steps_body.h",
                 "blockloop.hip", "eval.hip", "eval_mixed.hip")
-VJP_SOURCES = ("adjoint.hip", "device_math.h")
+VJP_SOURCES = ("adjoint.hip", "sym_body.h", "sym_plan.h", "device_math.h")
 
 
 def eval_sources_sha256(sources=EVAL_SOURCES):
@@ -97,7 +97,7 @@ def _tag(k):
     for pat, tag in (("k_bl_eval<false, false>", "bl_eval_fp64"),
                      ("k_bl_eval<true, false>", "bl_eval_mixed"),
                      ("k_bl_finish", "bl_finish"),
-                     ("k_eval_vjp<2, 128, 0>", "eval_vjp")):
+                     ("k_vjp_sym<2>", "eval_vjp")):
         if pat in k:
             return tag
     return re.sub(r"\W+", "_", k)[:60]
