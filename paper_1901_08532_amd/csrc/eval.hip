@@ -301,8 +301,10 @@ EvalConfig choose_wg(h6_ctx ctx, int order, int precision, int n, int n_act) {
             const int tiles = ceil_div(slice, kWgThreads);
             const int steps = slice / kWgThreads * tgt + ceil_div(slice % kWgThreads, strands * run) * run;
             const float issue = (precision == H6_EX ? 2.6f : 0.196f) * (float)steps;
-            float cost = std::max(c * issue * kWgShare[l], issue + 0.7f * (float)tiles) + 1.2f * c;
-            if (eff > 1) cost += 1.2f + (float)eff * (float)n_act * 3.6e-5f;
+            // a tile's latency; without LDS (kDirectMaxTgt) that of a thread's pairs
+            const float wait = precision == H6_FP64 && order == 2 && tgt <= 2 ? 0.2f * (float)tgt : 0.7f;
+            float cost = std::max(c * issue * kWgShare[l], issue + wait * (float)tiles) + 1.2f * c;
+            if (eff > 1) cost += 2.0f + (float)eff * (float)n_act * 3.6e-5f;
             if (cost < best) {
                 best = cost;
                 cfg.ipl = tgt;

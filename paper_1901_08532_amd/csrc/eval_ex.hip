@@ -211,7 +211,7 @@ template <bool SKIPSELF>
 struct ExOps {
     using Word = float2;  // high and low part
     using Acc = float2;
-    static constexpr int kRun = 1, kMinTgt = 1;
+    static constexpr int kRun = 1, kMinTgt = 1, kDirectMaxTgt = 0;
     using Sum = CompSum;  // slices: FP64
     static constexpr int NF = 10, NREC = 5, NI = 9, NJ = 9, K = 1, kUnroll = 1;
     struct Target {

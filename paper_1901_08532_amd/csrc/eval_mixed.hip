@@ -63,7 +63,7 @@ template <bool SKIPSELF, int RUN>
 struct MixedOps {
     using Word = double;  // x0 x1 | x2 v0 | v1 v2 | (a0, a1) (a2, m) in FP32
     using Acc = float;
-    static constexpr int NREC = 4, NI = 9, kRun = RUN, kMinTgt = kMixedWgMinTgt;
+    static constexpr int NREC = 4, NI = 9, kRun = RUN, kMinTgt = kMixedWgMinTgt, kDirectMaxTgt = 0;
     static constexpr int kUnroll = 1;  // where RUN is 1
     struct Sum {
         double s;

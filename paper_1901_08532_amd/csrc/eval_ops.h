@@ -86,7 +86,7 @@ template <int ORDER, bool SKIPSELF>
 struct EvalOps {
     using Word = double;
     using Acc = double;
-    static constexpr int kRun = 1, kMinTgt = 1;
+    static constexpr int kRun = 1, kMinTgt = 1, kDirectMaxTgt = ORDER == 2 ? 2 : 0;
     using Sum = CompSum;
     static constexpr int NF = ORDER == 1 ? 7 : ORDER == 2 ? 10 : 13;  // x, m, v, a, j
     static constexpr int NREC = Traits<ORDER>::NREC;

@@ -13,7 +13,7 @@
 // busy at n = n_act = 1024). h6_evaluate, this kernel and any slice
 // reduction, before and after: n = n_act = 1024 63 -> 7.8 us, 40 of 4096
 // 41.7 -> 8.6 us, 4096 of 4096 67 -> 40 us, 300 of 65536 73 -> 53 us, 1000 of
-// 65536 137 -> 134 us, 7 of 1024 8.3 -> 6.2 us. The mixed form: 33 of 1024
+// 65536 137 -> 134 us, 7 of 1024 8.3 -> 5.1 us. The mixed form: 33 of 1024
 // 41 -> 9.2 us, 1024 of 1024 67 -> 9.8 us, 4096 of 4096 75 -> 37 us, 1000 of
 // 65536 168 -> 128 us.
 #pragma once
@@ -39,7 +39,8 @@ constexpr int wg_pool_bytes() {
 // Sums of the targets g * TGT .. g * TGT + TGT - 1 (of list; NULL: particles)
 // over the sources [jb, je), into fs[t * NI + q] (workgroup memory, TGT * NI
 // doubles). OPS as in sym_body.h (one(), add(), value()), with load_rec() and
-// pad_rec() for whole records, Acc the type of a strand's running sums, and
+// pad_rec() for whole records, kDirectMaxTgt the largest TGT that goes without
+// LDS tiles, Acc the type of a strand's running sums, and
 // kRun: a strand takes kRun consecutive sources in a row (1, or 8 for the mixed
 // form, whose FP32 sums cover 8 consecutive sources). Every thread of the
 // workgroup calls it; it ends with a barrier.
@@ -63,10 +64,44 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
         acc[q] = A{};
         sum[q] = {};
     }
+    auto flush = [&]() {
+#pragma unroll
+        for (int q = 0; q < NACC; ++q) {
+            OPS::add(sum[q], acc[q]);
+            acc[q] = A{};
+        }
+    };
+    // one or two targets: each thread loads its strand's sources itself, the next
+    // one ahead. A tile of 512 through LDS costs 0.9 us there, two barriers and
+    // the LDS round trip for one or two pairs a thread; with and without: 7 of
+    // 1024 5.7 / 5.1 us, 7 of 1500 7.0 / 5.7, 40 of 2048 7.4 / 6.2, 100 of 4096
+    // 9.4 / 8.6 (fewer slices pay now). With four targets no further gain.
+    constexpr bool kDirect = TGT <= OPS::kDirectMaxTgt;
+    if constexpr (kDirect) {
+        Word2<W> rec[NREC], next[NREC];
+        auto fetch = [&](int j, Word2<W> *r) {
+            if (j < je)
+                ops.load_rec(j, r);
+            else
+                OPS::pad_rec(r);
+        };
+        fetch(jb + s, next);
+        int since = 0;
+#pragma unroll 1
+        for (int j0 = jb; j0 < je; j0 += STR) {
+#pragma unroll
+            for (int q = 0; q < NREC; ++q) rec[q] = next[q];
+            fetch(j0 + STR + s, next);
+            ops.one(rec, tgt, j0 + s == pid, acc);
+            if (++since == kWgFlush) {
+                since = 0;
+                flush();
+            }
+        }
+    }
     auto *tile = static_cast<Word2<W> *>(pool);
-
     int since = 0;
-    for (int jt = jb; jt < je; jt += kWgThreads) {
+    for (int jt = jb; !kDirect && jt < je; jt += kWgThreads) {
         const int cnt = min(kWgThreads, je - jt);
         // the target's own entry (never the padding past a slice's end: a mixed
         // term overflows where a mask makes the radius of 1e15 one)
@@ -93,13 +128,6 @@ __device__ __forceinline__ void wg_sums(const OPS &ops, const int32_t *__restric
             for (int q = 0; q < NREC; ++q) rec[q] = tile[q * kWgThreads + i * STR + s];
             const int e = RUN == 1 ? i * STR + s : (i / RUN * STR + s) * RUN + i % RUN;
             ops.one(rec, tgt, e == own, acc);
-        };
-        auto flush = [&]() {
-#pragma unroll
-            for (int q = 0; q < NACC; ++q) {
-                OPS::add(sum[q], acc[q]);
-                acc[q] = A{};
-            }
         };
         if constexpr (RUN == 1) {
 #pragma unroll OPS::kUnroll
