@@ -221,16 +221,23 @@ hipError_t dispatch_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const 
 constexpr int64_t kWaveReduceMaxOut = 2048;
 // From this many slices the reduction splits them over waves.
 constexpr int kManyReduceMinSplit = 16;
-// Mixed evaluations of up to this many pairs take the whole-workgroup kernel.
-// Beyond, the tile kernel's two targets a lane, which share each record's LDS
-// reads, tell. Tile / whole workgroups: 33 of 1024 41 / 9.2 us, 300 of 10007
-// 42.6 / 15.2, 6000 of 20000 230 / 212, 1000 of 65536 168 / 130, 2000 of 65536
-// 235 / 240, 8192 of 65536 772 / 835 us.
-constexpr int64_t kWgMaxPairsMixed = 120000000;
-// Active sets up to this size use the whole-workgroup kernel (FP64); beyond,
-// the two-targets-per-lane tile kernel is as fast (N = 16384: 8000 targets
-// 252 against 254 us, all 495 against 468).
-constexpr int kWgMaxAct = 8192;
+// Evaluations of up to this many pairs, over up to this many sources, take the
+// whole-workgroup kernel. Beyond, the tile kernel fills the GPU too and is as fast
+// or faster, with two targets a lane that share each record's LDS reads, unless
+// its groups of 64 or 128 targets are padded by 6% more than groups of 32. Tile /
+// whole workgroups, us: FP64 1000 of 20000 123 / 55, 1500 of 65536 255 / 235, 2000
+// of 65536 299 / 305, 8192 of 65536 999 / 1044, 1000 of 131072 300 / 308; padded,
+// 400 of 524288 508 / 468, 500 (512) 550 / 566; 40 of 1000000 171 / 122. Mixed: 33
+// of 1024 41 / 9.2, 300 of 10007 42.6 / 15.2, 6000 of 20000 230 / 212, 1000 of 65536
+// 168 / 130, 2000 of 65536 235 / 240, 8192 of 65536 772 / 835, 100 of 524288 127 / 131.
+constexpr int64_t kWgMaxPairs = 125000000;
+constexpr int kWgMaxSrc = 262144;
+constexpr int kWgAlwaysMax = 64;
+bool wg_wins(int n, int n_act) {
+    if (n_act <= kWgAlwaysMax || (n <= kWgMaxSrc && (int64_t)n * n_act <= kWgMaxPairs)) return true;
+    const int tile = n_act <= 512 ? 64 : 128;
+    return 1.06 * 32.0 * ceil_div(n_act, 32) < (double)tile * ceil_div(n_act, tile);
+}
 // Waves a launch aims to put in flight (256 CUs x 4 SIMDs x 2).
 constexpr int kTargetWaves = 2048;
 // Shortest source slice of the source-parallel kernel (4 sources per lane).
@@ -334,10 +341,10 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
     // (the mixed source-parallel kernel of the smallest sets sums other sources
     // together in FP32, and is as fast)
     const bool forced = order == 2 && eval_shape_forced(ctx);
-    if (precision == H6_FP64 && n_act <= kWgMaxAct && !forced)
+    if (precision == H6_FP64 && !forced && wg_wins(n, n_act))
         return choose_wg(ctx, order, precision, n, n_act);
-    if (precision == H6_MIXED && order == 2 && n_act > kDefaultSmallMax &&
-        (int64_t)n * n_act <= kWgMaxPairsMixed && !forced)
+    if (precision == H6_MIXED && order == 2 && n_act > kDefaultSmallMax && !forced &&
+        wg_wins(n, n_act))
         return choose_wg(ctx, order, precision, n, n_act);
     const int small_max = ctx->cfg_small >= 0 ? ctx->cfg_small : kDefaultSmallMax;
     if (order == 2 && n_act <= small_max) {
