@@ -309,7 +309,8 @@ __device__ __forceinline__ void two_sum(double a, double b, double &s, double &e
 // workgroup's particles are taken by the first slice. Workgroup sums as
 // compensated (hi, lo) trees; the last workgroup adds them in order.
 // Bound by FP64 issue (about 13 operations a pair); with one target a thread
-// the two LDS reads a pair bounded it instead (n = 16384: 101 -> 69 us).
+// the two LDS reads a pair bounded it instead (n = 65536: 1063 -> 938 us; the
+// call at n = 16384 134 -> 116 us, at 1024 54 -> 39 us).
 __global__ __launch_bounds__(kEnergyThreads) void k_energy(h6_state st, int n, double eps2,
                                                            double *partial, unsigned *counter,
                                                            double *out) {

@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("eps", [1e-4, 0.0])
 @pytest.mark.parametrize("n,n_act", [(33, 33), (65, 34), (257, 48), (511, 100), (513, 513),
                                      (1031, 49), (4097, 1000), (20001, 33), (10007, 10007),
-                                     (20001, 5999), (20001, 6000)])
+                                     (20001, 6249), (20001, 6250)])
 def test_evaluation_edges(n, n_act, eps):
     x, v, a, m = plummer_pred(n, 300 + n + n_act, eps * eps)
     act = np.random.Generator(np.random.PCG64(n_act)).choice(n, n_act, replace=False).astype(np.int32)

@@ -25,7 +25,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("eps", [1e-4, 0.0])
 @pytest.mark.parametrize("n,n_act", [(2, 1), (65, 33), (511, 2), (512, 257), (513, 513), (1025, 31),
-                                     (2049, 1000), (4097, 129), (20001, 5), (9001, 3000)])
+                                     (2049, 1000), (4097, 129), (20001, 5), (9001, 3000),
+                                     (12500, 9999), (12500, 10001)])
 def test_evaluation_edges(n, n_act, eps):
     x, v, a, m = plummer_pred(n, 500 + n + n_act, eps * eps)
     rng = np.random.Generator(np.random.PCG64(n_act))
