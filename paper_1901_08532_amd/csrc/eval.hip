@@ -493,6 +493,26 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
     return launch_reduce(ctx, ctx->partial, cfg.n_split, ncomp, out0, n_act, out, 0u, nullptr);
 }
 
+hipError_t launch_ex_chains(h6_ctx ctx, const SrcPtrs &src, int n, const OutPtrs &out) {
+    // the single-precision chains' slices
+    EvalConfig cfg = choose_eval_config(ctx, 2, H6_SP, n, n);
+    const int slice_len = ceil_div(ceil_div(n, cfg.n_split), kSpBlock) * kSpBlock;
+    cfg.n_split = ceil_div(n, slice_len);
+    OutPtrs dst = out;
+    if (cfg.n_split > 1)
+        for (int c = 0; c < 9; ++c) dst.p[c] = ctx->partial + (int64_t)c * n;
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    hipError_t e = ctx->prof ? prof_begin(ctx, &ev0, &ev1) : hipSuccess;
+    if (e == hipSuccess)
+        e = dispatch_ex_chain(self_pair_masked(ctx->eps2, H6_EX),
+                              dim3(ceil_div(n, kSpBlock), cfg.n_split), ctx->stream, src, n,
+                              ctx->eps2, slice_len, dst, (int64_t)9 * n);
+    if (e == hipSuccess && ctx->prof)
+        e = prof_end(ctx, ev0, ev1, 2, cfg, H6_EX, n, (double)n * (double)n);
+    if (e != hipSuccess || cfg.n_split == 1) return e;
+    return launch_reduce(ctx, ctx->partial, cfg.n_split, 9, 0, n, out, 0u, nullptr);
+}
+
 hipError_t launch_reduce(h6_ctx ctx, const double *partial, int n_split, int ncomp, int out0,
                          int n_act, const OutPtrs &out, unsigned acc_mask, const int32_t *list) {
     const int64_t total = (int64_t)ncomp * n_act;

@@ -37,7 +37,7 @@
 // sources of a strand, the steps of a cell, the targets a travelling source
 // meets in a wave; slices are combined in FP64. SP keeps one target per lane
 // over LDS tiles, its slices combined by the common FP64 reduction.
-#include "shared_step_body.h"
+#include "eval_wg_body.h"
 
 namespace h6 {
 namespace {
@@ -178,14 +178,14 @@ __device__ __forceinline__ fpair ds_dot3(const fpair *p, const fpair *q) {
                          ds_mul_raw(p[2], q[2]));
 }
 
-// The vectors of an order-2 pair in double-single: r, w, u and R^-3, with
+// The vectors of an order-2 pair in double-single: w, u, 1/R and 1/R^2, with
 // R^2 = |r|^2 + eps^2, alpha = r.v/R^2, beta = (v.v + r.a)/R^2 + alpha^2,
 // w = v - 3 alpha r, u = a - 6 alpha w - 3 beta r: A = m r/R^3, J = m w/R^3,
 // S = m u/R^3.
-__device__ __forceinline__ fpair pair_ex(const fpair *r, const fpair *v, const fpair *a, fpair r2,
-                                         fpair *w, fpair *u) {
-    const fpair rinv = ds_rsqrt(r2);
-    const fpair rinv2 = ds_sqr(rinv);
+__device__ __forceinline__ void pair_ex(const fpair *r, const fpair *v, const fpair *a, fpair r2,
+                                        fpair *w, fpair *u, fpair &rinv, fpair &rinv2) {
+    rinv = ds_rsqrt(r2);
+    rinv2 = ds_sqr(rinv);
     const fpair alpha = ds_mul(ds_dot3(r, v), rinv2);
     const fpair a3 = ds_mul_f(alpha, 3.0f);
 #pragma unroll
@@ -197,7 +197,6 @@ __device__ __forceinline__ fpair pair_ex(const fpair *r, const fpair *v, const f
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         u[c] = ds_sub_sloppy(ds_sub_sloppy(a[c], ds_mul_raw(a6, w[c])), ds_mul_raw(b3, r[c]));
-    return ds_mul(rinv, rinv2);
 }
 
 // Far, massless padding source: contributes exactly zero.
@@ -245,9 +244,10 @@ struct ExOps {
         }
         t.m = in ? ds_from(src.m[kc]) : fpair{0.0f, 0.0f};
     }
-    // the pair's r, w, u and R^-3
-    __device__ __forceinline__ fpair pair(const Word2<float2> *e, const Target &t, bool self,
-                                          fpair *r, fpair *w, fpair *u, fpair &mj) const {
+    // the pair's r, w, u, 1/R and 1/R^2
+    __device__ __forceinline__ void pair(const Word2<float2> *e, const Target &t, bool self,
+                                         fpair *r, fpair *w, fpair *u, fpair &mj, fpair &rinv,
+                                         fpair &rinv2) const {
         auto f = [&](int q) {
             const float2 d = q & 1 ? e[q >> 1].y : e[q >> 1].x;
             return fpair{d.x, d.y};
@@ -267,7 +267,7 @@ struct ExOps {
             r2 = {1.0f, 0.0f};
             mj = {0.0f, 0.0f};
         }
-        return pair_ex(r, v, a, r2, w, u);
+        pair_ex(r, v, a, r2, w, u, rinv, rinv2);
     }
     static __device__ __forceinline__ void accumulate(float2 *acc, fpair p, const fpair *r,
                                                       const fpair *w, const fpair *u) {
@@ -280,16 +280,31 @@ struct ExOps {
     }
     __device__ __forceinline__ void both(const Word2<float2> *e, const Target &t, float2 *acci,
                                          float2 *accj) const {
-        fpair r[3], w[3], u[3], mj;
-        const fpair r3 = pair(e, t, false, r, w, u, mj);
+        fpair r[3], w[3], u[3], mj, rinv, rinv2;
+        pair(e, t, false, r, w, u, mj, rinv, rinv2);
+        const fpair r3 = ds_mul(rinv, rinv2);
         accumulate(acci, ds_mul(mj, r3), r, w, u);
         accumulate(accj, ds_neg(ds_mul(t.m, r3)), r, w, u);
     }
     __device__ __forceinline__ void one(const Word2<float2> *e, const Target &t, bool self,
                                         float2 *acci) const {
-        fpair r[3], w[3], u[3], mj;
-        const fpair r3 = pair(e, t, SKIPSELF && self, r, w, u, mj);
-        accumulate(acci, ds_mul(mj, r3), r, w, u);
+        fpair r[3], w[3], u[3], mj, rinv, rinv2;
+        pair(e, t, SKIPSELF && self, r, w, u, mj, rinv, rinv2);
+        accumulate(acci, ds_mul(mj, ds_mul(rinv, rinv2)), r, w, u);
+    }
+    // the pair's ten numbers m/R^3, r, w, u as a chain adds them
+    __device__ __forceinline__ void terms(const Word2<float2> *e, const Target &t, bool self,
+                                          float2 *out) const {
+        fpair r[3], w[3], u[3], mj, rinv, rinv2;
+        pair(e, t, SKIPSELF && self, r, w, u, mj, rinv, rinv2);
+        const fpair p = ds_mul(ds_mul(mj, rinv), rinv2);
+        out[0] = make_float2(p.h, p.l);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            out[1 + c] = make_float2(r[c].h, r[c].l);
+            out[4 + c] = make_float2(w[c].h, w[c].l);
+            out[7 + c] = make_float2(u[c].h, u[c].l);
+        }
     }
     static __device__ __forceinline__ double value(float2 x) { return (double)x.x + (double)x.y; }
     static __device__ __forceinline__ void add(Sum &s, float2 x) {
@@ -302,6 +317,92 @@ template <bool SKIPSELF>
 __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_ex_sym(
     SrcPtrs src, SymPlan P, double eps2, double *__restrict__ partial) {
     sym_run(ExOps<SKIPSELF>{src, eps2}, P, partial);
+}
+
+// A target's sums over a slice as one serial chain of double-single additions,
+// for shared steps: the interpolated crackle divides a difference of a by h^3 /
+// 60, so that another order of these additions (1e-14 of a) shows in it, by more
+// the fewer the particles. A workgroup takes one chain of 64 targets: of each 8
+// sources every wave computes one's terms, which go to LDS, and then adds one or
+// two of the nine components of all eight, in source order. Bound by FP32 issue,
+// 740 operations a pair; one wave a chain, with the same additions, left three of
+// four SIMDs idle at n = 1024 (256 chains), and one wave alone issues at 4.8
+// clocks an operation. A shared step, one wave a chain and this: n = 256 92 -> 33
+// us, 1024 96 -> 35, 2048 135 -> 76, 2999 290 -> 152. (Two sets of terms, so that a
+// batch needs one barrier, leave one workgroup a CU: 1024 32, 2048 95 us.)
+constexpr int kChainWaves = 8, kChainTile = 64;
+template <bool SKIPSELF>
+__global__ __launch_bounds__(64 * kChainWaves) void k_ex_chain(SrcPtrs src, int n, double eps2,
+                                                               int slice_len, OutPtrs out,
+                                                               int64_t slice_stride) {
+    using Ops = ExOps<SKIPSELF>;
+    const Ops ops{src, eps2};
+    __shared__ Word2<float2> tile[2][kChainTile][Ops::NREC];
+    __shared__ float2 terms[kChainWaves][10][64];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int k = (int)blockIdx.x * 64 + lane, kc = k < n ? k : n - 1;
+    typename Ops::Target t;
+    ops.load(kc, n, t);
+    fpair acc[2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};  // component w, and 8 (wave 7)
+    const int jb = (int)blockIdx.y * slice_len, je = min(n, jb + slice_len);
+    // word w (and 8 + w) of source lane of the tile at jt
+    const double *f0 = nullptr, *f1 = nullptr;
+#pragma unroll
+    for (int f = 0; f < Ops::NF; ++f) {
+        if (f == w) f0 = ops.field(f);
+        if (f == w + 8) f1 = ops.field(f);
+    }
+    float2 pre[2];
+    auto fetch = [&](int jt) {
+        const int j = jt + lane;
+        pre[0] = j < je ? Ops::word(f0[j]) : Ops::pad(w);
+        if (f1) pre[1] = j < je ? Ops::word(f1[j]) : Ops::pad(w + 8);
+    };
+    auto stage = [&](int b) {
+        float2 *rec = reinterpret_cast<float2 *>(&tile[b][lane][0]);
+        rec[w] = pre[0];
+        if (f1) rec[w + 8] = pre[1];
+    };
+    if (jb < je) {
+        fetch(jb);
+        stage(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int jt = jb; jt < je; jt += kChainTile, buf ^= 1) {
+        const bool more = jt + kChainTile < je;
+        if (more) fetch(jt + kChainTile);
+#pragma unroll 1
+        for (int b = 0; b < kChainTile / kChainWaves; ++b) {
+            const int q = b * kChainWaves + w;
+            float2 x[10];
+            ops.terms(&tile[buf][q][0], t, jt + q == kc, x);
+#pragma unroll
+            for (int f = 0; f < 10; ++f) terms[w][f][lane] = x[f];
+            if (more && b == kChainTile / kChainWaves - 1) stage(buf ^ 1);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < kChainWaves; ++s) {
+                const float2 p = terms[s][0][lane];
+                auto add = [&](fpair &sum, int f) {
+                    const float2 y = terms[s][f][lane];
+                    sum = ds_add_sloppy(sum, ds_mul_raw({p.x, p.y}, {y.x, y.y}));
+                };
+                add(acc[0], 1 + w);
+                if (w == 7) add(acc[1], 9);
+            }
+            __syncthreads();
+        }
+    }
+    if (k < n) {
+        const int64_t soff = (int64_t)blockIdx.y * slice_stride;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            if (q == w) out.p[q][soff + k] = (double)acc[0].h + (double)acc[0].l;
+            if (q == 8 && w == 7) out.p[q][soff + k] = (double)acc[1].h + (double)acc[1].l;
+        }
+    }
 }
 
 // ---------------------------------------------------------------- SP
@@ -515,13 +616,14 @@ void launch_ex_sym_pairs(h6_ctx ctx, const SrcPtrs &src, const SymPlan &P) {
                            P, ctx->eps2, ctx->partial);
 }
 
-hipError_t launch_ex_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
-                                 bool predict, const h6_pred *out, const h6_force *f) {
-    return self_pair_masked(ctx->eps2, H6_EX)
-               ? stepbody::launch_shared_step_ops(ctx, ExOps<true>{src, ctx->eps2}, st, n, dt,
-                                                  predict, out, f)
-               : stepbody::launch_shared_step_ops(ctx, ExOps<false>{src, ctx->eps2}, st, n, dt,
-                                                  predict, out, f);
+hipError_t dispatch_ex_chain(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src, int n,
+                             double eps2, int slice_len, const OutPtrs &out, int64_t slice_stride) {
+    auto launch = [&](auto skip) {
+        hipLaunchKernelGGL((k_ex_chain<decltype(skip)::value>), grid, dim3(64 * kChainWaves), 0, st,
+                           src, n, eps2, slice_len, out, slice_stride);
+    };
+    if (skipself) launch(std::true_type{}); else launch(std::false_type{});
+    return hipGetLastError();
 }
 
 hipError_t dispatch_ex_wg(int tgt, bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src,

@@ -216,18 +216,16 @@ hipError_t launch_eval_sym(h6_ctx ctx, int order, int precision, const SrcPtrs &
                            const OutPtrs &out, bool *done);
 // From these sizes on the third law is the faster evaluation of all particles
 // (whole workgroups and this, us: FP64 n = 4096 45 and 51, 6000 84 and 75; EX
-// n = 1500 42 and 56, 4096 222 and 207); up to the second ones a shared step is
-// one kernel (the last whole round of 16 or 8 targets a workgroup on 256 CUs:
-// FP64 n = 4096 52 us a step and 5000 67 by the third law; EX 2048 77 and 2200
-// 98, in one kernel 135).
-constexpr int kSymMinF64 = 5000, kSymMinEx = 2200;
+// n = 1500 42 and 56, 4096 222 and 207). FP64 and mixed shared steps of up to
+// kOneKernelMax are one kernel (the last whole round of 16 targets a workgroup on
+// 256 CUs: FP64 n = 4096 52 us a step and 5000 67 by the third law). EX ones below
+// kSymStepMinEx take chains (n = 2400 106 us, 2999 152; the third law 104 and 142),
+// whose sums keep their order where few particles let it show in the crackle.
+constexpr int kSymMinF64 = 5000, kSymMinEx = 2200, kSymStepMinEx = 3000;
 // Active sets up to this size use the source-parallel kernel by default.
 constexpr int kDefaultSmallMax = 32;
-constexpr int kOneKernelMaxF64 = 4096, kOneKernelMaxEx = 2048;
+constexpr int kOneKernelMax = 4096;
 inline int sym_min(int precision) { return precision == H6_EX ? kSymMinEx : kSymMinF64; }
-inline int one_kernel_max(int precision) {
-    return precision == H6_EX ? kOneKernelMaxEx : kOneKernelMaxF64;
-}
 int balanced_split(h6_ctx ctx, int waves_per_simd, int block, int n, int blocks_i);
 // Mixed-precision order-2 kernels (eval_mixed.hip), launched with the shape
 // chosen for the FP64 kernels.
@@ -255,8 +253,8 @@ hipError_t launch_predict(h6_ctx ctx, const h6_state *st, int n, int64_t t_tick,
 hipError_t launch_correct(h6_ctx ctx, h6_state *st, const int32_t *active, int n_act,
                           const h6_force *f, int64_t t_next, double dt, const h6_params *prm,
                           bool shared);
-// One shared step of a small system in one kernel (shared_step.hip), FP64,
-// mixed or EX: reads the predicted sources src, corrects st, and either predicts the
+// One shared step of a small system in one kernel (shared_step.hip), FP64
+// or mixed: reads the predicted sources src, corrects st, and either predicts the
 // next step into out or, for the last one, writes the forces to f.
 // shared_step_targets: the targets a workgroup takes.
 int shared_step_targets(h6_ctx ctx, int n);
@@ -264,8 +262,11 @@ hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, int precision, co
                               double dt, bool predict, const h6_pred *out, const h6_force *f);
 hipError_t launch_mixed_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
                                     bool predict, const h6_pred *out, const h6_force *f);
-hipError_t launch_ex_shared_step(h6_ctx ctx, h6_state *st, int n, const SrcPtrs &src, double dt,
-                                 bool predict, const h6_pred *out, const h6_force *f);
+// Double-single chains of all targets (eval_ex.hip): the kernel, and the
+// evaluation with its slice sums.
+hipError_t dispatch_ex_chain(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs &src, int n,
+                             double eps2, int slice_len, const OutPtrs &out, int64_t slice_stride);
+hipError_t launch_ex_chains(h6_ctx ctx, const SrcPtrs &src, int n, const OutPtrs &out);
 hipError_t launch_initial_steps(h6_ctx ctx, h6_state *st, int n, double eta_s, int lev_min,
                                 int lev_max);
 hipError_t launch_next_block(h6_ctx ctx, const h6_state *st, int n, int32_t *active);

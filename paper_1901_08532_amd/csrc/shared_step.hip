@@ -58,7 +58,6 @@ int shared_step_targets(h6_ctx ctx, int n) {
 
 hipError_t launch_shared_step(h6_ctx ctx, h6_state *st, int n, int precision, const SrcPtrs &src,
                               double dt, bool predict, const h6_pred *out, const h6_force *f) {
-    if (precision == H6_EX) return launch_ex_shared_step(ctx, st, n, src, dt, predict, out, f);
     if (precision == H6_MIXED)
         return launch_mixed_shared_step(ctx, st, n, src, dt, predict, out, f);
     return self_pair_masked(ctx->eps2, H6_FP64)
