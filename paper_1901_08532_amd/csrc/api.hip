@@ -810,21 +810,22 @@ int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, co
     if (int rc = check_n(ctx, n)) return rc;
     if (!std::isfinite(dt) || dt <= 0.0 || nsteps < 0) return fail_arg(ctx, "bad dt or step count");
     if (!precision_ok(precision)) return fail_arg(ctx, "bad precision");
-    if (nsteps > 0 && (precision == H6_EX || (precision != H6_SP && !eval_shape_forced(ctx)))) {
+    const bool chains = precision == H6_EX && n < kSymStepMinEx;
+    if (nsteps > 0 && !chains &&
+        (precision == H6_EX || (precision != H6_SP && !eval_shape_forced(ctx)))) {
         if (precision != H6_EX && n <= kOneKernelMax)
             return shared_steps_small(ctx, st, n, pred, f, dt, nsteps, precision);
         SymPlan P;
-        if ((precision == H6_FP64 || (precision == H6_EX && n >= kSymStepMinEx)) &&
-            eval_sym_single(ctx, precision, (int)n, &P))
+        if (precision != H6_MIXED && eval_sym_single(ctx, precision, (int)n, &P))
             return shared_steps_sym(ctx, st, P, pred, f, dt, nsteps, precision);
     }
     for (int64_t k = 0; k < nsteps; ++k) {
         H6_TRY(ctx, launch_predict(ctx, st, (int)n, 0, dt, true, pred), "predict");
         const SrcPtrs src = src_from_pred(pred, st->m);
         H6_TRY(ctx,
-               precision == H6_EX ? launch_ex_chains(ctx, src, (int)n, out_from_force(f))
-                                  : launch_eval(ctx, 2, precision, src, (int)n, nullptr, (int)n,
-                                                out_from_force(f), nullptr),
+               chains ? launch_ex_chains(ctx, src, (int)n, out_from_force(f))
+                      : launch_eval(ctx, 2, precision, src, (int)n, nullptr, (int)n,
+                                    out_from_force(f), nullptr),
                "evaluate");
         H6_TRY(ctx, launch_correct(ctx, st, nullptr, (int)n, f, 0, dt, nullptr, true), "correct");
     }
