@@ -389,7 +389,7 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))
 // of a small system still fill the GPU. Workgroup (x, y) takes tile group x
 // and the y-th part of the chunks. Sums of k are added to the outputs when
 // one part covers all chunks, else they go through the partial sums, as the
-// sums of j do (a slot per tile group).
+// sums of j do (a slot per tile group; large lists in batches whose slots fit).
 //
 // Bound by latency for small blocks, by FP64 issue (150 operations a pair) for
 // large ones. One h6_evaluate_vjp_active call, the two halves before and this:
@@ -410,8 +410,7 @@ __device__ __forceinline__ double ring_next(double v) {
 template <int R, int WK>
 __global__ __launch_bounds__(kActThreads) __attribute__((amdgpu_waves_per_eu(2))) void k_vjp_active(
     SrcPtrs src, CotPtrs cot, int n, const int32_t *__restrict__ list, int n_act, double eps2,
-    int group0, int part_chunks, double *__restrict__ part_j, double *__restrict__ part_k,
-    OutPtrs out) {
+    int part_chunks, double *__restrict__ part_j, double *__restrict__ part_k, OutPtrs out) {
     static_assert(R == 4 || R == 16 || R == 64, "ring of a quad, a row or a wave");
     constexpr int NW = 18;                            // words of a source: x, v, a, g
     constexpr int kSteps = WK == 4 ? R : R / 4;       // steps of a wave per chunk
@@ -420,8 +419,7 @@ __global__ __launch_bounds__(kActThreads) __attribute__((amdgpu_waves_per_eu(2))
     __shared__ double sums[4][10][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = group0 + (int)blockIdx.x;
-    const int kt = (group * WK + (WK == 4 ? wave : 0)) * 64;
+    const int kt = ((int)blockIdx.x * WK + (WK == 4 ? wave : 0)) * 64;
     const int k = kt + lane, kc = k < n ? k : n - 1;
     const int sa = WK == 4 ? 0 : wave * kSteps, sb = sa + kSteps;
     // lane's place in its ring
@@ -1012,8 +1010,6 @@ hipError_t launch_predict_dt_vjp(h6_ctx ctx, h6_state *cot, int n, const h6_pred
 
 hipError_t launch_eval_vjp_active(h6_ctx ctx, const SrcPtrs &src, const double *const *cot, int n,
                                   const int32_t *active, int n_act, const OutPtrs &out) {
-    CotPtrs cp;
-    for (int q = 0; q < 9; ++q) cp.g[q] = cot[q];
     // ring: the least padding that does not multiply the chunks' fixed cost
     const int ring = n_act <= 4 ? 4 : n_act <= 48 ? 16 : 64;
     const int chunks = ceil_div_i(n_act, ring);
@@ -1021,39 +1017,46 @@ hipError_t launch_eval_vjp_active(h6_ctx ctx, const SrcPtrs &src, const double *
     // four tiles a workgroup once they fill the GPU twice over
     const int wk = ring == 64 && (int64_t)ceil_div_i(n, 256) * chunks >= 4 * cu ? 4 : 1;
     const int groups = ceil_div_i(n, 64 * wk);
-    // one part of the chunks per workgroup, or more parts to fill the GPU at
-    // the price of a reduction. Times in us: a step 0.27 alone on its SIMD, 0.9
-    // a chunk for staging and sums, 5 a reduction and 1 per 3 MB it reads. The
-    // tile groups go in batches whose sums of j fit the scratch.
+    // The active particles go in batches, each over all tile groups, whose sums
+    // of j (a slot per group) fit the scratch: the list is cut, never the groups,
+    // which fill the GPU (groups in batches left 8 workgroups to all of 262144
+    // particles, 8.5 s; the list in batches 0.35 s). One part of a batch's chunks
+    // per workgroup, or more parts to fill the GPU at the price of a reduction.
+    // Times in us: a step 0.27 alone on its SIMD, 0.9 a chunk for staging and
+    // sums, 5 a reduction and 1 per 3 MB it reads.
     const double tc = 0.27 * (wk == 4 ? ring : ring / 4) + 0.9;
-    int parts = 1, batch = groups;
+    int parts = 1, batch = 0;  // chunks a batch
     double best = 1e300;
     for (int p = 1; p <= chunks && p <= 64; p *= 2) {
         const int64_t left = ctx->partial_cap - (p > 1 ? (int64_t)p * 10 * n : 0);
-        const int64_t fit = left / ((int64_t)9 * n_act);
+        const int64_t fit = left / ((int64_t)9 * groups * ring);
         if (fit < 1) break;
-        const int bt = (int)std::min<int64_t>(groups, fit);
-        const double one = (double)ceil_div_i((int64_t)bt * p, cu) * ceil_div_i(chunks, p) * tc +
-                           5.0 + 2.4e-5 * bt * (double)n_act;
-        const double t = ceil_div_i(groups, bt) * one + (p > 1 ? 5.0 + 2.7e-5 * p * (double)n : 0.0);
+        const int bt = (int)std::min<int64_t>(chunks, fit);
+        const double one = (double)ceil_div_i((int64_t)groups * p, cu) * ceil_div_i(bt, p) * tc + 5.0 +
+                           2.4e-5 * groups * (double)bt * ring + (p > 1 ? 5.0 + 2.7e-5 * p * (double)n : 0.0);
+        const double t = ceil_div_i(chunks, bt) * one;
         if (t < best) {
             best = t;
             parts = p;
             batch = bt;
         }
     }
-    const int part_chunks = ceil_div_i(chunks, parts);
-    parts = ceil_div_i(chunks, part_chunks);
-    double *part_k = parts > 1 ? ctx->partial : nullptr;
-    double *part_j = ctx->partial + (parts > 1 ? (int64_t)parts * 10 * n : 0);
-    for (int g0 = 0; g0 < groups; g0 += batch) {
-        const int gn = std::min(batch, groups - g0);
-        const dim3 grid(gn, parts);
+    if (batch < 1) return hipErrorInvalidValue;  // not with the scratch of a context (9 n doubles for one chunk)
+    for (int c0 = 0; c0 < chunks; c0 += batch) {
+        const int a0 = c0 * ring, an = std::min(n_act - a0, batch * ring);
+        const int32_t *list = active + a0;
+        CotPtrs cp;
+        for (int q = 0; q < 9; ++q) cp.g[q] = cot[q] + a0;
+        const int bc = ceil_div_i(an, ring);
+        const int part_chunks = ceil_div_i(bc, parts);
+        const int bp = ceil_div_i(bc, part_chunks);
+        double *part_k = bp > 1 ? ctx->partial : nullptr;
+        double *part_j = ctx->partial + (bp > 1 ? (int64_t)bp * 10 * n : 0);
+        const dim3 grid(groups, bp);
 #define H6_ACT(R, W)                                                                            \
     if (ring == R && wk == W)                                                                   \
         hipLaunchKernelGGL((k_vjp_active<R, W>), grid, dim3(kActThreads), 0, ctx->stream, src,  \
-                           cp, n, active, n_act, ctx->eps2, g0, part_chunks, part_j, part_k,    \
-                           out);
+                           cp, n, list, an, ctx->eps2, part_chunks, part_j, part_k, out);
         H6_ACT(4, 1)
         H6_ACT(16, 1)
         H6_ACT(64, 1)
@@ -1061,10 +1064,11 @@ hipError_t launch_eval_vjp_active(h6_ctx ctx, const SrcPtrs &src, const double *
 #undef H6_ACT
         hipError_t e = hipGetLastError();
         // the sums of j, added to the active particles
-        if (e == hipSuccess) e = launch_reduce(ctx, part_j, gn, 9, 0, n_act, out, 0x1ffu, active);
+        if (e == hipSuccess) e = launch_reduce(ctx, part_j, groups, 9, 0, an, out, 0x1ffu, list);
+        if (e == hipSuccess && bp > 1) e = launch_reduce(ctx, part_k, bp, 10, 0, n, out, 0x3ffu, nullptr);
         if (e != hipSuccess) return e;
     }
-    return parts > 1 ? launch_reduce(ctx, part_k, parts, 10, 0, n, out, 0x3ffu, nullptr) : hipSuccess;
+    return hipSuccess;
 }
 
 hipError_t launch_correct_block_vjp(h6_ctx ctx, h6_state *cot, const int32_t *active, int n_act,
