@@ -49,9 +49,14 @@ struct SymPlan {
         const int64_t less = half && I > h ? (int64_t)(I - h) * per_d() : 0;
         return (int64_t)I * full - less;
     }
-    // run holding cell x: runs are [r * cells / runs, (r + 1) * cells / runs)
+    // first cell of run r, and the run holding cell x: the runs are [r * cells / runs,
+    // (r + 1) * cells / runs); in ordered form a run is a superblock's cells (the
+    // products with runs = nsb would leave 64 bits from 3.4e8 particles on)
+    __host__ __device__ int64_t run_start(int r) const {
+        return r * (ordered ? first_cell(1) : cells) / (ordered ? 1 : runs);
+    }
     __host__ __device__ int run_of(int64_t x) const {
-        return (int)(((x + 1) * runs - 1) / cells);
+        return (int)((ordered ? x : (x + 1) * runs - 1) / (ordered ? first_cell(1) : cells));
     }
     // first run of superblock I, and how many touch it
     __host__ __device__ int first_run(int I) const { return run_of(first_cell(I)); }
