@@ -25,13 +25,13 @@ __global__ __launch_bounds__(kSymThreads) __attribute__((amdgpu_waves_per_eu(2))
     sym_run(EvalOps<ORDER, SKIPSELF>{src, eps2}, P, partial);
 }
 
-// One sum of a batch's slots per thread.
+// One sum of a batch's slots per thread, components from c0 on.
 __global__ __launch_bounds__(256) void k_sym_reduce(const double *__restrict__ partial, SymPlan P,
-                                                    int ncomp, int out0, OutPtrs out,
+                                                    int ncomp, int c0, int nc, int out0, OutPtrs out,
                                                     unsigned acc_mask) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= (int64_t)ncomp * P.n) return;
-    const int c = (int)(idx / P.n), k = (int)(idx - (int64_t)c * P.n);
+    if (idx >= (int64_t)nc * P.n) return;
+    const int cl = (int)(idx / P.n), c = c0 + cl, k = (int)(idx - (int64_t)cl * P.n);
     double s;
     sym_sums<1>(partial, P, ncomp, c, k, &s);
     double *dst = &out.p[out0 + c][k];
@@ -120,9 +120,14 @@ SymPlan sym_plan_ordered(int n, int block) {
 
 hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
                              unsigned acc_mask) {
-    const int64_t total = (int64_t)ncomp * P.n;
-    hipLaunchKernelGGL(k_sym_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
-                       ctx->stream, ctx->partial, P, ncomp, out0, out, acc_mask);
+    // a launch holds fewer than 2^32 threads: the largest systems a few components at a time
+    const int most = (int)std::min<int64_t>(ncomp, ((int64_t)1 << 31) / P.n);
+    for (int c0 = 0; c0 < ncomp; c0 += most) {
+        const int nc = std::min(most, ncomp - c0);
+        hipLaunchKernelGGL(k_sym_reduce, dim3((unsigned)(((int64_t)nc * P.n + 255) / 256)),
+                           dim3(256), 0, ctx->stream, ctx->partial, P, ncomp, c0, nc, out0, out,
+                           acc_mask);
+    }
     return hipGetLastError();
 }
 
