@@ -20,6 +20,8 @@ static __device__ __align__(256) double scratch[H6_NOALLOC_SCRATCH_BYTES / sizeo
 
 namespace {
 
+constexpr int64_t kThirdLawScratchMax = (int64_t)1 << 23;
+
 static_assert(sizeof(LoopDesc) <= kHostSlot1 - kHostSlot0 && kHostSlot1 + sizeof(LoopDesc) <= kHostBytes,
               "descriptor slots");
 
@@ -306,10 +308,11 @@ int h6_create(h6_ctx *out, int64_t n_max, double eps, void *hip_stream) {
         return H6_EHIP;
     }
     ctx->n_cu = n_cu > 0 ? n_cu : 256;
-    // partial sums: n_split * ncomp * n_act doubles, n_split * n_act <= cap
-    // (the third-law kernels need three slots of 13 sums a particle, large
-    // systems included; half of that serves every call too, more slowly)
-    int64_t cap_pairs = std::max<int64_t>(5 * n_max, (int64_t)1 << 21);
+    // partial sums: n_split * ncomp * n_act doubles, n_split * n_act <= cap. 18 n_max
+    // serve every call; the third-law kernels take three slots of 13 sums a
+    // particle, 45 n_max with room to spare. Beyond kThirdLawScratchMax particles
+    // (3 GB), where one call over all pairs takes minutes, the memory stays the caller's.
+    int64_t cap_pairs = std::max<int64_t>((n_max <= kThirdLawScratchMax ? 5 : 2) * n_max, (int64_t)1 << 21);
     if (hipMalloc(&ctx->partial, sizeof(double) * 9 * cap_pairs) != hipSuccess) {
         (void)hipGetLastError();
         ctx->partial = nullptr;
@@ -758,7 +761,7 @@ int h6_run_blocks(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred, cons
 // scratch so that the last step's are the caller's, as with separate kernels.
 static int shared_steps_small(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
                               const h6_force *f, double dt, int64_t nsteps, int precision) {
-    h6_pred other;  // 9 n doubles of the partial sums' 18 n_max
+    h6_pred other;  // 9 n doubles of the partial sums' 18 n_max or more
     for (int c = 0; c < 3; ++c) {
         other.x[c] = ctx->partial + c * n;
         other.v[c] = ctx->partial + (3 + c) * n;
