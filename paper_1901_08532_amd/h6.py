@@ -162,7 +162,10 @@ def _ptr(t: torch.Tensor):
 
 def _row_ptrs(t: torch.Tensor, rows: int) -> array:
     """Addresses of the first `rows` rows of t, from one base and stride: as
-    t[k].data_ptr() for each, which costs over a microsecond a row."""
+    t[k].data_ptr() for each, which costs over a microsecond a row and serves
+    sequences of row tensors."""
+    if not isinstance(t, torch.Tensor):
+        return array("Q", [t[k].data_ptr() for k in range(rows)])
     if t.shape[0] < rows:
         raise IndexError("tensor has %d rows, %d needed" % (t.shape[0], rows))
     p, step = t.data_ptr(), t.stride(0) * t.element_size()
