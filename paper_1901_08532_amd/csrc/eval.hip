@@ -233,6 +233,7 @@ constexpr int kManyReduceMinSplit = 16;
 constexpr int64_t kWgMaxPairs = 125000000;
 constexpr int kWgMaxSrc = 262144;
 constexpr int kWgAlwaysMax = 64;
+constexpr int kWgMaxAct = 1 << 27;  // targets of one launch
 bool wg_wins(int n, int n_act) {
     if (n_act <= kWgAlwaysMax || (n <= kWgMaxSrc && (int64_t)n * n_act <= kWgMaxPairs)) return true;
     const int tile = n_act <= 512 ? 64 : 128;
@@ -401,6 +402,18 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
 hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src, int n,
                        const int32_t *active, int n_act, const OutPtrs &out, EvalConfig *used) {
     if (n_act <= 0) return hipSuccess;
+    // whole workgroups of 512 threads for 32 targets pass a launch's 2^32 threads
+    // from 2^28 targets on; only EX takes them at any size
+    if (precision == H6_EX && active && n_act > kWgMaxAct) {
+        hipError_t e = hipSuccess;
+        for (int k0 = 0; k0 < n_act && e == hipSuccess; k0 += kWgMaxAct) {
+            OutPtrs part = out;
+            for (int c = 0; c < 9; ++c) part.p[c] += k0;
+            e = launch_eval(ctx, order, precision, src, n, active + k0,
+                            std::min(kWgMaxAct, n_act - k0), part, used);
+        }
+        return e;
+    }
     // (EX and SP have no forced shapes)
     const bool sym = (precision == H6_EX ||
                       (precision == H6_FP64 && !(order == 2 && eval_shape_forced(ctx)))) &&
