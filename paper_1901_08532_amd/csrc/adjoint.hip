@@ -696,7 +696,7 @@ __global__ __launch_bounds__(256) void k_predict_block_vjp(h6_state cot, int n,
 // per thread over all sources left 192 of 256 CUs idle at n = 16384) and two
 // pairs share an LDS record. The self test is made only in the tiles that
 // hold targets of the group. With
-// GRAD, n = 16384: 986 -> 190 us (25 TFLOP/s at 18 operations a pair, FMA 2).
+// GRAD, n = 16384: 986 -> 205 us (24 TFLOP/s at 18 operations a pair, FMA 2).
 constexpr int kPotThreads = 512;
 constexpr int kPotPerSum = 16;  // strand sums one thread adds in the final reduction
 template <int TG, bool GRAD>
@@ -924,9 +924,12 @@ __global__ __launch_bounds__(256) void k_pot_sums(const double *__restrict__ par
     }
 }
 
-// From this size on each pair once, where one batch of slots holds the sums. The
-// ordered and the third-law form, us: GRAD n = 4096 23 and 34, 6000 48 and 47,
-// 8192 67 and 64; potential 4096 18 and 22, 6000 33 and 30.
+// From this size on each pair once, where one batch of slots holds the sums: up to
+// 91136 particles with GRAD, 137728 without (256 CUs, the scratch of a small
+// context), ordered beyond. The ordered and the third-law form, us: GRAD n = 4096
+// 23 and 34, 6000 48 and 47, 8192 67 and 64; potential 4096 18 and 22, 6000 33 and
+// 30. Either side of the end: GRAD 90000 3520, 95000 6000; potential 130000 4820,
+// 140000 9190.
 constexpr int kPotSymMin = 6000;
 
 // Thread targets TG (a power of two): the rounds of workgroups a CU takes

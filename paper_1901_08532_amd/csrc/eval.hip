@@ -158,24 +158,19 @@ hipError_t dispatch_f64(bool skipself, dim3 grid, hipStream_t st, const SrcPtrs 
     return hipGetLastError();
 }
 
-template <int ORDER>
 hipError_t dispatch_shape(const EvalConfig &cfg, bool skipself, dim3 grid, hipStream_t st,
                           const SrcPtrs &src, const int32_t *active, int n, int n_act,
                           double eps2, int slice_len, const OutPtrs &out, int64_t slice_stride) {
 #define H6_SHAPE(B, I)                                                                          \
     if (cfg.block == B && cfg.ipl == I)                                                         \
-        return dispatch_f64<ORDER, B, I>(skipself, grid, st, src, active, n, n_act, eps2,     \
-                                         slice_len, out, slice_stride);
-    if constexpr (ORDER == 2) {
-        H6_SHAPE(64, 1)
-        H6_SHAPE(128, 1)
-        H6_SHAPE(256, 1)
-        H6_SHAPE(64, 2)
-        H6_SHAPE(128, 2)
-        H6_SHAPE(256, 2)
-    } else {
-        H6_SHAPE(256, 1)
-    }
+        return dispatch_f64<2, B, I>(skipself, grid, st, src, active, n, n_act, eps2,           \
+                                     slice_len, out, slice_stride);
+    H6_SHAPE(64, 1)
+    H6_SHAPE(128, 1)
+    H6_SHAPE(256, 1)
+    H6_SHAPE(64, 2)
+    H6_SHAPE(128, 2)
+    H6_SHAPE(256, 2)
 #undef H6_SHAPE
     return hipErrorInvalidValue;
 }
@@ -338,17 +333,19 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
         cfg.n_split = split < 1 ? 1 : split;
         return cfg;
     }
+    // the start-up passes take the third law from kSymMinF64 particles on (whose
+    // three slots of six sums every scratch holds) and this below
+    if (order != 2) return choose_wg(ctx, order, precision, n, n_act);
     // a launch shape forced by h6_set_eval_config takes the kernels it names
     // (the mixed source-parallel kernel of the smallest sets sums other sources
     // together in FP32, and is as fast)
-    const bool forced = order == 2 && eval_shape_forced(ctx);
+    const bool forced = eval_shape_forced(ctx);
     if (precision == H6_FP64 && !forced && wg_wins(n, n_act))
         return choose_wg(ctx, order, precision, n, n_act);
-    if (precision == H6_MIXED && order == 2 && n_act > kDefaultSmallMax && !forced &&
-        wg_wins(n, n_act))
+    if (precision == H6_MIXED && n_act > kDefaultSmallMax && !forced && wg_wins(n, n_act))
         return choose_wg(ctx, order, precision, n, n_act);
     const int small_max = ctx->cfg_small >= 0 ? ctx->cfg_small : kDefaultSmallMax;
-    if (order == 2 && n_act <= small_max) {
+    if (n_act <= small_max) {
         // source-parallel kernel: one wave per TPW targets
         cfg.kind = 1;
         cfg.block = 64;
@@ -364,36 +361,28 @@ EvalConfig choose_eval_config(h6_ctx ctx, int order, int precision, int n, int n
         return cfg;
     }
     cfg.kind = 0;
-    if (order != 2) {
-        cfg.block = 256;
-        cfg.ipl = 1;
-    } else {
-        // measured on gfx950 at N = 65536: one target per lane in 64-thread
-        // workgroups up to 512 targets, two per lane beyond
-        cfg.block = ctx->cfg_block ? ctx->cfg_block : (n_act <= 16384 ? 64 : 256);
-        cfg.ipl = ctx->cfg_ipl ? (ctx->cfg_ipl > 2 ? 2 : ctx->cfg_ipl) : (n_act <= 512 ? 1 : 2);
-    }
+    // measured on gfx950 at N = 65536: one target per lane in 64-thread
+    // workgroups up to 512 targets, two per lane beyond
+    cfg.block = ctx->cfg_block ? ctx->cfg_block : (n_act <= 16384 ? 64 : 256);
+    cfg.ipl = ctx->cfg_ipl ? (ctx->cfg_ipl > 2 ? 2 : ctx->cfg_ipl) : (n_act <= 512 ? 1 : 2);
     const int per_block = cfg.block * cfg.ipl;
     const int blocks_i = ceil_div(n_act, per_block);
     int split;
-    if (ctx->cfg_split && order == 2) {
+    if (ctx->cfg_split) {
         split = ctx->cfg_split;
     } else {
-        // measured footprints on gfx950: order 2 with one target per lane
-        // <= 128 VGPRs (4 waves per SIMD), two per lane <= 256 (2 waves),
-        // except the mixed form's (FP32 pair terms, <= 128: 4 waves, and
-        // slices enough to fill them, 8% faster at N = 262144); start-up
-        // passes <= 128
-        const int waves_per_simd =
-            (order == 2 && cfg.ipl == 2 && precision != H6_MIXED) ? 2 : 4;
+        // measured footprints on gfx950: one target per lane <= 128 VGPRs (4
+        // waves per SIMD), two per lane <= 256 (2 waves), except the mixed
+        // form's (FP32 pair terms, <= 128: 4 waves, and slices enough to fill
+        // them, 8% faster at N = 262144)
+        const int waves_per_simd = (cfg.ipl == 2 && precision != H6_MIXED) ? 2 : 4;
         split = balanced_split(ctx, waves_per_simd, cfg.block, n, blocks_i);
     }
     const int max_by_tiles = ceil_div(n, cfg.block);
     if (split > max_by_tiles) split = max_by_tiles;
     if (split < 1) split = 1;
     // respect the partial-sum capacity
-    const int ncomp = order == 2 ? 9 : 6;
-    const int64_t cap_split = ctx->partial_cap / ((int64_t)ncomp * (n_act > 0 ? n_act : 1));
+    const int64_t cap_split = ctx->partial_cap / ((int64_t)9 * (n_act > 0 ? n_act : 1));
     if (split > 1 && split > cap_split) split = (int)(cap_split < 1 ? 1 : cap_split);
     cfg.n_split = split;
     return cfg;
@@ -472,7 +461,7 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
         e = dispatch_mixed_wg(cfg.ipl, skipself, dim3(ceil_div(n_act, cfg.ipl), cfg.n_split),
                               ctx->stream, src, active, n, n_act, ctx->eps2, slice_len, dst,
                               slice_stride);
-    } else if (order == 2 && precision == H6_MIXED) {
+    } else if (precision == H6_MIXED) {
         dim3 g = cfg.kind == 1 ? dim3(ceil_div(n_act, cfg.ipl), cfg.n_split) : grid;
         e = dispatch_mixed(cfg, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
                            slice_len, dst, slice_stride);
@@ -491,15 +480,10 @@ hipError_t launch_eval(h6_ctx ctx, int order, int precision, const SrcPtrs &src,
         else
             e = dispatch_wg<3>(cfg.ipl, skipself, g, ctx->stream, src, active, n, n_act, ctx->eps2,
                                slice_len, dst, slice_stride);
-    } else if (order == 1)
-        e = dispatch_shape<1>(cfg, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
-                              slice_len, dst, slice_stride);
-    else if (order == 2)
-        e = dispatch_shape<2>(cfg, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
-                              slice_len, dst, slice_stride);
-    else
-        e = dispatch_shape<3>(cfg, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
-                              slice_len, dst, slice_stride);
+    } else {
+        e = dispatch_shape(cfg, skipself, grid, ctx->stream, src, active, n, n_act, ctx->eps2,
+                           slice_len, dst, slice_stride);
+    }
     if (e == hipSuccess && ctx->prof)
         e = prof_end(ctx, ev0, ev1, order, cfg, precision, n_act, (double)n_act * (double)n);
     if (e != hipSuccess || cfg.n_split == 1) return e;

@@ -33,8 +33,8 @@
 //
 // EX runs in the FP64 evaluation's kernels with its own particles and pairs:
 // all particles by the third law (sym_body.h), active sets by whole workgroups
-// (eval_wg_body.h). Its sums are double-single within a slice: 64 to 128
-// sources of a strand, the steps of a cell, the targets a travelling source
+// (eval_wg_body.h). Its sums are double-single within a slice: 64 sources of a
+// strand, the steps of a cell, the targets a travelling source
 // meets in a wave; slices are combined in FP64. SP keeps one target per lane
 // over LDS tiles, its slices combined by the common FP64 reduction.
 #include "eval_wg_body.h"
@@ -204,7 +204,7 @@ constexpr float kPadPosF = 1.0e18f;
 
 // Particles and pairs of the EX evaluation (sym_body.h, eval_wg_body.h).
 // Bound by FP32 issue: about 720 operations for the terms of one particle and
-// 150 more for both. All particles of n = 4096: 335 -> 200 us
+// 160 more for both. All particles of n = 4096: 335 -> 200 us
 // (155 registers: three waves per SIMD).
 template <bool SKIPSELF>
 struct ExOps {
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(BLOCK) void k_eval_sp(SrcPtrs src, const int32_t *_
 // where 1099 lone waves on 1024 SIMDs were not. Bound by LDS now: 40 clocks of
 // its reads and writes a source and chain, four or five chains a CU. One wave and
 // this: n = 8192 142 -> 126 us, 10007 212 -> 191, 16384 509 -> 437, 65536 8.17 ->
-// 6.45 ms (26 to 42 TFLOP/s at 42 operations a pair). Three or five of eight by
+// 6.45 ms (22 to 30 TFLOP/s at 42 operations a pair). Three or five of eight by
 // the second wave: 10007 197 and 208 us; batches of four 199, of sixteen 271.
 // While all chains are resident, six workgroups a CU: 1536 chains (n = 98304)
 // 15.0 -> 13.4 ms, 2048 20.1 -> 27.6 ms.

@@ -7,7 +7,7 @@
 // pair that is 63 + 9 VALU operations at order 2
 // against 2 x 54 in ordered form; the bound stays FP64 issue. Evaluation of
 // all particles, ordered form and this: n = 8192 139 -> 116 us, 16384 493 ->
-// 364 us, 32768 1902 -> 1335 us, 65536 7585 -> 5200 us (64 TFLOP/s at 78
+// 357 us, 32768 1902 -> 1335 us, 65536 7585 -> 5200 us (64 TFLOP/s at 78
 // operations an ordered pair, 82% of the FP64 vector peak). Both start-up passes: n = 32768 3999 -> 2510 us.
 #include <algorithm>
 
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void k_sym_reduce(const double *__restrict__ p
 }
 
 // Particles of a superblock and the price of a cell. FP64: n = 16384 in 9
-// whole chunks a run takes 352 us, in 17 halves 358; EX, whose FP32 operations
+// whole chunks a run takes 1.6% less than in 17 halves; EX, whose FP32 operations
 // issue faster the more waves there are: a shared step of n = 4096 on two
 // workgroups a CU 243 us, on three 220, 8192 769 and 708.
 constexpr int kEvalBlock = kSymThreads * EvalOps<2, false>::K;

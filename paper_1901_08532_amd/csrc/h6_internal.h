@@ -216,8 +216,11 @@ hipError_t launch_eval_sym(h6_ctx ctx, int order, int precision, const SrcPtrs &
                            const OutPtrs &out, bool *done);
 // From these sizes on the third law is the faster evaluation of all particles
 // (whole workgroups and this, us: FP64 n = 4096 45 and 51, 6000 84 and 75; EX
-// n = 1500 42 and 56, 4096 222 and 207). FP64 and mixed shared steps of up to
-// kOneKernelMax are one kernel (the last whole round of 16 targets a workgroup on
+// n = 1500 42 and 56, 4096 222 and 207). Shared steps take it in two kernels where
+// one batch of slots holds the sums (up to 42496 particles in FP64, 31300 in EX, on
+// 256 CUs with the scratch of a small context), in four beyond: EX n = 33000 10.1 ms
+// a step, 19.0 by chains. FP64 and mixed shared steps of up to kOneKernelMax are
+// one kernel (the last whole round of 16 targets a workgroup on
 // 256 CUs: FP64 n = 4096 52 us a step and 5000 67 by the third law). EX ones below
 // kSymStepMinEx take chains (n = 2400 106 us, 2999 152; the third law 104 and 142),
 // whose sums keep their order where few particles let it show in the crackle.
