@@ -60,7 +60,8 @@ def _log(msg):
 
 
 def _kernel_name(rec, mixed):
-    """Kernel symbol (as rocprofv3 shows it) of an evaluation timing record."""
+    """Kernel symbol (as rocprofv3 shows it, without namespaces) of an evaluation
+    timing record."""
     if rec["kind"] == 2:
         return "k_bl_eval<%s, false>" % ("true" if mixed else "false")
     if rec["kind"] == 1:
@@ -68,7 +69,7 @@ def _kernel_name(rec, mixed):
     if rec["kind"] == 3:
         return "k_eval_sym<2, false>"
     if rec["block"] == 512:
-        return "k_eval_wg<2, %d, false>" % rec["ipl"]
+        return "k_eval_wg<%d, %s>" % (rec["ipl"], "MixedOps<false, 8>" if mixed else "EvalOps<2, false>")
     if mixed:
         return "k_eval_mixed<%d, %d, false>" % (rec["block"], rec["ipl"])
     return "k_eval_f64<2, %d, %d, false>" % (rec["block"], rec["ipl"])
@@ -830,9 +831,12 @@ def run_adjoint(args):
         "flops_convention": "algorithmic: the operations of the factored reverse sweep of one "
                             "pair (forward recompute 44, six dot products and G, G_alpha per "
                             "cotangent 2 x 43, mass weights 9, scalars 12, gradient sums 36, "
-                            "source-cotangent terms 42, target scalar sums 6); FMA 2, rsqrt 1",
+                            "source-cotangent terms 42, target scalar sums 6); FMA 2, rsqrt 1; every "
+                            "ordered pair counted, though the kernel takes each unordered pair once "
+                            "(executed_* count what it does)",
         "executed_flops_per_pair": fpp,
         "executed_tflops": fpp * pairs / t_vjp / 1e12 if fpp is not None else None,
+        "executed_frac": fpp * pairs / t_vjp / 1e12 / FP64_PEAK_TFLOPS if fpp is not None else None,
         "avg_call_us": 1e6 * t_vjp,
     }
 
