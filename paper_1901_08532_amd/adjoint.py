@@ -11,8 +11,8 @@ h6_init_forces_vjp), never from torch autograd of the arithmetic.
 ``hermite_block_run`` does the same for block time steps up to a given
 time: the steps are chosen by the forward run and then held fixed (the
 gradient does not flow through the step choice), and each block is
-reversed with h6_correct_vjp, h6_evaluate_vjp_active (2 n_act n pairs) and
-h6_predict_vjp. ``system_energy`` is the total energy as a differentiable
+reversed with h6_correct_vjp, h6_evaluate_vjp_active (n_act n pairs, each
+visited once) and h6_predict_vjp. ``system_energy`` is the total energy as a differentiable
 function of positions, velocities and masses (h6_energy forward;
 h6_evaluate and h6_potential for its gradient), for energy-based losses.
 

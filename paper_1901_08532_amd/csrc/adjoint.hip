@@ -627,9 +627,13 @@ hipError_t launch_vjp_order(h6_ctx ctx, const SrcPtrs &src, const CotPtrs &cot, 
     bool done = false;
     hipError_t e = sym_batches(ctx, n, kBlock, NOUT, SymCost{48.0f, 3.0f}, 0, out, acc_mask, &done, launch);
     if (e != hipSuccess || done) return e;
-    const SymPlan P = sym_plan_ordered(n, kBlock);
-    e = launch(P);
-    return e != hipSuccess ? e : launch_sym_reduce(ctx, P, NOUT, 0, out, acc_mask);
+    SymPlan P;
+    for (int d = 0; e == hipSuccess && (d == 0 || d < P.nsb); d = P.d1) {
+        P = sym_plan_ordered(n, kBlock, d);
+        e = launch(P);
+        if (e == hipSuccess) e = launch_sym_reduce(ctx, P, NOUT, 0, out, d > 0 ? (1u << NOUT) - 1u : acc_mask);
+    }
+    return e;
 }
 
 // Transpose of the block-step corrector for the active particles, each over

@@ -102,14 +102,14 @@ bool sym_plan(h6_ctx ctx, int n, int block, int ncomp, SymCost cost, int d0, Sym
     return true;
 }
 
-SymPlan sym_plan_ordered(int n, int block) {
+SymPlan sym_plan_ordered(int n, int block, int d0) {
     SymPlan P;
     P.n = n;
     P.block = block;
     P.nsb = (n + block - 1) / block;
     P.sub = 1;
-    P.d0 = 0;
-    P.d1 = P.nsb;
+    P.d0 = d0;
+    P.d1 = std::min(P.nsb, d0 + kOrderedMax);
     P.ordered = 1;
     P.half = 0;
     P.slots_j = 0;

@@ -69,7 +69,8 @@ __device__ __forceinline__ void sym_run(const OPS &ops, const SymPlan &P,
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = P.n, per_d = P.per_d(), part_steps = kSymChunk / P.sub;
-    const int64_t x0 = P.run_start((int)blockIdx.x), x1 = P.run_start((int)blockIdx.x + 1);
+    const int64_t x0 = (int64_t)blockIdx.x * P.cells / P.runs;
+    const int64_t x1 = (int64_t)(blockIdx.x + 1) * P.cells / P.runs;
     if (x0 >= x1) return;  // the whole workgroup
     // the superblock of the first cell
     int I;

@@ -34,7 +34,7 @@ struct SymPlan {
     int nsb;        // superblocks
     int sub;        // parts of a chunk's 64 steps
     int d0, d1;     // offsets d of this batch
-    int ordered;    // 1: d = 0 .. nsb - 1 in ordered form, no source-side sums
+    int ordered;    // 1: offsets up to nsb - 1 in ordered form, no source-side sums
     int half;       // 1: the batch holds d = nsb / 2 of an even nsb
     int runs;       // workgroups
     int slots_j;    // source-side slots (sub for each d >= 1 of the batch)
@@ -49,14 +49,9 @@ struct SymPlan {
         const int64_t less = half && I > h ? (int64_t)(I - h) * per_d() : 0;
         return (int64_t)I * full - less;
     }
-    // first cell of run r, and the run holding cell x: the runs are [r * cells / runs,
-    // (r + 1) * cells / runs); in ordered form a run is a superblock's cells (the
-    // products with runs = nsb would leave 64 bits from 3.4e8 particles on)
-    __host__ __device__ int64_t run_start(int r) const {
-        return r * (ordered ? first_cell(1) : cells) / (ordered ? 1 : runs);
-    }
+    // run holding cell x: runs are [r * cells / runs, (r + 1) * cells / runs)
     __host__ __device__ int run_of(int64_t x) const {
-        return (int)((ordered ? x : (x + 1) * runs - 1) / (ordered ? first_cell(1) : cells));
+        return (int)(((x + 1) * runs - 1) / cells);
     }
     // first run of superblock I, and how many touch it
     __host__ __device__ int first_run(int I) const { return run_of(first_cell(I)); }
@@ -118,8 +113,10 @@ __device__ __forceinline__ void sym_sums(const double *__restrict__ partial, con
 // The next batch from offset d0 on, for ncomp sums a particle; false at the
 // end, or at d0 = 0 where the slots do not suffice.
 bool sym_plan(h6_ctx ctx, int n, int block, int ncomp, SymCost cost, int d0, SymPlan *plan);
-// The ordered form (one slot).
-SymPlan sym_plan_ordered(int n, int block);
+// The ordered form (one slot) from offset d0 on, kOrderedMax offsets at most: a run is
+// a superblock there, and cells * runs stays within 64 bits at every size.
+constexpr int kOrderedMax = 1024;
+SymPlan sym_plan_ordered(int n, int block, int d0);
 hipError_t launch_sym_reduce(h6_ctx ctx, const SymPlan &P, int ncomp, int out0, const OutPtrs &out,
                              unsigned acc_mask);
 

@@ -118,3 +118,18 @@ def test_energy_gradient_and_active_gradient(n, per):
         got.append((G[0:3], G[3:6], gm, GP[0:3], GP[3:6], GP[6:9], gp))
     for p, q in zip(*got):
         assert float((p - q).abs().max()) <= 1e-11 * float(q.abs().max())
+
+
+def test_ordered_gradient_in_batches():
+    # more than 1024 superblocks of 256: the ordered form in two batches of offsets
+    n = 270_001
+    g = torch.Generator(device=DEV).manual_seed(n)
+    P, CF = (torch.randn((9, n), generator=g, device=DEV, dtype=torch.float64) for _ in range(2))
+    m = torch.rand(n, generator=g, device=DEV, dtype=torch.float64) / n
+    got = []
+    for ctx in (_context(n, 1e-2, 10), h6.Context(n, 1e-2)):
+        GP, gm = torch.full_like(P, float("nan")), torch.zeros_like(m)
+        ctx.h6_evaluate_vjp(P, m, CF, GP, gm)
+        got.append((GP[0:3], GP[3:6], GP[6:9], gm))
+    for p, q in zip(*got):
+        assert float((p - q).abs().max()) <= 1e-11 * float(q.abs().max())

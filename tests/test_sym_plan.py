@@ -21,10 +21,11 @@ using namespace h6;
 static void runs_of_plan(const SymPlan &P, int ncomp, int64_t cap) {
     const int64_t slots = cap / ((int64_t)ncomp * P.n);
     CHECK(P.first_cell(0) == 0 && P.first_cell(P.nsb) == P.cells && P.cells > 0);
-    CHECK(P.run_start(0) == 0 && P.run_start(P.runs) == P.cells);
+    auto start = [&](int64_t r) { return r * P.cells / P.runs; };
+    CHECK(start(0) == 0 && start(P.runs) == P.cells && P.runs > 0);
     const int step = P.runs > 4096 ? P.runs / 4096 : 1;
     for (int64_t r = 0; r < P.runs; r += step) {
-        const int64_t a = P.run_start((int)r), b = P.run_start((int)r + 1);
+        const int64_t a = start(r), b = start(r + 1);
         CHECK(a < b && a >= 0 && b <= P.cells);
         CHECK(P.run_of(a) == r && P.run_of(b - 1) == r);
     }
@@ -37,7 +38,7 @@ static void runs_of_plan(const SymPlan &P, int ncomp, int64_t cap) {
     if (P.ordered) {
         CHECK(P.runs == P.nsb);
         for (int64_t I = 0; I < P.nsb; I += sstep)
-            CHECK(P.first_run((int)I) == I && P.run_count((int)I) == 1 && P.run_start((int)I) == P.first_cell((int)I));
+            CHECK(P.first_run((int)I) == I && P.run_count((int)I) == 1 && start(I) == P.first_cell((int)I));
     }
 }
 
@@ -77,9 +78,15 @@ int main() {
                 }
     for (int64_t n : {(int64_t)1, (int64_t)256, (int64_t)1000, (int64_t)350000000, (int64_t)1 << 30})
         for (int ncomp : {7, 10, 13}) {
-            const SymPlan P = sym_plan_ordered((int)n, 256);
             const int64_t cap = 18 * n;
-            runs_of_plan(P, ncomp, cap);
+            const int nsb = (int)((n + 255) / 256);
+            int d = 0;
+            while (d < nsb) {
+                const SymPlan P = sym_plan_ordered((int)n, 256, d);
+                CHECK(P.d0 == d && P.d1 > d && P.d1 <= nsb && P.nsb == nsb);
+                if (d == 0 || P.d1 == nsb || d % 1000 == 0) runs_of_plan(P, ncomp, cap);
+                d = P.d1;
+            }
         }
     // third law at the largest sizes, in the smaller scratch
     for (int64_t n : {(int64_t)350000000, (int64_t)1 << 30}) {
