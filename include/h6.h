@@ -66,7 +66,7 @@ enum {
 enum {
     H6_FP64 = 0,  /* all pair arithmetic and sums in IEEE double */
     H6_MIXED = 1, /* double position and velocity differences and accumulators,
-                     float pair math */
+                     float pair math (block steps: see h6_run_blocks) */
     H6_EX = 2,    /* double-single ("float-float") pair arithmetic and
                      per-slice sums, float operations only */
     H6_SP = 3     /* single-precision pair arithmetic and per-slice sums */
@@ -126,7 +126,8 @@ int h6_create(h6_ctx *ctx, int64_t n_max, double eps, void *hip_stream);
 /* Free the context's scratch and the context. NULL is accepted. */
 int h6_destroy(h6_ctx ctx);
 
-/* Change the stream later calls enqueue on. */
+/* Change the stream later calls enqueue on. Calls share the context's scratch:
+ * work on the new stream has to be ordered after the old one's. */
 int h6_set_stream(h6_ctx ctx, void *hip_stream);
 
 /*
@@ -281,6 +282,15 @@ int h6_block_step(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
  * finishing the one before); from the host loop, the last block's own
  * predicted arrays.
  *
+ * A run takes as many blocks as its shortest steps ask for, up to one per
+ * 2^-lev_max. In H6_MIXED the float noise of the accelerations, which the
+ * corrector's interpolation differentiates, can rarely (in about one of a
+ * hundred samples of a cluster with a mass spectrum and hard binaries, one
+ * sync interval each) make a particle far below its natural step ask for ever
+ * smaller ones, down to 2^-lev_max: the run then takes a block per 2^-lev_max
+ * and returns H6_EDTMIN. A lev_max a few levels above the finest step in use
+ * bounds its length.
+ *
  * Both loops take the same block sequence; the evaluation shapes (and
  * hence last-bit rounding) may differ. Errors: as h6_block_step; H6_ESTATE
  * if the device loop's list bookkeeping ever went out of range (an
@@ -290,7 +300,8 @@ int h6_run_blocks(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
                   const h6_force *f, int32_t *active, const h6_params *prm,
                   int64_t t_end, h6_run_stats *stats);
 
-/* nsteps shared steps of length dt over all n particles (asynchronous). */
+/* nsteps shared steps of length dt over all n particles (asynchronous). On
+ * return pred and f hold the last step's predicted arrays and forces. */
 int h6_shared_steps(h6_ctx ctx, h6_state *st, int64_t n, const h6_pred *pred,
                     const h6_force *f, double dt, int64_t nsteps,
                     int precision);
@@ -372,9 +383,8 @@ int h6_init_forces_vjp(h6_ctx ctx, const h6_state *st, int64_t n,
  * cotangents of their evaluated a, j, s by rank (length n_act), and the
  * sources are all n particles (predicted src, masses m). ADDS the
  * cotangents of the predicted x, v, a of every particle to grad_src and of
- * the masses to grad_m (both length n). Work: about 2 n_act n pairs (each
- * pair's source part over the active sources for every particle, then its
- * target part over all sources for the active ones); self pairs skipped.
+ * the masses to grad_m (both length n). Work: n_act n pairs, each visited
+ * once for both particles' parts; self pairs skipped.
  * Active entries must be distinct and in [0, n) (not checked on the
  * device). n_act == 0 is a no-op. Errors: H6_EINVAL.
  */
@@ -462,7 +472,8 @@ typedef struct {
                        targets each); 1: source-parallel small-set kernel;
                        2: evaluation kernel of the device-resident loop (its
                        shape is chosen per block on the device); 3: all
-                       particles by the third law; 4: the loop's finishing kernel (on = 2) */
+                       particles by the third law; 4: the loop's finishing kernel (on = 2).
+                       A shared step taken in one kernel counts whole (kind 0, block 512) */
     int block, ipl; /* launch shape of the instantiation (kind 2: 64, 2;
                        kind 4: 0, 0) */
     int precision;  /* H6_FP64, H6_MIXED, H6_EX or H6_SP */
