@@ -757,9 +757,10 @@ __global__ __launch_bounds__(kPotThreads) __attribute__((amdgpu_waves_per_eu(4))
                     double r2 = fma(dz, dz, fma(dy, dy, fma(dx, dx, eps2)));
                     double mj = zm.y;
                     if (decltype(test_self)::value) {
-                        const bool self = jt + e == id[u];
-                        r2 = self ? 1.0 : r2;
-                        mj = self ? 0.0 : mj;
+                        // (the padding too: a lone particle may be at infinity)
+                        const bool none = jt + e == id[u] || jt + e >= n;
+                        r2 = none ? 1.0 : r2;
+                        mj = none ? 0.0 : mj;
                     }
                     const double rinv = rsqrt_f64(r2);
                     if constexpr (GRAD) {
